@@ -147,7 +147,7 @@ def kernel_source_hash() -> str:
     import re
     csrc = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2306_08881_amd", "csrc")
     h = hashlib.sha256()
-    for f in ("kernels.hip", "wide.hip", "device.hpp", "acp_internal.hpp", "plan.cpp", "probe.hip"):
+    for f in ("kernels.hip", "lowrank.hip", "wide.hip", "device.hpp", "acp_internal.hpp", "plan.cpp", "probe.hip"):
         text = open(os.path.join(csrc, f), encoding="utf-8").read()
         text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
         lines = (re.sub(r"//.*", "", ln).rstrip() for ln in text.splitlines())

@@ -5,8 +5,9 @@
 //   E arena   fp32, one slot per gradient-bucket element (vector slots unused); the E of a
 //             matrix sits at its bucket's E base + its offset in the gradient bucket.  After
 //             a Q-step it holds F = M' and E = F - P_hat Q_loc^T is implied (deferred).  After
-//             a P-step of rank >= 8 it holds X = M' and E = X - P_loc Q_hat^T is implied
-//             (P-deferred); after a P-step of rank <= 4 it holds E itself.
+//             a P-step of rank >= 8, or of rows longer than kFusedCols, it holds X = M' and
+//             E = X - P_loc Q_hat^T is implied (P-deferred); after another P-step it holds E
+//             itself.
 //   factors   fp32 per compressed matrix: P (n x r), Ph (n x r), Pl (n x r), Q (m x r),
 //             Qh (m x r), Ql (m x r), all row-major.  P / Q hold the aggregated factor of
 //             the last step that produced it, Ph / Qh the orthogonalised factors, Pl / Ql the
@@ -15,7 +16,8 @@
 //             factor that the next step orthogonalises.
 //   gpart     fp64 Gram partial sums, r x r per slice of factor rows (factors of more than one
 //             slice only).
-//   qpart     fp32 Q-step partial products, per row chunk: m_pad x r.
+//   qpart     fp32 Q-step partial products, per row chunk: m_pad x r (in a P-step of rows longer
+//             than kFusedCols, the column blocks' shares of P: n x r each).
 //   tables    MatDesc[], VecDesc[], Tile[] for every launch.
 // No kernel communicates across workgroups: every reduction that spans workgroups is
 // finished by a later kernel in the same stream.
@@ -28,7 +30,7 @@ namespace acp {
 constexpr int kBlock = 256;       // threads per workgroup (4 waves of 64)
 constexpr int kWave = 64;
 constexpr double kTau = 1e-4;     // rank-deficiency threshold of orth()
-constexpr int kMaxTileRows = 256; // rows per tile of the rank-4 row kernels (factor rows in LDS)
+constexpr int kMaxTileRows = 256; // rows per tile of the low-rank row kernels (factor rows in LDS)
 // K_QFIN entries (e = column * r + rank, over the whole matrix) per tile: one thread per entry
 // for up to 8 row chunks, 4 threads for up to 32, 8 for up to 64 (so that no thread adds more
 // than 8 chunks, all requested at once), 16 threads beyond
@@ -36,9 +38,11 @@ constexpr int qfin_entries(int32_t q_chunks) {
   return q_chunks <= 8 ? 1024 : (q_chunks <= 32 ? 64 : (q_chunks <= 64 ? 32 : 16));
 }
 constexpr int64_t kMaxCols = int64_t(1) << 24;  // columns of a compressed matrix, at most
-constexpr int kSmallRows = 256;  // T_SMALL matrices: rows (their P rows sit in LDS)
-constexpr int kSmallCols = 512;  // T_SMALL matrices: columns (their Q rows sit in LDS)
-constexpr int kReconRows = 4;   // rows per tile of the rank-4 decompress
+constexpr int kFusedCols = 5120; // longest row of the one-pass P-step up to rank 4 (k_pfused)
+constexpr int kReconRows = 4;   // rows per tile of the decompress up to rank 4
+// rows a P-step workgroup of column class S handles at a time, up to rank 4: as many as the
+// registers hold beside the class's factor rows (4 S r floats each of Qh and Q_loc)
+constexpr int pstep_rows(int r, int S) { return S == 1 ? 8 : S == 2 && r <= 2 ? 4 : S <= 4 ? 2 : r <= 2 ? 2 : 1; }
 constexpr int kQRows = 256;       // rows per Q-step row chunk (at most; the chunk's Ph rows sit in LDS)
 // Size of the static device array that holds one bucket's Q-step partials for the compress entry
 // point that allocates nothing (acp_compress_noalloc); a bucket that needs more is refused.
@@ -58,11 +62,12 @@ struct MatDesc {
   int32_t q_chunks;   // number of Q-step row chunks
   int32_t q_cb;       // Q-step column-block width
   int32_t fact_rows;  // factor rows per Gram slice
-  int32_t scls;       // column class S of the rank-4 kernels (64 S float4 groups per wave)
+  int32_t scls;       // column class S up to rank 4 (64 S float4 groups per wave; 0: narrow rows)
   int32_t bucket;     // bucket index
   int32_t fact_slices_p, fact_slices_q;  // Gram slices of the P / Q factor rows
   int32_t q_grp;      // Q-step row chunks whose rows interleave (see q_chunk_rows)
   int32_t tid;        // registration index of the tensor (keys the no-reuse draws)
+  int32_t xhold;      // a P-step leaves X in the arena (rank >= 8, rows longer than kFusedCols)
 };
 
 // the planner (host compiler) and the kernels (hipcc) share the chunk geometry below
@@ -95,14 +100,12 @@ struct VecDesc {
   int32_t bucket, pad;
 };
 
-enum TileKind : int32_t { T_ROWS = 0, T_FACT = 1, T_VEC = 2, T_QTILE = 3, T_SROWS = 4, T_SMALL = 5 };
+enum TileKind : int32_t { T_ROWS = 0, T_FACT = 1, T_VEC = 2, T_QTILE = 3, T_SROWS = 4 };
 
 // kind T_ROWS : idx = matrix, a = first row, b = row count (K_APPLY from kApplyMfmaRank on: + 65536 x
 //               the 64-column block of Xh)
-// kind T_SMALL: idx = matrix, the whole matrix in one workgroup (rank 4, small matrices whose
-//               rows are not 16-byte aligned: n <= kSmallRows, m <= kSmallCols)
-// kind T_SROWS: idx = matrix, a = first row, b = cb | stride << 4 | count << 16: columns
-//               [1024 cb, 1024 cb + 1024) of rows a + k stride, k < count
+// kind T_SROWS: idx = matrix, a = first row, b = srows_pack(cb, stride, count): columns
+//               [1024 cb, 1024 cb + 1024) of rows a + k stride, k < count (k_pfused: all columns)
 // kind T_FACT : idx = matrix, a = slice (+ 65536 x part of the Gram blocks from kBlockedRank
 //               on: gram_parts(r) parts), b = slice count; K_GSUM: a = entry block of
 //               kGsumEntries, b = slice count
@@ -115,15 +118,24 @@ struct Tile {
   int32_t kind, idx, a, b;
 };
 
+// T_SROWS: 15 bits of column block (kMaxCols / 1024 = 2^14 of them), 4 of stride (at most 8), 9 of
+// row count (at most kMaxTileRows)
+constexpr int32_t srows_pack(int64_t cb, int64_t stride, int64_t count) {
+  return static_cast<int32_t>(cb | (stride << 15) | (count << 19));
+}
+constexpr int32_t srows_block(int32_t b) { return b & 0x7fff; }
+constexpr int32_t srows_stride(int32_t b) { return (b >> 15) & 0xf; }
+constexpr int32_t srows_count(int32_t b) { return b >> 19; }
+
 enum KernelId : int32_t {
-  K_APPLY = 0,   // Xh = X W (orthogonalise the reused factor), general path
-  K_PFUSED,      // P-step, one pass (r = 4): Qh = Q W, P = M' Qh, E = M' - P Qh^T, vectors packed
-  K_PROW,        // P-step, general: P = M' Qh, one workgroup per row
-  K_EUPD,        // P-step, general: E = M' - P Qh^T
-  K_QSTEP,       // Q-step: F = M' written back, per-chunk partials of M'^T Ph, vectors packed
+  K_APPLY = 0,   // Xh = X W (orthogonalise the reused factor), ranks >= 8
+  K_PFUSED,      // P-step, r <= 4, one pass: Qh = Q W, P = M' Qh, E = M' - P Qh^T, vectors packed
+  K_PWIDE,       // P-step, r <= 4, rows longer than kFusedCols: X = M' written, shares of P
+  K_PFIN,        // P-step, r <= 4: P = sum of K_PWIDE's shares -> factor buffer and Pl
+  K_QSTEP,       // Q-step, r <= 4: F = M' written back, per-chunk partials of M'^T Ph, vectors packed
+                 // (variant 1: the rows K_PWIDE takes)
   K_QFIN,        // Q-step: Q_loc = sum of the chunk partials -> factor buffer and Ql
-  K_RECON,       // decompress, general: M_hat = P Q^T / p; factor tiles; vectors / p
-  K_RECON4,      // decompress, r = 4 register-resident columns; factor tiles; vectors / p
+  K_RECON4,      // decompress, r <= 4: M_hat = P Q^T / p; factor tiles; vectors / p
   K_FACT,        // factor tiles alone: Gram -> W (after bind / restore)
   K_CHOL,        // sum of a factor's Gram partials (more than one slice) -> W
   K_EMAT,        // materialise E into a bucket-shaped buffer
@@ -132,8 +144,8 @@ enum KernelId : int32_t {
   K_WQSTEP,      // Q-step, ranks 8..32 (MFMA): F = M' written, per-chunk partials of F^T Ph
   K_WRECON,      // decompress, ranks 8..32 (MFMA): M_hat = A B^T / p
   K_WFACT,       // decompress, ranks 8..32: factor tiles and vectors / p
-  // tile-size classes of the rank-4 narrow-row tiles (rows of at most 512 columns: several rows
-  // per wave); they run inside the K_PFUSED (S = 1), fused K_QSTEP and K_RECON4 launches
+  // tile-size classes of the narrow-row tiles up to rank 4 (rows of at most 512 columns: several
+  // rows per wave); they run inside the K_PFUSED (S = 1), K_QSTEP and K_RECON4 launches
   K_PNARROW,
   K_QNARROW,
   K_RNARROW,
@@ -142,8 +154,8 @@ enum KernelId : int32_t {
   K_IMAGE,       // Power-SGD: M' = M + E into the E arena (raw vectors too), W = I
 };
 
-// Narrow rows (r = 4, m / 4 = m4 <= 128 float4 groups): L lanes per row (16, 32 or 64), G float4
-// groups per lane (1 or 2); the launch variant is (L << 4) | G.
+// Narrow rows (r <= 4, m4 = ceil(m / 4) <= 128 float4 groups): L lanes per row (16, 32 or 64), G
+// float4 groups per lane (1 or 2); the variant is (L << 4) | G.
 constexpr int32_t narrow_variant(int32_t m4) {
   return m4 <= 16 ? (16 << 4) | 1 : m4 <= 32 ? (32 << 4) | 1 : m4 <= 64 ? (64 << 4) | 1 : (64 << 4) | 2;
 }
@@ -177,8 +189,6 @@ constexpr int kDrawRows = 256;     // K_DRAW factor rows per tile
 // K_IMAGE rows per tile: their row-factor rows sit in LDS (at most 16 KB)
 constexpr int image_rows(int32_t r) { return r <= 64 ? 64 : 4096 / r; }
 
-// K_QSTEP variants: column slots per lane | kQFused when the kernel also orthogonalises P
-constexpr int32_t kQFused = 16;
 // K_PFUSED variant bits: S = 1 on three waves, for rows of 516 to 768 columns; S = 2 on eight
 // waves, for rows of 3076 to 4096 columns
 constexpr int32_t kThreeWaves = 32;
@@ -189,8 +199,8 @@ constexpr int32_t kFactFromBuffer = 2;
 
 struct Launch {
   int32_t kernel;
-  int32_t variant;   // kernel-specific: column class S (K_PFUSED, K_RECON4), vector width
-                     // (K_QSTEP, K_RECON), factor P=0 / Q=1 (K_APPLY, K_FACT)
+  int32_t variant;   // kernel-specific: column class S (K_PFUSED), rows of K_PWIDE (K_QSTEP),
+                     // factor P=0 / Q=1 (K_APPLY, K_FACT)
   int64_t tile_off;  // first tile in the tile table
   int32_t ntiles;
   int32_t family;    // ACP_KERNEL_* family (host-side profiling)

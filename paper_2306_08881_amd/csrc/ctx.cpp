@@ -28,8 +28,8 @@ struct acp_ctx {
   int device = -1;
   float* scratch = nullptr;     // the bound device's static Q-step scratch (acp_compress_noalloc)
   std::string scratch_err;      // why it is null after a bind
-  // a second stream (default priority) and fork / join events on the bound device: the rank-4
-  // P-step's class launches after the first run there, beside it
+  // a second stream (default priority) and fork / join events on the bound device: the P-step's
+  // class launches up to rank 4 after the first run there, beside it
   hipStream_t side = nullptr;
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   std::vector<int64_t> last_step;   // per bucket: last completed step
@@ -53,14 +53,15 @@ namespace {
 constexpr uint64_t kMagic = 0x3153504341ull;  // "ACPS1"
 constexpr int64_t kVersion = 1;
 
-// What the E arena of a bucket holds: E itself, F = M' after a Q-step (E = F - Ph Ql^T), or
-// X = M' after a P-step of rank >= 8 (E = X - Pl Qh^T).
+// What the E arena of a bucket holds: E itself, F = M' after a Q-step (E = F - Ph Ql^T), or, after
+// a P-step of a bucket with such matrices, X = M' for those whose P-step leaves X
+// (MatDesc::xhold; E = X - Pl Qh^T) and E itself for the others.
 constexpr uint8_t kExplicit = 0, kHoldsF = 1, kHoldsX = 2;
 
-uint8_t form_after_compress(const acp_ctx* c, int64_t step) {
+uint8_t form_after_compress(const acp_ctx* c, int32_t b, int64_t step) {
   if (!c->plan.ef) return kExplicit;
   if (!(step & 1)) return kHoldsF;
-  return c->plan.rank >= acp::kWideRank ? kHoldsX : kExplicit;
+  return c->plan.buckets[b].xhold ? kHoldsX : kExplicit;
 }
 
 // the masks of KArgs for bucket slot i (bucket base + i)
@@ -107,7 +108,7 @@ bool overlaps(const void* x, int64_t x_floats, const void* y, int64_t y_floats) 
   return a < b + y_floats * 4 && b < a + x_floats * 4;
 }
 
-// A run of two or more consecutive rank-4 P-step launches (K_PFUSED: one per column class, on
+// A run of two or more consecutive P-step launches up to rank 4 (K_PFUSED: one per column class, on
 // disjoint matrices, none reading what another writes) from launch i on, each moving less than
 // kOverlapBytes: their tails are a large part of their time, which running them side by side
 // fills (larger launches slowed each other down when run so: BERT-base and BERT-large).
@@ -287,7 +288,7 @@ acp_status compress_bucket(acp_ctx* c, int64_t step, int32_t b, const float* gra
   const acp_status st = run(c, bk.compress[step & 1], a, static_cast<hipStream_t>(stream), o);
   if (st != ACP_OK) return st;
   c->pending[b] = step;
-  c->deferred[b] = form_after_compress(c, step);
+  c->deferred[b] = form_after_compress(c, b, step);
   c->applied[b] = 0;
   return ACP_OK;
 }
@@ -668,7 +669,7 @@ acp_status acp_compress_all(acp_ctx* c, int64_t step, const float* const* grads,
   }
   for (int32_t b = 0; b < nb; ++b) {
     c->pending[b] = step;
-    c->deferred[b] = form_after_compress(c, step);
+    c->deferred[b] = form_after_compress(c, b, step);
     c->applied[b] = 0;
   }
   return ACP_OK;

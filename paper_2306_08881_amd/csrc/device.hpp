@@ -14,55 +14,17 @@ namespace {
 
 __device__ inline int tid() { return static_cast<int>(threadIdx.x); }
 
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 __device__ inline double wave_sum(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
 
-__device__ inline float4 wave_sum(float4 v) {
-  v.x = wave_sum(v.x);
-  v.y = wave_sum(v.y);
-  v.z = wave_sum(v.z);
-  v.w = wave_sum(v.w);
-  return v;
-}
-
-__device__ inline float dot4(const float4& a, const float4& b) {
-  return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w;
-}
-
 __device__ inline float4 operator+(const float4& a, const float4& b) {
   return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
 }
 
-__device__ inline float4 scale4(const float4& a, float s) {
-  return make_float4(a.x * s, a.y * s, a.z * s, a.w * s);
-}
-
-__device__ inline float4 fma4(float s, const float4& v, const float4& acc) {
-  return make_float4(fmaf(s, v.x, acc.x), fmaf(s, v.y, acc.y), fmaf(s, v.z, acc.z),
-                     fmaf(s, v.w, acc.w));
-}
-
-__device__ inline float4 zero4() { return make_float4(0.f, 0.f, 0.f, 0.f); }
-
-// Streaming accesses: data read or written exactly once per step.
 typedef float v4f __attribute__((ext_vector_type(4)));
-__device__ inline float4 ld_stream(const float4* p) {
-  const v4f v = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p));
-  return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ inline void st_stream(float4* p, const float4& v) {
-  const v4f w = {v.x, v.y, v.z, v.w};
-  __builtin_nontemporal_store(w, reinterpret_cast<v4f*>(p));
-}
 
 // Tile-relative buffer accesses.  A buffer resource spans one tile from its first element;
 // a load past num_records returns zero and a store past it is dropped, so lanes and rows that
@@ -128,19 +90,103 @@ __device__ inline float wave_sum_dpp(float v) {
   const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 48));
   return ((r0 + r1) + r2) + r3;
 }
-__device__ inline float4 wave_sum_dpp(float4 v) {
-  return make_float4(wave_sum_dpp(v.x), wave_sum_dpp(v.y), wave_sum_dpp(v.z), wave_sum_dpp(v.w));
+// One row of a rank-RK factor (RK <= 4): the register and LDS form of the low-rank kernels.
+template <int RK>
+struct alignas(4 * RK) Fr {
+  float v[RK];
+};
+// RK contiguous floats that need only 4-byte alignment (rows in the caller's factor buffers).
+template <int RK>
+__device__ inline Fr<RK> ld_fr(const float* p) {
+  Fr<RK> f;
+  if constexpr (RK == 4) {
+    typedef float vu __attribute__((ext_vector_type(4), aligned(4)));
+    const vu x = *reinterpret_cast<const vu*>(p);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) f.v[k] = x[k];
+  } else if constexpr (RK == 2) {
+    typedef float vu __attribute__((ext_vector_type(2), aligned(4)));
+    const vu x = *reinterpret_cast<const vu*>(p);
+    f.v[0] = x[0];
+    f.v[1] = x[1];
+  } else {
+    f.v[0] = p[0];
+  }
+  return f;
+}
+template <int RK>
+__device__ inline Fr<RK> zero_fr() {
+  Fr<RK> f;
+#pragma unroll
+  for (int k = 0; k < RK; ++k) f.v[k] = 0.f;
+  return f;
+}
+template <int RK>
+__device__ inline Fr<RK> scale_fr(Fr<RK> a, float s) {
+#pragma unroll
+  for (int k = 0; k < RK; ++k) a.v[k] *= s;
+  return a;
+}
+template <int RK>
+__device__ inline float dot_fr(const Fr<RK>& a, const Fr<RK>& b) {
+  float s = a.v[0] * b.v[0];
+#pragma unroll
+  for (int k = 1; k < RK; ++k) s += a.v[k] * b.v[k];
+  return s;
+}
+template <int RK>
+__device__ inline void fma_fr(float s, const Fr<RK>& v, Fr<RK>& acc) {
+#pragma unroll
+  for (int k = 0; k < RK; ++k) acc.v[k] = fmaf(s, v.v[k], acc.v[k]);
+}
+template <int RK>
+__device__ inline void add_fr(Fr<RK>& a, const Fr<RK>& b) {
+#pragma unroll
+  for (int k = 0; k < RK; ++k) a.v[k] += b.v[k];
+}
+template <int RK>
+__device__ inline Fr<RK> bld_fr(Rsrc r, uint32_t off) {
+  Fr<RK> f;
+  if constexpr (RK == 4) {
+    const float4 x = bld4(r, off);
+    f.v[0] = x.x;
+    f.v[1] = x.y;
+    f.v[2] = x.z;
+    f.v[3] = x.w;
+  } else {
+#pragma unroll
+    for (int k = 0; k < RK; ++k) f.v[k] = bld1(r, off + 4u * k);
+  }
+  return f;
+}
+template <int RK>
+__device__ inline void bst_fr(Rsrc r, uint32_t off, const Fr<RK>& f) {
+  if constexpr (RK == 4) {
+    bst4(r, off, make_float4(f.v[0], f.v[1], f.v[2], f.v[3]));
+  } else {
+#pragma unroll
+    for (int k = 0; k < RK; ++k) bst1(r, off + 4u * k, f.v[k]);
+  }
+}
+template <int RK>
+__device__ inline Fr<RK> wave_sum_dpp(Fr<RK> f) {
+#pragma unroll
+  for (int k = 0; k < RK; ++k) f.v[k] = wave_sum_dpp(f.v[k]);
+  return f;
 }
 
-// x W for one row of a rank-4 factor (W upper triangular, fp64, row-major), rounded to fp32.
-__device__ inline float4 apply_w4(const float4& x, const double* W) {
-  const double x0 = x.x, x1 = x.y, x2 = x.z, x3 = x.w;
-  const double y0 = x0 * W[0];
-  const double y1 = fma(x0, W[1], x1 * W[5]);
-  const double y2 = fma(x0, W[2], fma(x1, W[6], x2 * W[10]));
-  const double y3 = fma(x0, W[3], fma(x1, W[7], fma(x2, W[11], x3 * W[15])));
-  return make_float4(static_cast<float>(y0), static_cast<float>(y1), static_cast<float>(y2),
-                     static_cast<float>(y3));
+// x W for one row of a rank-RK factor (W upper triangular, fp64, row-major), rounded to fp32.
+template <int RK>
+__device__ inline Fr<RK> apply_w(const Fr<RK>& x, const double* W) {
+  Fr<RK> y;
+#pragma unroll
+  for (int k = 0; k < RK; ++k) {
+    double s = static_cast<double>(x.v[k]) * W[k * RK + k];
+#pragma unroll
+    for (int l = k - 1; l >= 0; --l) s = fma(static_cast<double>(x.v[l]), W[l * RK + k], s);
+    y.v[k] = static_cast<float>(s);
+  }
+  return y;
 }
 
 // Buffers of a bucket in this launch's group.
@@ -149,8 +195,9 @@ __device__ inline float* dst_of(const KArgs& a, int32_t b) { return a.dst[b - a.
 __device__ inline bool deferred_of(const KArgs& a, int32_t b) {
   return ((a.deferred >> (b - a.base)) & 1ull) != 0;
 }
-__device__ inline bool deferred_p_of(const KArgs& a, int32_t b) {
-  return ((a.deferred_p >> (b - a.base)) & 1ull) != 0;
+// the arena holds X for this matrix (up to rank 4 only the wide rows' P-step leaves it)
+__device__ inline bool deferred_p_of(const KArgs& a, const MatDesc& d) {
+  return d.xhold != 0 && ((a.deferred_p >> (d.bucket - a.base)) & 1ull) != 0;
 }
 
 // Raw vectors: pack the gradient into the factor buffer (compress) or unpack the aggregated

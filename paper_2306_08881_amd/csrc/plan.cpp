@@ -23,13 +23,14 @@ namespace acp {
 namespace {
 
 constexpr int64_t kTileElems = 16384;   // gradient elements per streaming tile (unit)
-constexpr int64_t kSmallTileElems = 2048;  // per tile of the general P-step E update and decompress
 constexpr int64_t kTargetTiles = 1024;     // workgroups a launch class aims for (4 per CU)
 constexpr int64_t kMinTileElems = 2048;    // smallest tile of a class that has few elements
-constexpr int64_t kPGroup = 8;            // P-step tiles whose rows interleave (rank 4)
+constexpr int64_t kPGroup = 8;            // P-step tiles whose rows interleave (r <= 4)
 constexpr int64_t kMergeElems = int64_t(16) << 20;  // P-step classes below this share a launch
-constexpr int64_t kPMinRows = 8;          // fewest rows of a P-step tile (rank 4)
-constexpr int64_t kQGroup = 8;            // Q-step row chunks whose rows interleave (rank 4)
+constexpr int64_t kPMinRows = 8;          // fewest rows of a P-step tile (r <= 4)
+constexpr int64_t kPwRows = 64;           // most rows of a K_PWIDE tile
+constexpr int64_t kQGroup = 8;            // Q-step row chunks whose rows interleave (r <= 4)
+constexpr int64_t kMaxExtent = int64_t(1) << 30;  // bytes of a tile from its first element
 constexpr int64_t kVecChunk = 4096;     // raw-vector elements per copy tile
 constexpr int64_t kApplyRows = 256;     // factor rows per orthogonalisation tile
 constexpr int64_t kSlotAlign = 64;      // floats (256 bytes)
@@ -138,30 +139,28 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
     if (!cur.tids.empty()) plan.buckets.push_back(std::move(cur));
   }
 
-  // ---- launch classes of the rank-4 kernels and their total elements: a class with few
+  // ---- launch classes of the kernels up to rank 4 and their total elements: a class with few
   // elements gets smaller tiles, so that its (grouped) launch still has about kTargetTiles
   // workgroups instead of a few long serial ones
   const bool wide = r >= kWideRank;
   std::map<int64_t, int64_t> class_elems;
   auto class_key = [](int32_t kernel, int32_t variant) { return int64_t(kernel) * 65536 + variant; };
-  // (P-step kernel, variant), (Q-step kernel, variant), (decompress kernel, variant) of a
-  // rank-4 matrix that the register-resident kernels take; kernel -1 for the general path
-  auto rank4_classes = [&](int64_t m, int64_t grad_off, int64_t fac_p, int64_t fac_q) {
+  // (P-step kernel, variant), (Q-step kernel, variant), (decompress kernel, variant) of a matrix
+  // of m columns
+  auto low_classes = [&](int64_t m) {
     std::array<std::pair<int32_t, int32_t>, 3> c{};
-    const bool fast = r == 4 && m % 4 == 0 && grad_off % 4 == 0 && fac_p % 4 == 0 && fac_q % 4 == 0 &&
-                      cdiv(m / 4, 256) <= 5;
-    if (!fast) {
-      c.fill({-1, 0});
-    } else if (m / 4 <= 128) {
-      const int32_t v = narrow_variant(static_cast<int32_t>(m / 4));
+    const int64_t m4 = cdiv(m, 4);
+    if (m4 <= 128) {
+      const int32_t v = narrow_variant(static_cast<int32_t>(m4));
       c = {{{K_PNARROW, v}, {K_QNARROW, v}, {K_RNARROW, v}}};
-    } else if (m / 4 <= 192) {  // three waves cover a row of the P-step
-      c = {{{K_PFUSED, 1 | kThreeWaves}, {K_QSTEP, 4 | kQFused}, {K_RECON4, 0}}};
-    } else if (m / 4 > 768 && m / 4 <= 1024) {  // eight waves of two groups cover a row
-      c = {{{K_PFUSED, 2 | kEightWaves}, {K_QSTEP, 4 | kQFused}, {K_RECON4, 0}}};
+    } else if (m4 <= 192) {  // three waves cover a row of the P-step
+      c = {{{K_PFUSED, 1 | kThreeWaves}, {K_QSTEP, 0}, {K_RECON4, 0}}};
+    } else if (m4 > 768 && m4 <= 1024) {  // eight waves of two groups cover a row
+      c = {{{K_PFUSED, 2 | kEightWaves}, {K_QSTEP, 0}, {K_RECON4, 0}}};
+    } else if (m <= kFusedCols) {
+      c = {{{K_PFUSED, static_cast<int32_t>(cdiv(m4, 256))}, {K_QSTEP, 0}, {K_RECON4, 0}}};
     } else {
-      const int32_t S = static_cast<int32_t>(cdiv(m / 4, 256));
-      c = {{{K_PFUSED, S}, {K_QSTEP, 4 | kQFused}, {K_RECON4, 0}}};
+      c = {{{K_PWIDE, 0}, {K_QSTEP, 1}, {K_RECON4, 0}}};
     }
     return c;
   };
@@ -169,8 +168,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
     for (size_t k = 0; k < bk.tids.size(); ++k) {
       const TensorPlan& t = plan.tensors[bk.tids[k]];
       if (!t.compressed || wide) continue;
-      for (const auto& kv : rank4_classes(t.m, bk.grad_off[k], bk.fac_off_p[k], bk.fac_off_q[k]))
-        if (kv.first >= 0) class_elems[class_key(kv.first, kv.second)] += t.n * t.m;
+      for (const auto& kv : low_classes(t.m)) class_elems[class_key(kv.first, kv.second)] += t.n * t.m;
     }
   // elements per tile of a class: its total over kTargetTiles, between kMinTileElems and `base`
   auto class_tile = [&](int32_t kernel, int32_t variant, int64_t base) {
@@ -232,29 +230,24 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       d.qh_slot = d.q_slot + mp;
       d.ql_slot = d.q_slot + 2 * mp;
       fac_floats += 3 * np + 3 * mp;
-      const bool vec4 = (t.m % 4 == 0) && (d.grad_off % 4 == 0);
-      const int64_t cpt = (vec4 && r <= 8) ? 4 : 1;
-      d.q_cb = wide ? kWideQCols : static_cast<int32_t>(4 * 64 * cpt);
+      d.q_cb = wide ? kWideQCols : 1024;
+      d.xhold = wide || t.m > kFusedCols ? 1 : 0;
+      if (d.xhold) bk.xhold = true;
       // rows per chunk: kQRows (kWideQRows), fewer when a chunk's byte extent would pass 2^30
       // (the kernels address a tile with 32-bit offsets from the tile's first element)
       d.q_rows = static_cast<int32_t>(std::max<int64_t>(
           1, std::min<int64_t>(wide ? (r >= kBlockedRank ? 4 * kWideQRows : kWideQRows) : kQRows,
                                (int64_t(1) << 30) / (t.m * 4))));
-      // a small matrix the general kernels take is split into at least 4 chunks (16 rows or
-      // more each), so its Q-step is not one workgroup's serial walk
-      const bool fast = r == 4 && vec4 && d.fac_off_p % 4 == 0 && d.fac_off_q % 4 == 0 && t.m / 4 <= 1280;
-      if (!wide && !fast)
-        d.q_rows = std::min<int32_t>(d.q_rows, std::max<int32_t>(16, static_cast<int32_t>(cdiv(t.n, 4))));
-      if (!wide && fast) {
+      if (!wide) {
         // chunk rows of a multiple of 16 holding about the class's elements per tile
-        const auto qc = rank4_classes(t.m, d.grad_off, d.fac_off_p, d.fac_off_q)[1];
+        const auto qc = low_classes(t.m)[1];
         const int64_t cols = std::min<int64_t>(t.m, d.q_cb);
         const int64_t want = class_tile(qc.first, qc.second, int64_t(kQRows) * cols) / cols;
         d.q_rows = std::min<int32_t>(d.q_rows, static_cast<int32_t>(std::max<int64_t>(16, want / 16 * 16)));
       }
-      // the register-resident rank-4 Q-step interleaves the rows of kQGroup chunks (offsets of a
-      // chunk stay below 2^31: at most kQGroup * kQRows rows of at most 5120 columns)
-      d.q_grp = (!wide && fast && t.m / 4 > 128) ? static_cast<int32_t>(kQGroup) : 1;
+      // up to rank 4 the Q-step interleaves the rows of kQGroup chunks, unless their byte extent
+      // would pass kMaxExtent
+      d.q_grp = !wide && t.m > 512 && kQGroup * d.q_rows * t.m * 4 <= kMaxExtent ? static_cast<int32_t>(kQGroup) : 1;
       d.q_chunks = static_cast<int32_t>(cdiv(t.n, d.q_rows));
       const int64_t ncb = cdiv(t.m, d.q_cb);
       d.qpart = qpart;
@@ -345,7 +338,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       plan.tiles.push_back(Tile{T_ROWS, mi, static_cast<int32_t>(s),
                                 static_cast<int32_t>(std::min<int64_t>(rows_per_tile, d.n - s))});
   };
-  // rank-4 decompress tiles: 1024-column blocks of kReconRows rows.  Rows go in groups of
+  // decompress tiles up to rank 4: 1024-column blocks of kReconRows rows.  Rows go in groups of
   // gr * kReconRows (gr = 8 / column blocks, at least 1); the tiles of a group take rows
   // x, x + gr, x + 2 gr, ... (x < gr) and are ordered (x, block), so that tiles that run together
   // write whole adjacent rows.
@@ -358,12 +351,11 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       for (int64_t x = 0; x < gr && g0 + x < end; ++x) {
         const int64_t cnt = cdiv(end - g0 - x, gr);
         for (int64_t cb = 0; cb < nb; ++cb)
-          plan.tiles.push_back(Tile{T_SROWS, mi, static_cast<int32_t>(g0 + x),
-                                    static_cast<int32_t>(cb | (gr << 4) | (cnt << 16))});
+          plan.tiles.push_back(Tile{T_SROWS, mi, static_cast<int32_t>(g0 + x), srows_pack(cb, gr, cnt)});
       }
     }
   };
-  // rank-4 P-step tiles of rows_per_tile rows: groups of kPGroup tiles share kPGroup *
+  // P-step tiles (r <= 4) of rows_per_tile rows: groups of kPGroup tiles share kPGroup *
   // rows_per_tile rows, tile x of a group taking rows x, x + g, x + 2g, ... of it (g tiles in the
   // group, kPGroup except in the last one)
   auto pstep_tiles = [&](int32_t mi, int64_t rows_per_tile) {
@@ -372,29 +364,30 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       const int64_t rem = std::min<int64_t>(d.n - g0, kPGroup * rows_per_tile);
       const int64_t g = cdiv(rem, rows_per_tile);
       for (int64_t x = 0; x < g; ++x)
-        plan.tiles.push_back(Tile{T_SROWS, mi, static_cast<int32_t>(g0 + x),
-                                  static_cast<int32_t>((g << 4) | (cdiv(rem - x, g) << 16))});
+        plan.tiles.push_back(Tile{T_SROWS, mi, static_cast<int32_t>(g0 + x), srows_pack(0, g, cdiv(rem - x, g))});
     }
   };
-  // rank-4 matrices that one workgroup takes whole (T_SMALL) when the row kernels cannot
-  auto is_small = [&](int32_t mi) {
+  // K_PWIDE tiles: rows in groups as in pstep_tiles (of one tile where the extent of kPGroup would
+  // pass kMaxExtent), one tile per 1024-column block, a group's blocks of a row set together
+  auto pwide_tiles = [&](int32_t mi) {
     const MatDesc& d = plan.mats[mi];
-    return r == 4 && d.n <= kSmallRows && d.m <= kSmallCols;
+    const int64_t want = class_tile(K_PWIDE, 0, kPwRows * 1024) / 1024;
+    int64_t rows = std::max<int64_t>(kPMinRows, std::min<int64_t>(kPwRows, want / 8 * 8));
+    rows = std::max<int64_t>(1, std::min<int64_t>(rows, kMaxExtent / (int64_t(d.m) * 4)));
+    const int64_t grp = kPGroup * rows * d.m * 4 <= kMaxExtent ? kPGroup : 1;
+    const int64_t nb = cdiv(d.m, 1024);
+    for (int64_t g0 = 0; g0 < d.n; g0 += grp * rows) {
+      const int64_t rem = std::min<int64_t>(d.n - g0, grp * rows);
+      const int64_t g = cdiv(rem, rows);
+      for (int64_t x = 0; x < g; ++x)
+        for (int64_t cb = 0; cb < nb; ++cb)
+          plan.tiles.push_back(Tile{T_SROWS, mi, static_cast<int32_t>(g0 + x), srows_pack(cb, g, cdiv(rem - x, g))});
+    }
   };
-  auto is_vec4 = [&](int32_t mi) {
-    const MatDesc& d = plan.mats[mi];
-    return d.m % 4 == 0 && d.grad_off % 4 == 0;
-  };
-  // rank-4 register-resident kernels: 16-byte aligned rows and factor rows, m <= 5120
-  auto is_fast = [&](int32_t mi) {
-    const MatDesc& d = plan.mats[mi];
-    return r == 4 && is_vec4(mi) && d.fac_off_p % 4 == 0 && d.fac_off_q % 4 == 0 &&
-           cdiv(d.m / 4, 256) <= 5;
-  };
-  // rows per tile of the rank-4 kernels: a multiple of the rows handled per round
+  // rows per P-step tile up to rank 4: a multiple of the rows handled per round
   auto rows_for = [&](int32_t mi, int64_t elems) {
     const MatDesc& d = plan.mats[mi];
-    const int64_t rb = d.scls == 1 ? 8 : (d.scls <= 4 ? 2 : 1);
+    const int64_t rb = pstep_rows(static_cast<int>(r), d.scls);
     const int64_t rows = rb * std::max<int64_t>(1, elems / (int64_t(d.m) * rb));
     return std::min<int64_t>(rows, kMaxTileRows);
   };
@@ -404,7 +397,6 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
     Launch l = sink.begin(K_QFIN, 0);
     for (int32_t mi : bk.mats) {
       const MatDesc& d = plan.mats[mi];
-      if (d.scls < 0) continue;  // T_SMALL: the Q-step writes Q_loc itself
       const int64_t nblk = cdiv(int64_t(d.m) * r, qfin_entries(d.q_chunks));
       for (int64_t eb = 0; eb < nblk; ++eb)
         plan.tiles.push_back(Tile{T_QTILE, mi, static_cast<int32_t>(eb), 0});
@@ -477,36 +469,25 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       wide_lists(bk);
       continue;
     }
-    // fast: rank-4 register-resident kernels; narrow: rows of at most 512 columns (scls 0);
-    // small: rank-4 matrices of other rows, small enough for one workgroup (scls -1, T_SMALL
-    // tiles in the same launches); generic: the general kernels
-    // three: fast rows of 516-768 columns (three-wave P-step launch)
-    // eight: fast rows of 3076-4096 columns (eight-wave P-step launch)
-    std::vector<int32_t> fast, narrow, small, generic, three, eight;
+    // narrow: rows of at most 512 columns (scls 0); three: 513-768 columns (three-wave P-step
+    // launch); eight: 3073-4096 columns (eight-wave P-step launch); fast: the others up to
+    // kFusedCols; xwide: longer rows
+    std::vector<int32_t> fast, narrow, three, eight, xwide;
     for (int32_t mi : bk.mats) {
-      if (is_fast(mi)) {
-        const int64_t m4 = plan.mats[mi].m / 4;
-        plan.mats[mi].scls = m4 <= 128 ? 0 : static_cast<int32_t>(cdiv(m4, 256));
-        (m4 <= 128 ? narrow : (m4 <= 192 ? three : (m4 > 768 && m4 <= 1024 ? eight : fast))).push_back(mi);
-      } else if (is_small(mi)) {
-        plan.mats[mi].scls = -1;
-        small.push_back(mi);
-      } else {
-        generic.push_back(mi);
-      }
+      MatDesc& d = plan.mats[mi];
+      const int64_t m4 = cdiv(d.m, 4);
+      d.scls = m4 <= 128 ? 0 : static_cast<int32_t>(std::min<int64_t>(6, cdiv(m4, 256)));
+      (m4 <= 128 ? narrow : m4 <= 192 ? three : m4 > 768 && m4 <= 1024 ? eight : d.m <= kFusedCols ? fast : xwide).push_back(mi);
     }
-    auto small_tiles = [&]() {
-      for (int32_t mi : small) plan.tiles.push_back(Tile{T_SMALL, mi, 0, 0});
-    };
     auto of_narrow = [&](int32_t v) {
       std::vector<int32_t> out;
       for (int32_t mi : narrow)
-        if (narrow_variant(plan.mats[mi].m / 4) == v) out.push_back(mi);
+        if (narrow_variant((plan.mats[mi].m + 3) / 4) == v) out.push_back(mi);
       return out;
     };
     // rows per narrow tile: whole workgroup rounds (256 / L rows), about `elems` elements
     auto narrow_rows = [&](int32_t mi, int64_t elems) {
-      const int64_t rw = kBlock / (narrow_variant(plan.mats[mi].m / 4) >> 4);
+      const int64_t rw = kBlock / (narrow_variant((plan.mats[mi].m + 3) / 4) >> 4);
       return std::min<int64_t>(rw * std::max<int64_t>(1, elems / (int64_t(plan.mats[mi].m) * rw)),
                                kMaxTileRows);  // the decompress stages the tile's A rows in LDS
     };
@@ -522,9 +503,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
     {
       std::vector<Launch>& L = bk.compress[1];
       bool vec_done = bk.vecs.empty();
-      Launch l = sink.begin(K_APPLY, 1);
-      apply_tiles(generic, true);
-      sink.end(l, L);
+      Launch l{};
       // the classes S >= 2 with few elements in all (launch variant pmerge) share one launch
       auto pfused_tiles = [&](int32_t S) {
         // rows of 4 KB: 32K elements per tile; rows of 12 KB and more: 64K
@@ -536,10 +515,9 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       for (int32_t S = 1; S <= 5; ++S) {
         const bool merged = S >= 2 && class_of_p(S) != S;
         if (merged || (S == pmerge && S >= 2)) continue;  // the merged launch follows
-        if (of_class(S).empty() && (S > 1 || (narrow.empty() && small.empty()))) continue;
+        if (of_class(S).empty() && (S > 1 || narrow.empty())) continue;
         l = sink.begin(K_PFUSED, S);
-        if (S == 1) {  // the narrow-row and small matrices' tiles ride in the S = 1 launch
-          small_tiles();
+        if (S == 1) {  // the narrow-row matrices' tiles ride in the S = 1 launch
           for (int32_t v : narrow_vars)
             for (int32_t mi : of_narrow(v)) row_tiles(mi, narrow_rows(mi, class_tile(K_PNARROW, v, 2 * kTileElems)));
         }
@@ -575,17 +553,13 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
           sink.end(l, L);
         }
       }
-      if (!generic.empty()) {
-        l = sink.begin(K_PROW, 0);
-        for (int32_t mi : generic) row_tiles(mi, 1);
-        if (!vec_done) vec_tiles(bk), vec_done = true;
+      if (!xwide.empty()) {
+        l = sink.begin(K_PWIDE, 0);
+        for (int32_t mi : xwide) pwide_tiles(mi);
         sink.end(l, L);
-        if (list_ef) {
-          l = sink.begin(K_EUPD, 1);
-          for (int32_t mi : generic)
-            row_tiles(mi, std::max<int64_t>(1, kSmallTileElems / plan.mats[mi].m));
-          sink.end(l, L);
-        }
+        l = sink.begin(K_PFIN, 0);
+        for (int32_t mi : xwide) row_tiles(mi, kBlock);
+        sink.end(l, L);
       }
       if (!vec_done) {
         l = sink.begin(K_VEC, 1);
@@ -597,36 +571,21 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
     {
       std::vector<Launch>& L = bk.compress[0];
       bool vec_done = bk.vecs.empty();
-      Launch l = sink.begin(K_APPLY, 0);
-      apply_tiles(generic, false);
-      sink.end(l, L);
+      Launch l = sink.begin(K_QSTEP, 0);
       auto qtiles = [&](int32_t mi) {
         const MatDesc& d = plan.mats[mi];
         const int32_t ncb = static_cast<int32_t>(cdiv(d.m, d.q_cb));
         for (int32_t c = 0; c < d.q_chunks; ++c)
           for (int32_t cb = 0; cb < ncb; ++cb) plan.tiles.push_back(Tile{T_QTILE, mi, c, cb});
       };
-      for (int32_t variant : {4 | kQFused, 4, 1}) {
-        l = sink.begin(K_QSTEP, variant);
-        bool any = false;
-        if (variant & kQFused) {  // the small and narrow-row matrices ride in the fused launch
-          small_tiles();
-          for (int32_t mi : narrow) qtiles(mi);
-          any = !small.empty() || !narrow.empty();
-        }
-        const std::vector<int32_t>& set = (variant & kQFused) ? fast : generic;
-        if (variant & kQFused) {  // the three- and eight-wave P-step's matrices too
-          for (int32_t mi : three) qtiles(mi), any = true;
-          for (int32_t mi : eight) qtiles(mi), any = true;
-        }
-        for (int32_t mi : set) {
-          if (!(variant & kQFused) && plan.mats[mi].q_cb != 4 * 64 * variant) continue;
-          qtiles(mi);
-          any = true;
-        }
-        if (any && !vec_done) vec_tiles(bk), vec_done = true;
-        sink.end(l, L);
-      }
+      for (const auto* set : {&narrow, &three, &eight, &fast})
+        for (int32_t mi : *set) qtiles(mi);
+      if (static_cast<int64_t>(plan.tiles.size()) > l.tile_off && !vec_done) vec_tiles(bk), vec_done = true;
+      sink.end(l, L);
+      l = sink.begin(K_QSTEP, 1);  // the rows K_PWIDE takes
+      for (int32_t mi : xwide) qtiles(mi);
+      if (static_cast<int64_t>(plan.tiles.size()) > l.tile_off && !vec_done) vec_tiles(bk), vec_done = true;
+      sink.end(l, L);
       qfin_launch(bk, L, false);
       if (!vec_done) {
         l = sink.begin(K_VEC, 0);
@@ -638,40 +597,17 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
     for (int32_t par = 0; par < 2; ++par) {
       std::vector<Launch>& L = bk.decompress[par];
       const bool q = par == 0;
-      bool extra_done = false;
-      auto extra = [&]() {
-        if (extra_done) return;
-        for (int32_t mi : bk.mats) fact_tiles(mi, q);
-        vec_tiles(bk);
-        extra_done = true;
-      };
-      if (!fast.empty() || !narrow.empty() || !small.empty() || !three.empty() || !eight.empty()) {
-        Launch l = sink.begin(K_RECON4, 0);
-        extra();
-        small_tiles();
-        for (int32_t v : narrow_vars)
-          for (int32_t mi : of_narrow(v)) row_tiles(mi, narrow_rows(mi, class_tile(K_RNARROW, v, kTileElems)));
-        for (int32_t mi : fast) recon4_tiles(mi);
-        for (int32_t mi : three) recon4_tiles(mi);
-        for (int32_t mi : eight) recon4_tiles(mi);
-        sink.end(l, L);
-      }
-      for (int32_t vw : {4, 1}) {
-        Launch l = sink.begin(K_RECON, vw);
-        bool any = false;
-        for (int32_t mi : generic)
-          if ((vw == 4) == is_vec4(mi)) any = true;
-        if (any || vw == 1) extra();
-        for (int32_t mi : generic)
-          if ((vw == 4) == is_vec4(mi))
-            row_tiles(mi, std::max<int64_t>(1, 2 * kSmallTileElems / plan.mats[mi].m));
-        sink.end(l, L);
-      }
-      {
-        Launch l = sink.begin(K_CHOL, 0);
-        for (int32_t mi : bk.mats) chol_tiles(mi, q);
-        sink.end(l, L);
-      }
+      Launch l = sink.begin(K_RECON4, 0);
+      for (int32_t mi : bk.mats) fact_tiles(mi, q);
+      vec_tiles(bk);
+      for (int32_t v : narrow_vars)
+        for (int32_t mi : of_narrow(v)) row_tiles(mi, narrow_rows(mi, class_tile(K_RNARROW, v, kTileElems)));
+      for (const auto* set : {&fast, &three, &eight, &xwide})
+        for (int32_t mi : *set) recon4_tiles(mi);
+      sink.end(l, L);
+      l = sink.begin(K_CHOL, 0);
+      for (int32_t mi : bk.mats) chol_tiles(mi, q);
+      sink.end(l, L);
     }
     emat_launch(bk);
   }
@@ -735,20 +671,17 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
     if (t.kind == T_VEC) return 8.0 * t.b;
     const MatDesc& d = plan.mats[t.idx];
     const double n = d.n, m = d.m, rr = double(r);
-    if (t.kind == T_SMALL) {  // a whole small matrix: P-step, Q-step (with its finish), decompress
-      if (l.kernel == K_PFUSED) return n * m * eb + n * rr * 8.0 + m * rr * 12.0;
-      if (l.kernel == K_QSTEP) return n * m * eb + n * rr * 8.0 + m * rr * 8.0;
-      return n * m * 4.0 + n * rr * 4.0 + m * rr * 4.0;
-    }
     switch (l.kernel) {
       case K_PFUSED: {  // strided tiles, or a narrow-row matrix's block of rows
-        const double rows = t.kind == T_SROWS ? double(t.b >> 16) : double(t.b);
+        const double rows = t.kind == T_SROWS ? double(srows_count(t.b)) : double(t.b);
         return rows * m * eb + rows * rr * 8.0 + (t.a == 0 ? m * rr * 12.0 : 0.0);
       }
-      case K_PROW:
-        return m * (list_ef ? 8.0 : 4.0) + rr * 8.0 + (t.a == 0 ? m * rr * 12.0 : 0.0);
-      case K_EUPD:
-        return t.b * m * 4.0;
+      case K_PWIDE: {  // a column block of its rows and its shares of P
+        const double rows = srows_count(t.b), cols = std::min<double>(1024.0, m - 1024.0 * srows_block(t.b));
+        return rows * cols * eb + rows * rr * 4.0 + (t.a == 0 ? cols * rr * 12.0 : 0.0);
+      }
+      case K_PFIN:
+        return t.b * rr * 4.0 * (std::ceil(m / 1024.0) + 2.0);
       case K_QSTEP: {
         const double rows = q_chunk_rows(d, t.a).rows;
         const double cols = std::min<double>(d.q_cb, m - double(t.b) * d.q_cb);
@@ -758,14 +691,13 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
         const double ne = qfin_entries(d.q_chunks), e0 = double(t.a) * ne;
         return 8.0 * std::max(0.0, std::min<double>(ne, m * rr - e0));
       }
-      case K_RECON:
       case K_RECON4:
         if (t.kind == T_FACT) {
           const double rows = odd ? n : m;
           return std::min<double>(d.fact_rows, rows - double(t.a) * d.fact_rows) * rr * 8.0;
         }
         if (t.kind == T_SROWS) {
-          const double rows = t.b >> 16, cols = std::min<double>(1024.0, m - 1024.0 * (t.b & 15));
+          const double rows = srows_count(t.b), cols = std::min<double>(1024.0, m - 1024.0 * srows_block(t.b));
           return rows * cols * 4.0 + rows * rr * 4.0 + (t.a == 0 ? cols * rr * 4.0 : 0.0);
         }
         return t.b * m * 4.0 + t.b * rr * 4.0 + (t.a == 0 ? m * rr * 4.0 : 0.0);
@@ -809,14 +741,14 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
         return 0.0;
     }
   };
-  auto family_of = [](int32_t kernel, bool odd) -> int32_t {
+  auto family_of = [](int32_t kernel) -> int32_t {
     switch (kernel) {
-      case K_PFUSED: case K_PROW: case K_EUPD: case K_WPSTEP: case K_IMAGE:
+      case K_PFUSED: case K_PWIDE: case K_PFIN: case K_WPSTEP: case K_IMAGE:
         return 1;  // ACP_KERNEL_P_STEP
       case K_QSTEP: case K_WQSTEP:
         return 2;  // ACP_KERNEL_Q_STEP
       case K_QFIN: return 3;  // ACP_KERNEL_Q_FINISH
-      case K_RECON: case K_RECON4: case K_WRECON:
+      case K_RECON4: case K_WRECON:
         return 4;  // ACP_KERNEL_RECONSTRUCT
       case K_WFACT: return 5;                                              // ACP_KERNEL_ORTH
       case K_APPLY: case K_FACT: case K_CHOL: case K_GSUM: case K_DRAW: return 5;  // ACP_KERNEL_ORTH
@@ -825,7 +757,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
   };
   auto annotate = [&](std::vector<Launch>& list, bool odd) {
     for (Launch& l : list) {
-      l.family = family_of(l.kernel, odd);
+      l.family = family_of(l.kernel);
       l.alg_bytes = 0.0;
       for (int32_t i = 0; i < l.ntiles; ++i) l.alg_bytes += tile_bytes(l, plan.tiles[l.tile_off + i], odd);
     }
@@ -851,16 +783,15 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       case K_FACT: return -2;
       case K_APPLY: return 0;
       case K_PFUSED: return (l.variant & kEightWaves) ? 8 : (l.variant & kThreeWaves) ? 7 : 1 + l.variant;  // 2..8
-      case K_PROW: return 10;
-      case K_EUPD: return 11;
+      case K_PWIDE: return 10;
+      case K_PFIN: return 11;
       case K_WPSTEP: return 12;
       case K_WQSTEP: return 22;
       case K_WRECON: return 40;
       case K_WFACT: return 41;
-      case K_QSTEP: return (l.variant & kQFused) ? 20 : (l.variant == 4 ? 21 : 22);
+      case K_QSTEP: return 20;
       case K_QFIN: return 23;
       case K_RECON4: return 31;
-      case K_RECON: return l.variant == 4 ? 40 : 41;
       case K_GSUM: return 42;
       case K_CHOL: return 43;
       case K_VEC: return 50;

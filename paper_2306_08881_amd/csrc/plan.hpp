@@ -30,6 +30,7 @@ struct BucketPlan {
   int64_t qpart_base = 0;             // first Q-step partial of the bucket's matrices (floats)
   int64_t qpart_floats = 0;           // Q-step partials of the bucket's matrices (floats)
   std::vector<int32_t> mats, vecs;    // members by kind
+  bool xhold = false;                 // it has a matrix whose P-step leaves X in the arena
   std::vector<Launch> compress[2];    // [0] even step (Q-step), [1] odd step (P-step)
   std::vector<Launch> decompress[2];
   std::vector<Launch> emat;

@@ -256,7 +256,7 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
   // valid columns of the wave's block: none for a block past m (its wave loads zeros, stores
   // nothing and keeps the others' barriers)
   const int64_t w = (m - c0) < 32 ? ((m - c0) > 0 ? (m - c0) : 0) : 32;
-  const bool xform = deferred_p_of(a, d.bucket);
+  const bool xform = deferred_p_of(a, d);
   const uint32_t row_bytes = u32(m) * 4u;
   // the workgroup's columns ct ... ct + wt - 1
   const int64_t ct = static_cast<int64_t>(t.b) * kWideQWaves * d.q_cb;
@@ -684,7 +684,7 @@ __global__ __launch_bounds__(kWave * split_waves(RK), 2) void k_sqstep(KArgs a) 
   const int rows = static_cast<int>((r0 + d.q_rows < n) ? d.q_rows : n - r0);
   const int64_t c0 = static_cast<int64_t>(t.b) * d.q_cb;
   const int64_t w = (m - c0) < 32 ? (m - c0) : 32;  // valid columns of the block
-  const bool xform = deferred_p_of(a, d.bucket);
+  const bool xform = deferred_p_of(a, d);
   const uint32_t row_bytes = u32(m) * 4u;
   const uint32_t ext = u32(rows - 1) * row_bytes + u32(w) * 4u;
   const Rsrc G = tile_rsrc(src_of(a, d.bucket) + d.grad_off + r0 * m + c0, ext);
