@@ -111,9 +111,7 @@ enum TileKind : int32_t { T_ROWS = 0, T_FACT = 1, T_VEC = 2, T_QTILE = 3, T_SROW
 //               kGsumEntries, b = slice count
 // kind T_VEC  : idx = vector, a = first element, b = element count
 // kind T_QTILE: idx = matrix, a = row chunk (K_QSTEP) or entry block (K_QFIN), b = column block;
-//               K_IMAGE: a = first row, b = column block | row count << 16 (kImageCols columns)
 // K_DRAW      : T_ROWS, idx = matrix, a = first factor row, b = row count
-// K_IMAGE     : T_FACT, idx = matrix (W = I); T_VEC as for the vector copies
 struct Tile {
   int32_t kind, idx, a, b;
 };
@@ -151,7 +149,6 @@ enum KernelId : int32_t {
   K_RNARROW,
   K_GSUM,        // from kBlockedRank on: a factor's Gram partials summed (and mirrored) into the first
   K_DRAW,        // no reuse: a fresh standard normal factor into the P (variant 0) or Q (1) slot
-  K_IMAGE,       // Power-SGD: M' = M + E into the E arena (raw vectors too), W = I
 };
 
 // Narrow rows (r <= 4, m4 = ceil(m / 4) <= 128 float4 groups): L lanes per row (16, 32 or 64), G
@@ -184,11 +181,7 @@ constexpr int kWidePWaves = 4;     // ranks 8..32: waves of a K_WPSTEP workgroup
 constexpr int kWideQWaves = 4;     // ranks 8..32: waves of a K_WQSTEP workgroup (adjacent column blocks)
 constexpr int kWideQRows = 512;    // K_WQSTEP rows per chunk (at most)
 constexpr int kWideRCols = 1024;   // K_WRECON columns per tile: 32 blocks of 32
-constexpr int kImageCols = 256;    // K_IMAGE columns per tile: one per thread
 constexpr int kDrawRows = 256;     // K_DRAW factor rows per tile
-// K_IMAGE rows per tile: their row-factor rows sit in LDS (at most 16 KB)
-constexpr int image_rows(int32_t r) { return r <= 64 ? 64 : 4096 / r; }
-
 // K_PFUSED variant bits: S = 1 on three waves, for rows of 516 to 768 columns; S = 2 on eight
 // waves, for rows of 3076 to 4096 columns
 constexpr int32_t kThreeWaves = 32;
@@ -235,6 +228,7 @@ struct KArgs {
   float inv_p;          // 1 / world size
   int32_t parity;       // 1 on odd (P-) steps, 0 on even (Q-) steps
   int32_t copy_only;    // factor tiles copy the aggregated factor but build no W (Power-SGD)
+  int32_t image;        // P-step of Power-SGD: P = M' Q with Q as it is, M' left in the E arena
   uint64_t seed;        // K_DRAW: the context's seed
   int64_t step;         // K_DRAW: the step whose factors are drawn
 };

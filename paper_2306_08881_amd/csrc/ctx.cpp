@@ -293,8 +293,8 @@ acp_status compress_bucket(acp_ctx* c, int64_t step, int32_t b, const float* gra
   return ACP_OK;
 }
 
-// Power-SGD: the bucket's image of M' in the E arena (the source of both products with error
-// feedback), else the gradient itself
+// Power-SGD's second half: the bucket's image of M' in the E arena with error feedback, else the
+// gradient itself
 const float* psgd_source(const acp_ctx* c, int32_t b, const float* grad) {
   if (!c->plan.ef) return grad;
   return reinterpret_cast<const float*>(c->dev + c->plan.off_e) + c->plan.buckets[b].e_base;
@@ -316,22 +316,23 @@ acp_status psgd_ready(const acp_ctx* c, int64_t step, int32_t b, int32_t phase) 
   return ACP_OK;
 }
 
-acp_status psgd_p_bucket(acp_ctx* c, int64_t step, int32_t b, const float* grad, float* p_buf, hipStream_t s) {
-  const acp::BucketPlan& bk = c->plan.buckets[b];
+// the first half's launches: the P-step lists on M' = M + E with Q as it is (no orthogonal factor
+// to form), M' left in the E arena
+acp_status psgd_p_run(const acp_ctx* c, const std::vector<acp::Launch>& list, acp::KArgs a, hipStream_t s) {
+  a.parity = 1;
+  a.image = 1;
+  RunOpts o;
+  o.skip_apply = true;
+  return run(c, list, a, s, o);
+}
+
+acp_status psgd_p_bucket(acp_ctx* c, int32_t b, const float* grad, float* p_buf, hipStream_t s) {
   acp::KArgs a = base_args(c);
   a.base = b;
   a.src[0] = grad;
-  a.parity = 1;
+  a.dst[0] = p_buf;
   set_form(a, 0, c->deferred[b]);
-  acp_status st = run(c, bk.psgd_image, a, s);
-  if (st != ACP_OK) return st;
-  acp::KArgs m = base_args(c);
-  m.ef = 0;
-  m.base = b;
-  m.src[0] = psgd_source(c, b, grad);
-  m.dst[0] = p_buf;
-  m.parity = 1;
-  return run(c, bk.compress[1], m, s);
+  return psgd_p_run(c, c->plan.buckets[b].compress[1], a, s);
 }
 
 acp_status psgd_q_bucket(acp_ctx* c, int32_t b, const float* grad, const float* p_agg, float* q_buf,
@@ -734,7 +735,7 @@ acp_status acp_powersgd_p(acp_ctx* c, int64_t step, int32_t b, const float* grad
   const acp::BucketPlan& bk = c->plan.buckets[b];
   if (overlaps(grad, bk.grad_elems, p_buf, bk.fac_elems_p)) return fail(c, ACP_E_INVALID, "p_buf overlaps grad");
   if ((st = check_device(c)) != ACP_OK) return st;
-  if ((st = psgd_p_bucket(c, step, b, grad, p_buf, static_cast<hipStream_t>(stream))) != ACP_OK) return st;
+  if ((st = psgd_p_bucket(c, b, grad, p_buf, static_cast<hipStream_t>(stream))) != ACP_OK) return st;
   c->pending[b] = step;
   c->phase[b] = 1;
   return ACP_OK;
@@ -799,18 +800,14 @@ acp_status acp_powersgd_p_all(acp_ctx* c, int64_t step, const float* const* grad
   if (st != ACP_OK) return st;
   const hipStream_t s = static_cast<hipStream_t>(stream);
   for (size_t g = 0; g < c->plan.group_compress.size(); ++g) {
-    acp::KArgs a = base_args(c), m = base_args(c);
-    a.base = m.base = static_cast<int32_t>(g) * acp::kMaxGroup;
-    a.parity = m.parity = 1;
-    m.ef = 0;
+    acp::KArgs a = base_args(c);
+    a.base = static_cast<int32_t>(g) * acp::kMaxGroup;
     for (int32_t i = 0; i < acp::kMaxGroup && a.base + i < nb; ++i) {
       a.src[i] = grads[a.base + i];
+      a.dst[i] = p_bufs[a.base + i];
       set_form(a, i, c->deferred[a.base + i]);
-      m.src[i] = psgd_source(c, a.base + i, grads[a.base + i]);
-      m.dst[i] = p_bufs[a.base + i];
     }
-    if ((st = run(c, c->plan.group_psgd_image[g], a, s)) != ACP_OK) return st;
-    if ((st = run(c, c->plan.group_compress[g][1], m, s)) != ACP_OK) return st;
+    if ((st = psgd_p_run(c, c->plan.group_compress[g][1], a, s)) != ACP_OK) return st;
   }
   for (int32_t b = 0; b < nb; ++b) {
     c->pending[b] = step;

@@ -200,8 +200,9 @@ __device__ inline bool deferred_p_of(const KArgs& a, const MatDesc& d) {
   return d.xhold != 0 && ((a.deferred_p >> (d.bucket - a.base)) & 1ull) != 0;
 }
 
-// Raw vectors: pack the gradient into the factor buffer (compress) or unpack the aggregated
-// sum / p into the output bucket (decompress).
+// Raw vectors: pack the gradient into the factor buffer (compress; the first half of a Power-SGD
+// step with error feedback also keeps them in the E arena, the second half's source) or unpack the
+// aggregated sum / p into the output bucket (decompress).
 __device__ void vec_tile(const KArgs& a, const Tile& t, bool compress) {
   const VecDesc v = a.vecs[t.idx];
   const int64_t foff = a.parity ? v.fac_off_p : v.fac_off_q;
@@ -209,10 +210,13 @@ __device__ void vec_tile(const KArgs& a, const Tile& t, bool compress) {
   float* dst = dst_of(a, v.bucket);
   for (int i = tid(); i < t.b; i += static_cast<int>(blockDim.x)) {  // launches of 3 or 4 waves
     const int64_t k = static_cast<int64_t>(t.a) + i;
-    if (compress)
-      dst[foff + k] = src[v.grad_off + k];
-    else
+    if (compress) {
+      const float x = src[v.grad_off + k];
+      dst[foff + k] = x;
+      if (a.image && a.ef) a.e[v.e_off + k] = x;
+    } else {
       dst[v.grad_off + k] = src[foff + k] * a.inv_p;
+    }
   }
 }
 

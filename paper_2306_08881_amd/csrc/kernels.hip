@@ -75,59 +75,6 @@ __global__ __launch_bounds__(kBlock) void k_draw(KArgs a) {
   }
 }
 
-// Power-SGD's first half with error feedback: the E arena receives M' = M + E_{t-1}, the image of
-// the bucket that both of the step's products then read, E_{t-1} taken in the form the arena holds
-// it (E itself, or F - Ph Q_loc^T after a Q-step).  T_QTILE tiles: `rows` rows from t.a and
-// kImageCols columns of a matrix, one thread per column; the tile's rows of the term's row factor
-// sit in LDS and, up to rank 32, the thread's column-factor row in registers.  T_VEC tiles copy
-// raw vectors into their arena slots; T_FACT tiles set W = I, so that the P-step kernels multiply
-// by Q_{t-1} itself.
-template <int RK>
-__global__ __launch_bounds__(kBlock) void k_image(KArgs a) {
-  const Tile t = a.tiles[blockIdx.x];
-  if (t.kind == T_FACT) {
-    const MatDesc d = a.mats[t.idx];
-    for (int e = tid(); e < RK * RK; e += kBlock) a.w[d.w_slot + e] = (e / RK == e % RK) ? 1.0 : 0.0;
-    return;
-  }
-  if (t.kind == T_VEC) {
-    const VecDesc v = a.vecs[t.idx];
-    const float* src = src_of(a, v.bucket) + v.grad_off + t.a;
-    float* dst = a.e + v.e_off + t.a;
-    for (int i = tid(); i < t.b; i += kBlock) dst[i] = src[i];
-    return;
-  }
-  const MatDesc d = a.mats[t.idx];
-  const int cb = t.b & 0xffff, rows = t.b >> 16;
-  const int64_t m = d.m;
-  const int64_t c = static_cast<int64_t>(cb) * kImageCols + tid();
-  const bool fform = deferred_of(a, d.bucket), xform = deferred_p_of(a, d);
-  const bool term = fform || xform;
-  const float* L = a.fac + (xform ? d.qh_slot : d.ql_slot);  // column factor of the term (m x r)
-  const float* R = a.fac + (xform ? d.pl_slot : d.ph_slot);  // row factor of the term (n x r)
-  __shared__ float rs[4096];  // the tile's rows of R (rows * RK <= 4096)
-  if (term)
-    for (int e = tid(); e < rows * RK; e += kBlock) rs[e] = R[static_cast<int64_t>(t.a) * RK + e];
-  __syncthreads();
-  if (c >= m) return;
-  constexpr int KR = RK <= 32 ? RK : 32;  // ranks of the column-factor row held in registers
-  float l[KR];
-#pragma unroll
-  for (int k = 0; k < KR; ++k) l[k] = term ? L[c * RK + k] : 0.f;
-  const float* M = src_of(a, d.bucket) + d.grad_off;
-  float* X = a.e + d.e_off;
-  for (int i = 0; i < rows; ++i) {
-    const int64_t idx = (static_cast<int64_t>(t.a) + i) * m + c;
-    float v = M[idx] + X[idx];
-    if (term) {
-#pragma unroll
-      for (int k = 0; k < KR; ++k) v -= rs[i * RK + k] * l[k];
-      for (int k = KR; k < RK; ++k) v -= rs[i * RK + k] * L[c * RK + k];
-    }
-    X[idx] = v;
-  }
-}
-
 // Cholesky G = R^T R and W = R^-1 of a Gram matrix in shared memory (RK = 128, row-major; only
 // the upper triangle is read) for ranks from kBlockedRank on, by the whole workgroup, in blocks
 // of 32.  For each diagonal block K in order:
@@ -776,7 +723,6 @@ hipError_t launch_rank(const Launch& l, const KArgs& args, hipStream_t s) {
     case K_QFIN: hipLaunchKernelGGL(k_qfin<RK>, grid, block, 0, s, args); break;
     case K_VEC: hipLaunchKernelGGL(k_vec, grid, block, 0, s, args); break;
     case K_DRAW: hipLaunchKernelGGL(k_draw<RK>, grid, block, 0, s, args); break;
-    case K_IMAGE: hipLaunchKernelGGL(k_image<RK>, grid, block, 0, s, args); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -113,7 +113,7 @@ __device__ inline void fma_dots(const float4& v, const Fr<RK> (&q)[4], Fr<RK>& a
   fma_fr(v.w, q[3], acc);
 }
 
-// The rows of Qh = Q W and of Q_loc of the four columns from 4 c4 on, of which nv are in the row
+// The rows of Qh = Q W (of Q itself in Power-SGD's first half) and of Q_loc of the four columns from 4 c4 on, of which nv are in the row
 // (the others and, unless E is deferred, Q_loc's are zero); stored to the Qh slot when store_qh.
 template <int RK>
 __device__ inline void column_factors(const KArgs& a, const MatDesc& d, const double* Wsh, int c4, int nv,
@@ -125,12 +125,22 @@ __device__ inline void column_factors(const KArgs& a, const MatDesc& d, const do
   for (int c = 0; c < 4; ++c) {
     const bool ok = c < nv;
     const int j = ok ? 4 * c4 + c : 0;  // in-range row for columns past m
-    const Fr<RK> q = apply_w(Q[j], Wsh);
+    const Fr<RK> q0 = Q[j], qw = apply_w(q0, Wsh);
+    const Fr<RK> q = a.image ? q0 : qw;
     const Fr<RK> l = Ql[j];
     qh[c] = ok ? q : zero_fr<RK>();
     ql[c] = ok && deferred ? l : zero_fr<RK>();
     if (store_qh && ok) Qh[j] = q;
   }
+}
+
+// The row of P whose term E leaves out: in Power-SGD's first half none (M' itself stays in the arena).
+template <int RK>
+__device__ inline Fr<RK> residual_row(const KArgs& a, const Fr<RK>& P) {
+  Fr<RK> f;
+#pragma unroll
+  for (int k = 0; k < RK; ++k) f.v[k] = a.image ? 0.f : P.v[k];
+  return f;
 }
 
 // W of a matrix into shared memory (RK x RK doubles); the caller synchronises.
@@ -140,7 +150,7 @@ __device__ inline void stage_w(const KArgs& a, const MatDesc& d, double* Wsh) {
 }
 
 // P-step, narrow rows: per row M' = M + E (or M + F - Ph_row Q_loc^T), P = M' Qh (row sum),
-// E = M' - P Qh^T, P to the factor buffer.  U rounds of rows are in flight per lane.  Wsh: RK x RK
+// E = M' - P Qh^T (with Power-SGD's first half M' itself), P to the factor buffer.  U rounds of rows are in flight per lane.  Wsh: RK x RK
 // doubles of shared memory.
 template <int RK, int L, int G, bool RAG>
 __device__ void pnarrow_tile(const KArgs& a, const Tile& t, const MatDesc& d, double* Wsh) {
@@ -201,7 +211,7 @@ __device__ void pnarrow_tile(const KArgs& a, const Tile& t, const MatDesc& d, do
       for (int i = 0; i < RK; ++i) P.v[i] = row_sum<L>(acc[u].v[i]);
       const uint32_t row = static_cast<uint32_t>(nm.row(k + u));
 #pragma unroll
-      for (int g = 0; g < G; ++g) nm.store(Er, row * row_bytes, g, minus_dots(mp[u][g], P, qh[g]));
+      for (int g = 0; g < G; ++g) nm.store(Er, row * row_bytes, g, minus_dots(mp[u][g], residual_row(a, P), qh[g]));
       bst_fr(Pr, nm.cl == 0 ? row * 4u * RK : kOut, P);
     }
   }
@@ -515,7 +525,7 @@ __global__ __launch_bounds__(64 * W) void k_pfused(KArgs a) {
 #pragma unroll
         for (int w = 1; w < W; ++w) add_fr(Pr, red[buf][w][rb]);
 #pragma unroll
-        for (int s = 0; s < S; ++s) bst4_nt(Er, roff + coff[s], minus_dots(mp[rb][s], Pr, qh[s]));
+        for (int s = 0; s < S; ++s) bst4_nt(Er, roff + coff[s], minus_dots(mp[rb][s], residual_row(a, Pr), qh[s]));
         bst_fr(P, tid() == 0 ? static_cast<uint32_t>((r0 + rb) * stride) * 4u * RK : kOut, Pr);
       }
     }

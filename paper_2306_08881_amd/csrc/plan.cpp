@@ -72,9 +72,6 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
   plan.ef = ef;
   plan.reuse = reuse;
   plan.psgd = psgd;
-  // Power-SGD runs ACP-SGD's product kernels without error feedback on the image M' = M + E that
-  // its first half writes into the E arena: their lists carry no E update of their own
-  const bool list_ef = ef && !psgd;
   const int64_t r = rank;
 
   // ---- tensors: reshape and eligibility
@@ -632,26 +629,12 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       chol_launches(bk.mats, q, L);
     }
   }
-  // ---- Power-SGD: the first half writes M' = M + E (raw vectors too) into the E arena and sets
-  // W = I, then runs the P-step lists on it; the second half copies the all-reduced P into its slot
-  // and forms its W, then runs the Q-step lists; decompress is the Q-step decompress
+  // ---- Power-SGD: the first half is the P-step lists with Q as it is, leaving M' in the E arena;
+  // the second half copies the all-reduced P into its slot and forms its W, then runs the Q-step
+  // lists on M'; decompress is the Q-step decompress
   for (BucketPlan& bk : plan.buckets) {
     if (!psgd) break;
-    Launch l = sink.begin(K_IMAGE, 0);
-    const int64_t ir = image_rows(rank);
-    for (int32_t mi : bk.mats) {
-      plan.tiles.push_back(Tile{T_FACT, mi, 0, 0});
-      if (!ef) continue;
-      const MatDesc& d = plan.mats[mi];
-      const int64_t ncb = cdiv(d.m, kImageCols);
-      for (int64_t r0 = 0; r0 < d.n; r0 += ir)
-        for (int64_t cb = 0; cb < ncb; ++cb)
-          plan.tiles.push_back(Tile{T_QTILE, mi, static_cast<int32_t>(r0),
-                                    static_cast<int32_t>(cb | (std::min<int64_t>(ir, d.n - r0) << 16))});
-    }
-    if (ef) vec_tiles(bk);
-    sink.end(l, bk.psgd_image);
-    l = sink.begin(K_FACT, kFactFromBuffer);
+    Launch l = sink.begin(K_FACT, kFactFromBuffer);
     for (int32_t mi : bk.mats) fact_tiles(mi, false);
     sink.end(l, bk.psgd_fact);
     chol_launches(bk.mats, false, bk.psgd_fact);
@@ -667,7 +650,8 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
 
   // ---- launch families and algorithmic bytes (host-side profiling)
   auto tile_bytes = [&](const Launch& l, const Tile& t, bool odd) -> double {
-    const double eb = list_ef ? 12.0 : 4.0;  // M read, E read, E written per compress element
+    // M read, E read, E written per compress element (Power-SGD's second half reads M' only)
+    const double eb = ef && (odd || !psgd) ? 12.0 : 4.0;
     if (t.kind == T_VEC) return 8.0 * t.b;
     const MatDesc& d = plan.mats[t.idx];
     const double n = d.n, m = d.m, rr = double(r);
@@ -732,18 +716,13 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
         return (t.b + 1.0) * kGsumEntries * 8.0;
       case K_DRAW:
         return t.b * rr * 4.0;
-      case K_IMAGE: {  // M read, E read, M' written
-        if (t.kind != T_QTILE) return 0.0;
-        const double cols = std::min<double>(kImageCols, m - double(t.b & 0xffff) * kImageCols);
-        return double(t.b >> 16) * cols * 12.0;
-      }
       default:
         return 0.0;
     }
   };
   auto family_of = [](int32_t kernel) -> int32_t {
     switch (kernel) {
-      case K_PFUSED: case K_PWIDE: case K_PFIN: case K_WPSTEP: case K_IMAGE:
+      case K_PFUSED: case K_PWIDE: case K_PFIN: case K_WPSTEP:
         return 1;  // ACP_KERNEL_P_STEP
       case K_QSTEP: case K_WQSTEP:
         return 2;  // ACP_KERNEL_Q_STEP
@@ -770,7 +749,6 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
     annotate(bk.emat, false);
     annotate(bk.draw[0], false);
     annotate(bk.draw[1], true);
-    annotate(bk.psgd_image, true);
     annotate(bk.psgd_fact, false);
   }
   annotate(plan.gram_init, false);
@@ -779,7 +757,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
   // one, in the dependency order the per-bucket lists already follow
   auto order_of = [](const Launch& l) -> int32_t {
     switch (l.kernel) {
-      case K_DRAW: case K_IMAGE: return -3;
+      case K_DRAW: return -3;
       case K_FACT: return -2;
       case K_APPLY: return 0;
       case K_PFUSED: return (l.variant & kEightWaves) ? 8 : (l.variant & kThreeWaves) ? 7 : 1 + l.variant;  // 2..8
@@ -851,8 +829,6 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       for (int32_t par = 0; par < 2; ++par)
         gw[par] = merge(b0, b1, [par](const BucketPlan& bk) -> const std::vector<Launch>& { return bk.draw[par]; }, par == 1);
       plan.group_draw.push_back(gw);
-      plan.group_psgd_image.push_back(
-          merge(b0, b1, [](const BucketPlan& bk) -> const std::vector<Launch>& { return bk.psgd_image; }, true));
       plan.group_psgd_fact.push_back(
           merge(b0, b1, [](const BucketPlan& bk) -> const std::vector<Launch>& { return bk.psgd_fact; }, false));
     }

@@ -35,7 +35,6 @@ struct BucketPlan {
   std::vector<Launch> decompress[2];
   std::vector<Launch> emat;
   std::vector<Launch> draw[2];        // no reuse: the fresh reused factor and its W, before compress
-  std::vector<Launch> psgd_image;     // Power-SGD, first half: M' into the E arena, W = I
   std::vector<Launch> psgd_fact;      // Power-SGD, second half: the all-reduced P into its slot, W
 };
 
@@ -54,7 +53,7 @@ struct Plan {
   // launches covering whole groups of kMaxGroup buckets (the *_all entry points):
   // [group][parity] -> launches
   std::vector<std::array<std::vector<Launch>, 2>> group_compress, group_decompress, group_draw;
-  std::vector<std::vector<Launch>> group_psgd_image, group_psgd_fact;
+  std::vector<std::vector<Launch>> group_psgd_fact;
 
   // device state regions (byte offsets from the block base)
   int64_t off_e = 0, off_fac = 0, off_w = 0, off_gpart = 0, off_qpart = 0;

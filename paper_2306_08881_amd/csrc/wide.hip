@@ -6,7 +6,8 @@
 // Both compress steps apply the error-feedback residual of the previous step in deferred
 // form and write M' back, so neither waits for its own reduction before writing:
 //   P-step:  X = M + E_arena (- Ph Ql^T when the arena holds F), X written to the arena,
-//            P_loc = X Qh;  afterwards E = X - P_loc Qh^T is implied.
+//            P_loc = X Qh;  afterwards E = X - P_loc Qh^T is implied (the first half of a
+//            Power-SGD step takes Q itself for Qh and keeps X as the second half's source).
 //   Q-step:  F = M + E_arena (- Pl Qh^T when the arena holds X), F written to the arena,
 //            Q_loc = F^T Ph; afterwards E = F - Ph Q_loc^T is implied.
 // Each is one rank-r correction and one rank-r product per element.  From rank 64 the waves of
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
   const Rsrc E = tile_rsrc(a.e + d.e_off + r0 * m, a.ef ? ext : 0u);
   const Rsrc Phr = tile_rsrc(a.fac + d.ph_slot + r0 * RK, fform ? u32(rows) * RK * 4u : 0u);
   const Rsrc Qlr = tile_rsrc(a.fac + d.ql_slot, fform ? u32(m) * RK * 4u : 0u);
-  const Rsrc Qhr = tile_rsrc(a.fac + d.qh_slot, u32(m) * RK * 4u);
+  const Rsrc Qhr = tile_rsrc(a.fac + (a.image ? d.q_slot : d.qh_slot), u32(m) * RK * 4u);
   const bool ph4 = aligned16(a.fac + d.ph_slot), ql4 = aligned16(a.fac + d.ql_slot);
   static_assert(RK < kSplitRank, "from kSplitRank on the rank-split kernel takes the P-step");
   float pa[KH];  // correction A operand: -Ph[r0 + l % 32][KH h + s]
@@ -571,7 +572,7 @@ __global__ __launch_bounds__(kWave * split_waves(RK), 2) void k_spstep(KArgs a) 
   const Rsrc E = tile_rsrc(a.e + d.e_off + r0 * m, a.ef ? ext : 0u);
   const Rsrc Phr = tile_rsrc(a.fac + d.ph_slot + r0 * RK, fform ? u32(rows) * RK * 4u : 0u);
   const Rsrc Qlr = tile_rsrc(a.fac + d.ql_slot, fform ? u32(m) * RK * 4u : 0u);
-  const Rsrc Qhr = tile_rsrc(a.fac + d.qh_slot, u32(m) * RK * 4u);
+  const Rsrc Qhr = tile_rsrc(a.fac + (a.image ? d.q_slot : d.qh_slot), u32(m) * RK * 4u);
   const bool ph4 = aligned16(a.fac + d.ph_slot), ql4 = aligned16(a.fac + d.ql_slot);
   float pa[KH];  // correction A operand: -Ph[r0 + l % 32][rk0 + KH h + s]
   load_run<KH>(Phr, u32(li * RK + rk0 + KH * h) * 4u, ph4, pa);

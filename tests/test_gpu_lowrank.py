@@ -9,6 +9,7 @@ import torch
 
 import synthgrad as sg
 from tests import parity_util as PU
+from tests.test_gpu_powersgd import run_psgd_parity
 
 pytestmark = pytest.mark.gpu
 
@@ -67,3 +68,16 @@ def test_long_rows_resume_after_a_p_step(rank):
         assert torch.equal(a.fbuf[0], b.fbuf[0]) and torch.equal(a.out[0], b.out[0]), t
         # the residual's term is rounded once more when it is written out: a few fp32 roundings
         assert PU.rel_err(c.out[0].cpu().numpy(), a.out[0].cpu().numpy()) < 1e-5, t
+
+
+@pytest.mark.parametrize("rank", [1, 2, 4, 8])
+@pytest.mark.parametrize("ef", [True, False])
+def test_powersgd_row_classes(rank, ef):
+    """Power-SGD's first half runs in the P-step kernels: P = M' Q with Q as it is, M' kept."""
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    shapes = [s for s in COLS if len(s) == 1 or min(s) > rank]
+    params = [sg.Param(f"t{i}", s) for i, s in enumerate(shapes)]
+    wl = sg.Workload("cols", params, rank, 4, lambda p: 0.05, seed=6, cap_bytes=1 << 20)
+    rep = run_psgd_parity(wl, 4, list(range(len(shapes))), ef=ef, free=2)
+    assert not rep.failures, "\n".join(rep.failures[:20])
