@@ -30,6 +30,8 @@ import time
 
 HBM_PEAK_GBS = 8000.0
 MFMA_F32_PEAK_TFLOPS = 157.3  # dense fp32 matrix-core peak of MI355X
+# dense bf16 matrix-core peak over the six products of a split fp32 one (the kernels from rank 64 on)
+MFMA_SPLIT_PEAK_TFLOPS = 2500.0 / 6
 
 
 def algorithmic_bytes(wl, rank):
@@ -102,13 +104,12 @@ def host_info():
 
 
 def kernel_families(rank: int):
-    """(label, ACP_KERNEL_* family, kernel symbol prefix) of the timed kernel families: the rank-4
-    register-resident kernels; the one-wave MFMA kernels of ranks 8 to 32; from rank 64 the
-    rank-split MFMA compress kernels, with the one-wave decompress up to rank 128 and the
-    rank-split one at 256; and the separate orthogonalisation kernels."""
+    """(label, ACP_KERNEL_* family, kernel symbol prefix) of the timed kernel families: the streaming
+    kernels up to rank 4; the MFMA kernels of ranks 8 to 32; from rank 64 the kernels with split bf16
+    operands; and the separate orthogonalisation kernels."""
     from paper_2306_08881_amd import _lib as L
     if rank >= 64:
-        p, q, d = "k_spstep", "k_sqstep", "k_srecon" if rank >= 256 else "k_wrecon"
+        p, q, d = f"k_bstep<{rank}, true>", f"k_bstep<{rank}, false>", "k_brecon"
     elif rank >= 8:
         p, q, d = "k_wpstep", "k_wqstep", "k_wrecon"
     else:
@@ -147,7 +148,7 @@ def kernel_source_hash() -> str:
     import re
     csrc = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2306_08881_amd", "csrc")
     h = hashlib.sha256()
-    for f in ("kernels.hip", "lowrank.hip", "wide.hip", "device.hpp", "acp_internal.hpp", "plan.cpp", "probe.hip"):
+    for f in ("kernels.hip", "lowrank.hip", "split.hip", "wide.hip", "device.hpp", "acp_internal.hpp", "plan.cpp", "probe.hip"):
         text = open(os.path.join(csrc, f), encoding="utf-8").read()
         text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
         lines = (re.sub(r"//.*", "", ln).rstrip() for ln in text.splitlines())
@@ -521,15 +522,16 @@ def main():
             "bytes_per_launch": round(dk["bytes_per_launch"], 1)}
     if wl.rank >= 8 and dom == fams[1][0]:
         # the MFMA Q-step does one rank-r correction and one rank-r product per compressed element
-        # (4 r flop); past the machine balance its bound is the fp32 matrix-core peak
+        # (4 r flop); past the machine balance its bound is the matrix-core peak
+        peak = MFMA_SPLIT_PEAK_TFLOPS if wl.rank >= 64 else MFMA_F32_PEAK_TFLOPS
         flops = 4 * wl.rank * nc / (dk["launches"] / (steps / 2))
         t_hbm = dk["bytes_per_launch"] / (HBM_PEAK_GBS * 1e9)
-        t_mfma = flops / (MFMA_F32_PEAK_TFLOPS * 1e12)
+        t_mfma = flops / (peak * 1e12)
         tflops = flops / (dk["avg_launch_us"] * 1e-6) / 1e12
         roof["flops_per_launch"] = flops
         if t_mfma > t_hbm:
-            roof.update({"bound": "mfma", "achieved": round(tflops, 2), "peak": MFMA_F32_PEAK_TFLOPS,
-                         "unit": "TFLOP/s", "frac": round(tflops / MFMA_F32_PEAK_TFLOPS, 4),
+            roof.update({"bound": "mfma", "achieved": round(tflops, 2), "peak": round(peak, 1),
+                         "unit": "TFLOP/s", "frac": round(tflops / peak, 4),
                          "hbm_gbs": round(dk["gbs"], 2)})
     res = {
         "metric": metric_of(wl),

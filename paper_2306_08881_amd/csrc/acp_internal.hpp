@@ -159,12 +159,13 @@ constexpr int32_t narrow_variant(int32_t m4) {
 
 constexpr int32_t kWideRank = 8;   // ranks at or above this take the K_W* kernels
 constexpr int32_t kBlockedRank = 128;  // ranks whose W K_CHOL forms from Gram partials in global memory
-// ranks whose MFMA compress kernels split the rank over the four waves of a workgroup
-// (kSplitRank), whose decompress kernel does (kSplitReconRank), and whose W is factored in
-// 2 x 2 blocks of 128 (kCholBlockRank)
+// ranks whose products run on the bf16 matrix cores with split operands (split.hip), and whose W is
+// factored in 2 x 2 blocks of 128 (kCholBlockRank)
 constexpr int32_t kSplitRank = 64;
-constexpr int32_t kSplitReconRank = 256;
 constexpr int32_t kCholBlockRank = 256;
+// rows (P-step) or columns (Q-step) of a tile from kSplitRank on, and rows of a decompress tile
+constexpr int split_fix(int r) { return r >= 256 ? 64 : 128; }
+constexpr int kSplitRecon = 128;
 // ranks whose orthogonal factor X W is formed on the fp64 matrix cores (one block of
 // min(r, 64) columns per tile; below kBlockedRank a factor has one such block)
 constexpr int32_t kApplyMfmaRank = 32;

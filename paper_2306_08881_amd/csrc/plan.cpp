@@ -276,6 +276,8 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
   }
 
   // ---- launch tables
+  // columns of a Q-step tile from kWideRank on: kWideQWaves column blocks below kSplitRank
+  const int64_t q_tile_cols = r < kSplitRank ? kWideQCols * kWideQWaves : split_fix(static_cast<int>(r));
   TileSink sink{plan.tiles};
   auto vec_tiles = [&](const BucketPlan& bk) {
     for (int32_t v : bk.vecs) {
@@ -417,7 +419,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       apply_tiles(bk.mats, true);
       sink.end(l, L);
       l = sink.begin(K_WPSTEP, 0);
-      for (int32_t mi : bk.mats) row_tiles(mi, 32);
+      for (int32_t mi : bk.mats) row_tiles(mi, r < kSplitRank ? 32 : split_fix(static_cast<int>(r)));
       vec_tiles(bk);  // packed by the P-step launch's workgroups
       sink.end(l, L);
     }
@@ -430,23 +432,22 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       l = sink.begin(K_WQSTEP, 0);
       for (int32_t mi : bk.mats) {
         const MatDesc& d = plan.mats[mi];
-        // below kSplitRank a tile takes kWideQWaves adjacent column blocks, one per wave
-        const int32_t per = r < kSplitRank ? kWideQWaves : 1;
-        const int32_t ncb = static_cast<int32_t>(cdiv(cdiv(d.m, d.q_cb), per));
+        const int32_t ncb = static_cast<int32_t>(cdiv(d.m, q_tile_cols));
         for (int32_t c = 0; c < d.q_chunks; ++c)
           for (int32_t cb = 0; cb < ncb; ++cb) plan.tiles.push_back(Tile{T_QTILE, mi, c, cb});
       }
       sink.end(l, L);
       qfin_launch(bk, L, true);  // the vectors packed by the finish launch's workgroups
     }
-    // -- decompress: (32-row block, 512-column group) tiles, then factor tiles and vectors
+    // -- decompress: (row block, 1024-column group) tiles, then factor tiles and vectors
+    const int64_t recon_rows = r < kSplitRank ? 32 : kSplitRecon;
     for (int32_t par = 0; par < 2; ++par) {
       std::vector<Launch>& L = bk.decompress[par];
       const bool q = par == 0;
       Launch l = sink.begin(K_WRECON, 0);
       for (int32_t mi : bk.mats) {
         const MatDesc& d = plan.mats[mi];
-        const int32_t nrb = static_cast<int32_t>(cdiv(d.n, 32));
+        const int32_t nrb = static_cast<int32_t>(cdiv(d.n, recon_rows));
         const int32_t ncg = static_cast<int32_t>(cdiv(d.m, kWideRCols));
         for (int32_t rb = 0; rb < nrb; ++rb)
           for (int32_t cg = 0; cg < ncg; ++cg) plan.tiles.push_back(Tile{T_QTILE, mi, rb, cg});
@@ -690,7 +691,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       case K_WQSTEP: {
         const double r0 = double(t.a) * d.q_rows;
         const double rows = std::min<double>(d.q_rows, n - r0);
-        const double cw = double(d.q_cb) * (r < kSplitRank ? kWideQWaves : 1);  // a tile's columns
+        const double cw = double(q_tile_cols);  // a tile's columns
         const double cols = std::min<double>(cw, m - double(t.b) * cw);
         return rows * cols * eb + (t.b == 0 ? rows * rr * 8.0 : 0.0);
       }
@@ -700,7 +701,8 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
         return std::min<double>(d.fact_rows, rows - double(t.a & 0xffff) * d.fact_rows) * rr * 8.0;
       }
       case K_WRECON: {
-        const double rows = std::min<double>(32.0, n - 32.0 * t.a);
+        const double rb = r < kSplitRank ? 32.0 : kSplitRecon;
+        const double rows = std::min<double>(rb, n - rb * t.a);
         const double cols = std::min<double>(kWideRCols, m - double(kWideRCols) * t.b);
         return rows * cols * 4.0 + (t.b == 0 ? rows * rr * 4.0 : 0.0) + (t.a == 0 ? cols * rr * 4.0 : 0.0);
       }

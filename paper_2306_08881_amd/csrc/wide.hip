@@ -1,4 +1,4 @@
-// gfx950 MFMA kernels of the ACP-SGD compressor for ranks 8 to 256 (arXiv 2306.08881,
+// gfx950 MFMA kernels of the ACP-SGD compressor for ranks 8 to 32 (arXiv 2306.08881,
 // Algorithm 2).  At these ranks a step costs 2r multiply-adds per gradient element against
 // 12 bytes of HBM traffic, more than the fp32 vector units sustain at full bandwidth, so the
 // rank-r contractions run on v_mfma_f32_32x32x2f32.
@@ -10,9 +10,8 @@
 //            Power-SGD step takes Q itself for Qh and keeps X as the second half's source).
 //   Q-step:  F = M + E_arena (- Pl Qh^T when the arena holds X), F written to the arena,
 //            Q_loc = F^T Ph; afterwards E = F - Ph Q_loc^T is implied.
-// Each is one rank-r correction and one rank-r product per element.  From rank 64 the waves of
-// a workgroup split the rank in the compress kernels (k_spstep, k_sqstep), at rank 256 in the
-// decompress kernel too (k_srecon); the one-wave decompress keeps r / 32 output blocks per wave.
+// Each is one rank-r correction and one rank-r product per element.  From rank 64 on the kernels of
+// split.hip take the steps.
 //
 // MFMA layout (one wave): D (32 x 32) += A (32 x 2) B (2 x 32).  Lane l supplies
 // A[l % 32][l / 32] and B[l / 32][l % 32]; register v of lane l holds D[drow(v, l / 32)][l % 32].
@@ -24,6 +23,8 @@
 #include <type_traits>
 
 namespace acp {
+
+hipError_t launch_split(const Launch& l, int32_t rank, const KArgs& args, hipStream_t s);
 
 namespace {
 
@@ -385,83 +386,6 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
   }
 }
 
-// Decompress from rank 64 (the four-wave kernel below takes the lower ranks): M_hat = A B^T / p
-// over a tile (32-row block t.a, 1024-column group t.b), one wave per workgroup walking the
-// group's 32-column blocks in bursts.  Odd step: A = P_agg (factor buffer), B = Qh; even step:
-// A = Ph, B = Q_agg.  A burst of BURST blocks is computed into one accumulator block each, then
-// stored row pair by row pair: lane l stores column c0 + l % 32 of rows drow(v, l / 32) for each
-// block of the burst in turn.  Stores are nontemporal (plain stores leave M_hat's lines dirty in
-// the caches, and the next step's kernels pay for writing them back).  Each block's B rows are
-// requested one block ahead of its MFMAs.
-template <int RK>
-__global__ __launch_bounds__(kWideBlock) void k_wrecon(KArgs a) {
-  constexpr int KH = RK / 2;
-  constexpr int NB = kWideRCols / 32;                          // column blocks per tile
-  constexpr int BURST = RK <= 64 ? 2 : 1;  // blocks per burst (accumulators)
-  static_assert(NB % (2 * BURST) == 0, "pairs of bursts tile the column group");
-  const Tile t = a.tiles[blockIdx.x];
-  const bool odd = a.parity != 0;
-  const MatDesc d = a.mats[t.idx];
-  const int lane = tid(), h = lane >> 5, li = lane & 31;
-  const int64_t n = d.n, m = d.m;
-  const int64_t r0 = static_cast<int64_t>(t.a) * 32;
-  const int rows = static_cast<int>((r0 + 32 < n) ? 32 : n - r0);
-  const float* agg = src_of(a, d.bucket);
-  const float* A = odd ? agg + d.fac_off_p : a.fac + d.ph_slot;
-  const float* B = odd ? a.fac + d.qh_slot : agg + d.fac_off_q;
-  const Rsrc Ar = tile_rsrc(A + r0 * RK, u32(rows) * RK * 4u);
-  const Rsrc Br = tile_rsrc(B, u32(m) * RK * 4u);
-  const bool a4 = aligned16(A), b4 = aligned16(B);
-  float av[KH];  // A operand: A[r0 + l % 32][KH h + s] / p
-  load_run<KH>(Ar, u32(li * RK + KH * h) * 4u, a4, av);
-#pragma unroll
-  for (int s = 0; s < KH; ++s) av[s] *= a.inv_p;
-  float* O = dst_of(a, d.bucket) + d.grad_off + r0 * m;
-  const uint32_t row_bytes = u32(m) * 4u;
-  // one resource over the tile's rows: rows past `rows` fall outside it; columns past m are masked
-  const Rsrc Or = tile_rsrc(O, u32(rows) * row_bytes);
-  const uint32_t lane_row = u32(4 * h) * row_bytes;  // drow(v, h) = 8 (v / 4) + v % 4 + 4 h
-  auto bcol = [&](int j) { return static_cast<int64_t>(t.b) * kWideRCols + j * 32; };
-  auto boff = [&](int j) { return bcol(j) + li < m ? u32((bcol(j) + li) * RK + KH * h) * 4u : kOut; };
-  float bv[2][KH];  // B operand: B[c0 + l % 32][KH h + s] of block j in bv[j % 2], and the next
-  load_run<KH>(Br, boff(0), b4, bv[0]);
-  // one burst from block j0, whose parity P is a compile-time constant (register indices are)
-  auto burst = [&](int j0, auto parity) {
-    constexpr int P = decltype(parity)::value;
-    // the products: block j0 + jb into o[jb], the next block's B rows requested first
-    v16f o[BURST];
-#pragma unroll
-    for (int jb = 0; jb < BURST; ++jb) {
-      if (j0 + jb + 1 < NB) load_run<KH>(Br, boff(j0 + jb + 1), b4, bv[(P + jb + 1) & 1]);
-      o[jb] = zero16();
-#pragma unroll
-      for (int s = 0; s < KH; ++s) o[jb] = mfma(av[s], bv[(P + jb) & 1][s], o[jb]);
-    }
-    // the stores: the lane's offset per block (kOut past m), to which each row adds a
-    // wave-uniform part; the empty asm keeps the compiler from carrying a running offset per row
-    const int64_t cb = bcol(j0);
-    const int wb = static_cast<int>((m - cb) < BURST * 32 ? (m - cb) : BURST * 32);
-    uint32_t base = lane_row + u32(cb + li) * 4u;
-    asm volatile("" : "+v"(base));
-    uint32_t bo[BURST];
-#pragma unroll
-    for (int jb = 0; jb < BURST; ++jb) bo[jb] = jb * 32 + li < wb ? base + u32(jb * 128) : kOut;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const uint32_t roff = u32(8 * (v >> 2) + (v & 3)) * row_bytes;
-#pragma unroll
-      for (int jb = 0; jb < BURST; ++jb) bst1_nt(Or, bo[jb] + roff, o[jb][v]);
-    }
-  };
-  // two bursts per iteration: the first starts on an even block, the second on block j0 + BURST
-  for (int j0 = 0; j0 < NB; j0 += 2 * BURST) {
-    if (bcol(j0) >= m) break;
-    burst(j0, std::integral_constant<int, 0>{});
-    if (bcol(j0 + BURST) >= m) break;
-    burst(j0 + BURST, std::integral_constant<int, BURST & 1>{});
-  }
-}
-
 // Decompress up to rank 32 with four waves per tile (32-row block t.a, 1024-column group t.b):
 // at step k the waves compute the 32 x 32 blocks 4k ... 4k + 3 (wave w block 4k + w), as the
 // one-wave kernel does, and put them in an LDS tile of 32 rows x 128 columns; then all 256
@@ -534,306 +458,6 @@ __global__ __launch_bounds__(kBlock) void k_wrecon4w(KArgs a) {
   }
 }
 
-// ---------------------------------------------------------------------------------------
-// From kSplitRank on one wave cannot hold the operands of every rank, so the SW waves of a
-// workgroup (split_waves: 2 at rank 64, 4 from rank 128) split the rank: wave w takes ranks
-// rk0 = w r / SW ... of each rank-r term (r / 2 SW K steps per lane half, r / 32 SW 32-rank
-// output blocks), with the operand layout of the kernels above.  A correction (or a
-// decompressed block) is a sum over all ranks, so each wave writes its partial 32 x 32 block to
-// LDS and wave w adds the SW partials, in wave order, for its EPW = 16 / SW entries
-// v = EPW w + j (j < EPW) of the MFMA layout, rows drow(v, l / 32) of the block.  Wave w also
-// loads M and E for those entries only.  LDS buffers alternate between blocks, so one barrier
-// per use suffices.
-constexpr int split_waves(int r) { return r >= 128 ? 4 : 2; }
-
-// P-step over a 32-row tile, the 32-column blocks in order: partial corrections -Ph Ql^T (F
-// form) -> X = M + E + their sum for the wave's entries, stored to the arena and to the
-// transposing tile -> P += X Qh over the wave's ranks.  The next block's M, E and factor rows are
-// requested before the current block's MFMAs.
-template <int RK>
-__global__ __launch_bounds__(kWave * split_waves(RK), 2) void k_spstep(KArgs a) {
-  constexpr int SW = split_waves(RK), EPW = 16 / SW, RS = RK / SW, KH = RS / 2, NR = RS / 32;
-  static_assert(RS % 32 == 0 && EPW * SW == 16, "whole 32-rank blocks and entries per wave");
-  constexpr int LD = 33;
-  const Tile t = a.tiles[blockIdx.x];
-  if (t.kind == T_VEC) {  // a raw vector packed into the factor buffer
-    vec_tile(a, t, true);
-    return;
-  }
-  const MatDesc d = a.mats[t.idx];
-  const int wave = tid() >> 6, lane = tid() & 63, h = lane >> 5, li = lane & 31;
-  const int rk0 = wave * RS;
-  const int64_t m = d.m, r0 = t.a;
-  const int rows = t.b;
-  const bool fform = deferred_of(a, d.bucket);
-  const uint32_t row_bytes = u32(m) * 4u;
-  const uint32_t ext = u32(rows) * row_bytes;
-  const Rsrc G = tile_rsrc(src_of(a, d.bucket) + d.grad_off + r0 * m, ext);
-  const Rsrc E = tile_rsrc(a.e + d.e_off + r0 * m, a.ef ? ext : 0u);
-  const Rsrc Phr = tile_rsrc(a.fac + d.ph_slot + r0 * RK, fform ? u32(rows) * RK * 4u : 0u);
-  const Rsrc Qlr = tile_rsrc(a.fac + d.ql_slot, fform ? u32(m) * RK * 4u : 0u);
-  const Rsrc Qhr = tile_rsrc(a.fac + (a.image ? d.q_slot : d.qh_slot), u32(m) * RK * 4u);
-  const bool ph4 = aligned16(a.fac + d.ph_slot), ql4 = aligned16(a.fac + d.ql_slot);
-  float pa[KH];  // correction A operand: -Ph[r0 + l % 32][rk0 + KH h + s]
-  load_run<KH>(Phr, u32(li * RK + rk0 + KH * h) * 4u, ph4, pa);
-#pragma unroll
-  for (int s = 0; s < KH; ++s) pa[s] = -pa[s];
-
-  auto load_block = [&](int64_t c0, float* g, float* e) {  // the wave's entries
-    const uint32_t coff = c0 + li < m ? u32(c0 + li) * 4u : kOut;
-#pragma unroll
-    for (int j = 0; j < EPW; ++j) {
-      const uint32_t o = coff == kOut ? kOut : u32(drow(EPW * wave + j, h)) * row_bytes + coff;
-      g[j] = bld1_nt(G, o);
-      e[j] = bld1_nt(E, o);
-    }
-  };
-  auto load_ql = [&](int64_t c0, float* qa) {  // correction B operand: Ql rows
-    const int64_t qcol = c0 + li;
-    load_run<KH>(Qlr, qcol < m ? u32(qcol * RK + rk0 + KH * h) * 4u : kOut, ql4, qa);
-  };
-  auto load_qh = [&](int64_t c0, float (*qb)[16]) {  // product B operand: Qh rows
-#pragma unroll
-    for (int kb = 0; kb < NR; ++kb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t col = c0 + drow(v, h);
-        qb[kb][v] = bld1(Qhr, col < m ? u32(col * RK + rk0 + kb * 32 + li) * 4u : kOut);
-      }
-  };
-  __shared__ float red[2][SW][16 * kWave];
-  __shared__ float xt[2][32 * LD];
-  float g[EPW], e[EPW], qa[KH], qb[NR][16];
-  load_block(0, g, e);
-  if (fform) load_ql(0, qa);
-  load_qh(0, qb);
-  v16f p[NR];
-#pragma unroll
-  for (int kb = 0; kb < NR; ++kb) p[kb] = zero16();
-  int buf = 0;
-  for (int64_t c0 = 0; c0 < m; c0 += 32, buf ^= 1) {
-    // each operand's registers take the next block's values once this block has used them
-    if (fform) {  // the wave's share of -Ph Ql^T: A = -Ph (row, rank), B = Ql^T (rank, column)
-      v16f x = zero16();
-#pragma unroll
-      for (int s = 0; s < KH; ++s) x = mfma(pa[s], qa[s], x);
-      load_ql(c0 + 32, qa);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) red[buf][wave][v * kWave + lane] = x[v];
-      __syncthreads();
-    }
-    float cg[EPW], ce[EPW];
-#pragma unroll
-    for (int j = 0; j < EPW; ++j) {
-      cg[j] = g[j];
-      ce[j] = e[j];
-    }
-    load_block(c0 + 32, g, e);  // next block (past m: zeros, no traffic)
-    const uint32_t coff = c0 + li < m ? u32(c0 + li) * 4u : kOut;
-#pragma unroll
-    for (int j = 0; j < EPW; ++j) {
-      const int v = EPW * wave + j, row = drow(v, h);
-      float xv = cg[j] + ce[j];
-      if (fform) {
-        float c = red[buf][0][v * kWave + lane];
-#pragma unroll
-        for (int w = 1; w < SW; ++w) c += red[buf][w][v * kWave + lane];
-        xv += c;
-      }
-      bst1_nt(E, coff == kOut ? kOut : u32(row) * row_bytes + coff, xv);
-      xt[buf][row * LD + li] = xv;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {  // P += X Qh: A = X (row, column), B = Qh (column, rank)
-      const float xa = xt[buf][li * LD + drow(v, h)];
-#pragma unroll
-      for (int kb = 0; kb < NR; ++kb) p[kb] = mfma(xa, qb[kb][v], p[kb]);
-    }
-    load_qh(c0 + 32, qb);
-  }
-
-  float* P = dst_of(a, d.bucket) + d.fac_off_p;
-  float* Pl = a.fac + d.pl_slot;
-#pragma unroll
-  for (int kb = 0; kb < NR; ++kb) {
-    const int rank = rk0 + kb * 32 + li;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = drow(v, h);
-      if (row < rows) {
-        P[(r0 + row) * RK + rank] = p[kb][v];
-        Pl[(r0 + row) * RK + rank] = p[kb][v];
-      }
-    }
-  }
-}
-
-// Q-step over a tile (row chunk t.a, 32-column block t.b), the 32-row blocks in order: partial
-// corrections -Pl Qh^T (X form) -> F = M + E + their sum for the wave's entries, stored to the
-// arena and shared through LDS -> Q += F^T Ph over the wave's ranks, into the chunk's partials.
-template <int RK>
-__global__ __launch_bounds__(kWave * split_waves(RK), 2) void k_sqstep(KArgs a) {
-  constexpr int SW = split_waves(RK), EPW = 16 / SW, RS = RK / SW, KH = RS / 2, NR = RS / 32;
-  static_assert(RS % 32 == 0 && EPW * SW == 16, "whole 32-rank blocks and entries per wave");
-  const Tile t = a.tiles[blockIdx.x];
-  const MatDesc d = a.mats[t.idx];
-  const int wave = tid() >> 6, lane = tid() & 63, h = lane >> 5, li = lane & 31;
-  const int rk0 = wave * RS;
-  const int64_t n = d.n, m = d.m;
-  const int64_t r0 = static_cast<int64_t>(t.a) * d.q_rows;
-  const int rows = static_cast<int>((r0 + d.q_rows < n) ? d.q_rows : n - r0);
-  const int64_t c0 = static_cast<int64_t>(t.b) * d.q_cb;
-  const int64_t w = (m - c0) < 32 ? (m - c0) : 32;  // valid columns of the block
-  const bool xform = deferred_p_of(a, d);
-  const uint32_t row_bytes = u32(m) * 4u;
-  const uint32_t ext = u32(rows - 1) * row_bytes + u32(w) * 4u;
-  const Rsrc G = tile_rsrc(src_of(a, d.bucket) + d.grad_off + r0 * m + c0, ext);
-  const Rsrc E = tile_rsrc(a.e + d.e_off + r0 * m + c0, a.ef ? ext : 0u);
-  const Rsrc Qhr = tile_rsrc(a.fac + d.qh_slot + c0 * RK, xform ? u32(w) * RK * 4u : 0u);
-  const Rsrc Plr = tile_rsrc(a.fac + d.pl_slot + r0 * RK, xform ? u32(rows) * RK * 4u : 0u);
-  const Rsrc Phr = tile_rsrc(a.fac + d.ph_slot + r0 * RK, u32(rows) * RK * 4u);
-  const bool qh4 = aligned16(a.fac + d.qh_slot), pl4 = aligned16(a.fac + d.pl_slot);
-  float qv[KH];  // correction B operand: Qh[c0 + l % 32][rk0 + KH h + s]
-  load_run<KH>(Qhr, u32(li * RK + rk0 + KH * h) * 4u, qh4, qv);
-  const uint32_t coff = li < w ? u32(li) * 4u : kOut;
-
-  auto load_block = [&](int rb, float* g, float* e) {  // the wave's entries
-#pragma unroll
-    for (int j = 0; j < EPW; ++j) {
-      const uint32_t o = coff == kOut ? kOut : u32(rb + drow(EPW * wave + j, h)) * row_bytes + coff;
-      g[j] = bld1_nt(G, o);
-      e[j] = bld1_nt(E, o);
-    }
-  };
-  auto load_ops = [&](int rb, float* pa, float (*pb)[16]) {
-    if (xform) load_run<KH>(Plr, u32((rb + li) * RK + rk0 + KH * h) * 4u, pl4, pa);
-#pragma unroll
-    for (int kb = 0; kb < NR; ++kb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v)
-        pb[kb][v] = bld1(Phr, u32((rb + drow(v, h)) * RK + rk0 + kb * 32 + li) * 4u);
-  };
-  __shared__ float red[2][SW][16 * kWave];
-  __shared__ float fs[2][16 * kWave];
-  float g[EPW], e[EPW], pa[KH], pb[NR][16];
-  load_block(0, g, e);
-  load_ops(0, pa, pb);
-  v16f q[NR];
-#pragma unroll
-  for (int kb = 0; kb < NR; ++kb) q[kb] = zero16();
-  int buf = 0;
-  for (int rb = 0; rb < rows; rb += 32, buf ^= 1) {
-    float cg[EPW], ce[EPW], ca[KH], cb[NR][16];
-#pragma unroll
-    for (int j = 0; j < EPW; ++j) {
-      cg[j] = g[j];
-      ce[j] = e[j];
-    }
-#pragma unroll
-    for (int s = 0; s < KH; ++s) ca[s] = pa[s];
-#pragma unroll
-    for (int kb = 0; kb < NR; ++kb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) cb[kb][v] = pb[kb][v];
-    load_block(rb + 32, g, e);  // next block (past the chunk: zeros, no traffic)
-    load_ops(rb + 32, pa, pb);
-    if (xform) {  // the wave's share of -Pl Qh^T: A = -Pl (row, rank), B = Qh^T (rank, column)
-      v16f x = zero16();
-#pragma unroll
-      for (int s = 0; s < KH; ++s) x = mfma(-ca[s], qv[s], x);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) red[buf][wave][v * kWave + lane] = x[v];
-      __syncthreads();
-    }
-#pragma unroll
-    for (int j = 0; j < EPW; ++j) {
-      const int v = EPW * wave + j;
-      float f = cg[j] + ce[j];
-      if (xform) {
-        float c = red[buf][0][v * kWave + lane];
-#pragma unroll
-        for (int w2 = 1; w2 < SW; ++w2) c += red[buf][w2][v * kWave + lane];
-        f += c;
-      }
-      bst1_nt(E, coff == kOut ? kOut : u32(rb + drow(v, h)) * row_bytes + coff, f);
-      fs[buf][v * kWave + lane] = f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {  // Q += F^T Ph: A = F^T, B = Ph
-      const float fv = fs[buf][v * kWave + lane];
-#pragma unroll
-      for (int kb = 0; kb < NR; ++kb) q[kb] = mfma(fv, cb[kb][v], q[kb]);
-    }
-  }
-  const int64_t ncb = (m + d.q_cb - 1) / d.q_cb;
-  const int64_t stride = ncb * d.q_cb * RK;  // one row chunk of partials
-  float* part = a.qpart + d.qpart + static_cast<int64_t>(t.a) * stride + c0 * RK;
-#pragma unroll
-  for (int kb = 0; kb < NR; ++kb)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) part[drow(v, h) * RK + rk0 + kb * 32 + li] = q[kb][v];
-}
-
-// Decompress over a tile (32-row block t.a, 1024-column group t.b): per 32-column block the
-// wave's share of A B^T / p, the shares added in wave order for the wave's entries and stored
-// with nontemporal stores.  The next block's B rows are requested before the current MFMAs.
-template <int RK>
-__global__ __launch_bounds__(kWave * split_waves(RK), 2) void k_srecon(KArgs a) {
-  constexpr int SW = split_waves(RK), EPW = 16 / SW, RS = RK / SW, KH = RS / 2;
-  static_assert(RS % 32 == 0 && EPW * SW == 16, "whole 32-rank blocks and entries per wave");
-  const Tile t = a.tiles[blockIdx.x];
-  const bool odd = a.parity != 0;
-  const MatDesc d = a.mats[t.idx];
-  const int wave = tid() >> 6, lane = tid() & 63, h = lane >> 5, li = lane & 31;
-  const int rk0 = wave * RS;
-  const int64_t n = d.n, m = d.m;
-  const int64_t r0 = static_cast<int64_t>(t.a) * 32;
-  const int rows = static_cast<int>((r0 + 32 < n) ? 32 : n - r0);
-  const float* agg = src_of(a, d.bucket);
-  const float* A = odd ? agg + d.fac_off_p : a.fac + d.ph_slot;
-  const float* B = odd ? a.fac + d.qh_slot : agg + d.fac_off_q;
-  const Rsrc Ar = tile_rsrc(A + r0 * RK, u32(rows) * RK * 4u);
-  const Rsrc Br = tile_rsrc(B, u32(m) * RK * 4u);
-  const bool a4 = aligned16(A), b4 = aligned16(B);
-  float av[KH];  // A operand: A[r0 + l % 32][rk0 + KH h + s] / p
-  load_run<KH>(Ar, u32(li * RK + rk0 + KH * h) * 4u, a4, av);
-#pragma unroll
-  for (int s = 0; s < KH; ++s) av[s] *= a.inv_p;
-  float* O = dst_of(a, d.bucket) + d.grad_off + r0 * m;
-  const uint32_t row_bytes = u32(m) * 4u;
-  constexpr int NB = kWideRCols / 32;  // column blocks per tile
-  auto bcol = [&](int j) { return static_cast<int64_t>(t.b) * kWideRCols + j * 32; };
-  auto boff = [&](int64_t c) { return c + li < m ? u32((c + li) * RK + rk0 + KH * h) * 4u : kOut; };
-  __shared__ float red[2][SW][16 * kWave];
-  float bv[2][KH];  // B operand: B[c0 + l % 32][rk0 + KH h + s], this block and the next
-  load_run<KH>(Br, boff(bcol(0)), b4, bv[0]);
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const int64_t c0 = bcol(j);
-    if (c0 >= m) break;
-    if (j + 1 < NB) load_run<KH>(Br, boff(bcol(j + 1)), b4, bv[(j + 1) & 1]);
-    v16f o = zero16();
-#pragma unroll
-    for (int s = 0; s < KH; ++s) o = mfma(av[s], bv[j & 1][s], o);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) red[j & 1][wave][v * kWave + lane] = o[v];
-    __syncthreads();
-    const int64_t w = (m - c0) < 32 ? (m - c0) : 32;
-    const Rsrc Or = tile_rsrc(O + c0, u32(rows - 1) * row_bytes + u32(w) * 4u);
-    const uint32_t coff = li < w ? u32(li) * 4u : kOut;
-#pragma unroll
-    for (int jj = 0; jj < EPW; ++jj) {
-      const int v = EPW * wave + jj;
-      float s = red[j & 1][0][v * kWave + lane];
-#pragma unroll
-      for (int w2 = 1; w2 < SW; ++w2) s += red[j & 1][w2][v * kWave + lane];
-      bst1_nt(Or, coff == kOut ? kOut : u32(drow(v, h)) * row_bytes + coff, s);
-    }
-  }
-}
-
 // Decompress companions of K_WRECON (whole workgroups): factor tiles keep the aggregated
 // factor as the next step's reused factor and build its W; vector tiles unpack sum / p.
 template <int RK>
@@ -853,28 +477,17 @@ __global__ __launch_bounds__(kBlock) void k_wfact(KArgs a) {
 template <int RK>
 hipError_t launch_wide_rank(const Launch& l, const KArgs& args, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(l.ntiles));
-  if constexpr (RK >= kSplitRank) {
-    const dim3 block(kWave * split_waves(RK));
+  if (l.kernel == K_WFACT) {
+    hipLaunchKernelGGL(k_wfact<RK>, grid, dim3(kBlock), 0, s, args);
+  } else if constexpr (RK < kSplitRank) {
     switch (l.kernel) {
-      case K_WFACT: hipLaunchKernelGGL(k_wfact<RK>, grid, dim3(kBlock), 0, s, args); break;
-      case K_WPSTEP: hipLaunchKernelGGL(k_spstep<RK>, grid, block, 0, s, args); break;
-      case K_WQSTEP: hipLaunchKernelGGL(k_sqstep<RK>, grid, block, 0, s, args); break;
-      case K_WRECON:
-        if constexpr (RK >= kSplitReconRank)
-          hipLaunchKernelGGL(k_srecon<RK>, grid, block, 0, s, args);
-        else
-          hipLaunchKernelGGL(k_wrecon<RK>, grid, dim3(kWideBlock), 0, s, args);
-        break;
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    switch (l.kernel) {
-      case K_WFACT: hipLaunchKernelGGL(k_wfact<RK>, grid, dim3(kBlock), 0, s, args); break;
       case K_WPSTEP: hipLaunchKernelGGL(k_wpstep<RK>, grid, dim3(kWideBlock * kWidePWaves), 0, s, args); break;
       case K_WQSTEP: hipLaunchKernelGGL(k_wqstep<RK>, grid, dim3(kWideBlock * kWideQWaves), 0, s, args); break;
       case K_WRECON: hipLaunchKernelGGL(k_wrecon4w<RK>, grid, dim3(kBlock), 0, s, args); break;
       default: return hipErrorInvalidValue;
     }
+  } else {
+    return launch_split(l, RK, args, s);
   }
   return hipGetLastError();
 }

@@ -1,0 +1,66 @@
+"""GPU parity of the rank 64, 128 and 256 kernels (split bf16 operands) at the edges of their tiles:
+rows and columns on both sides of the 32-index blocks, of the 64- and 128-index tiles, of the
+1024-column decompress tiles and of a Q-step row chunk, row lengths that are not a multiple of four,
+values of very different sizes, and the error against 64 bits beside that of plain fp32 products."""
+
+import numpy as np
+import pytest
+import torch
+
+import synthgrad as sg
+from tests import parity_util as PU
+from tests.test_gpu_powersgd import run_psgd_parity
+
+pytestmark = pytest.mark.gpu
+
+
+def _shapes(rank):
+    """Sides of at least twice the rank (a factor close to square is ill-conditioned)."""
+    lo = 2 * rank
+    return [(lo, lo + 1), (lo + 31, lo + 32), (5,), (lo + 33, lo + 63), (lo + 65, lo + 127), (lo + 129, lo + 2),
+            (3,), (lo + 96, 1023), (lo, 1025), (2049 + (512 if rank == 64 else 1), lo + 3)]
+
+
+@pytest.mark.parametrize("rank", [64, 128, 256])
+@pytest.mark.parametrize("ef", [True, False])
+def test_tile_edges(rank, ef):
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    shapes = _shapes(rank)
+    params = [sg.Param(f"t{i}", s) for i, s in enumerate(shapes)]
+    wl = sg.Workload("edges", params, rank, 4, lambda p: 0.05, seed=8, cap_bytes=1 << 20)
+    rep = PU.run_parity(wl, "fresh", 4, range(1, 5), list(range(len(shapes))), ef=ef, free=2, grouped=not ef)
+    assert not rep.failures, "\n".join(rep.failures[:20])
+
+
+def test_powersgd_tile_edges():
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    shapes = _shapes(64)
+    wl = sg.Workload("edges", [sg.Param(f"t{i}", s) for i, s in enumerate(shapes)], 64, 3, lambda p: 0.05, seed=9,
+                     cap_bytes=1 << 20)
+    rep = run_psgd_parity(wl, 3, list(range(len(shapes))), free=2)
+    assert not rep.failures, "\n".join(rep.failures[:20])
+
+
+@pytest.mark.parametrize("rank", [64, 256])
+@pytest.mark.parametrize("scale", [1.0, 1e-12, 1e12])
+def test_error_is_that_of_fp32(rank, scale):
+    """One P-step and its decompress on a matrix whose entries span six orders of magnitude: the
+    split products are as close to 64 bits as fp32 products (CPU, fp32 accumulation) of the same
+    operands, within a factor of 1.5 for the order of the sums."""
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    n, m = 600, 1100
+    rng = np.random.default_rng(4)
+    g = (scale * rng.standard_normal((n, m)) * 10.0 ** rng.uniform(-3, 3, (n, m))).astype(np.float32)
+    run = PU.Runner([(n, m)], rank)
+    run.step(1, run.pack({0: g}))
+    torch.cuda.synchronize()
+    p, hat, q = run.factor_slice(1, 0).reshape(n, rank), run.out_slice(0).reshape(n, m), run.ortho(1, 0).reshape(m, rank)
+    for x, a, b in ((p, g, q), (hat, p, np.ascontiguousarray(q.T))):
+        exact = a.astype(np.float64) @ b.astype(np.float64)
+        plain = np.zeros(exact.shape, np.float32)
+        for k in range(a.shape[1]):  # one rounding per term, as a chain of fp32 multiply-adds has
+            plain += a[:, k:k + 1] * b[k:k + 1, :]
+        assert PU.rel_err(x, exact) <= 1.5 * PU.rel_err(plain, exact)
