@@ -176,7 +176,7 @@ acp_status acp_init_factor(const acp_ctx *ctx, int32_t tensor_id, int32_t which,
  * bucket `grad` (device), updates E in the state and writes the local factors and raw vectors
  * into `factor_buf` (device, factor_elems_p/q(b) floats by parity), enqueued on `stream`.
  * `factor_buf` must not overlap `grad`.  The caller all-reduces (sums) factor_buf across workers.
- * At rank 4 a P-step whose column-class launches are all small may run some of them on a stream
+ * Up to rank 4 a P-step whose column-class launches are all small may run some of them on a stream
  * the context owns (made at bind on the bound device, default priority), forked from `stream`
  * by an event and joined back into it before the call returns: work enqueued on `stream` after
  * the call, and a graph captured on it, see the whole step.
@@ -206,9 +206,9 @@ acp_status acp_compress_noalloc(acp_ctx *ctx, int64_t step, int32_t b, const flo
  * M_hat = P_t Q_t^T / p for every compressed tensor and raw/p for every vector into `out`
  * (device, grad_elems(b) floats; may alias the gradient bucket but not agg_factor), and keep the
  * aggregated factor as the next step's reused factor (Section IV-A, query reuse).
- * At ranks 8 to 64 the orthogonalisation of that factor (Section IV-A: its Gram, Cholesky and
- * W, and the orthogonal factor the next compress multiplies by) runs on the context's second
- * stream beside the decompress kernel, forked from `stream` and joined back into it before the
+ * From rank 8 on the decompress kernel runs on the context's second stream beside the
+ * orthogonalisation of that factor (Section IV-A: its Gram, Cholesky and W, and the orthogonal
+ * factor the next compress multiplies by), forked from `stream` and joined back into it before the
  * call returns; the bucket's next compress then skips forming the orthogonal factor itself (it
  * forms it after a fresh bind, a state load, or with fresh draws).
  * ACP_E_STEP unless compress(step) of this bucket came last; ACP_E_INVALID for bad buffers.
@@ -316,7 +316,7 @@ acp_status acp_set_state(acp_ctx *ctx, const void *host_buf, int64_t bytes);
 #define ACP_KERNEL_Q_FINISH 3     /* Q-step partial-sum finish */
 #define ACP_KERNEL_RECONSTRUCT 4  /* decompress kernels */
 #define ACP_KERNEL_ORTH 5         /* separate orthogonalisation kernels (general path, r > 8) */
-/* Raw-vector launches of their own (ranks 8 and up) belong to no family; at rank 4 the vectors
+/* Raw-vector launches of their own belong to no family; up to rank 4 the vectors
  * ride in the P-step, Q-step and decompress launches. */
 acp_status acp_profile_start(acp_ctx *ctx, int32_t kernel_family, int32_t max_launches);
 acp_status acp_profile_stop(acp_ctx *ctx, int64_t *launches, double *seconds, double *alg_bytes);

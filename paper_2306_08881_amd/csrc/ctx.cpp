@@ -122,39 +122,43 @@ bool small_pstep_run(const std::vector<acp::Launch>& launches, size_t i) {
   return k - i >= 2;
 }
 
-// The Gram finish of the aggregated factor (K_WFACT, then K_GSUM and K_CHOL) after a rank 8-256
-// decompress launch (K_WRECON): it reads the aggregated factor only and writes the factor slot,
-// the Gram partials, W and the raw vectors' part of the output, none of which the decompress
-// reads or writes, so it runs on the side stream beside the decompress (its few workgroups and
-// dependent launches are latency-bound, the decompress is bound by HBM writes).  From
-// kBlockedRank on the Gram's matrix-core work slowed the decompress beside it by more than the
-// overlap saved (BERT-large r=128), so those ranks keep the one stream.
-bool orth_kernel(int32_t k) { return k == acp::K_WFACT || k == acp::K_GSUM || k == acp::K_CHOL; }
-bool orth_after_recon(const acp_ctx* c, const std::vector<acp::Launch>& launches, size_t i) {
-  return c->plan.rank < acp::kBlockedRank && launches[i].kernel == acp::K_WRECON &&
-         i + 1 < launches.size() && launches[i + 1].kernel == acp::K_WFACT;
-}
-
-// Enqueues `launches` on s; skip_chol leaves out the Gram finish (K_GSUM, K_CHOL), which factor
-// tiles that only copy (KArgs::copy_only) do not need, and skip_apply the orthogonal factor's
-// product (K_APPLY), when the previous decompress formed it.  Two kinds of run are split over two
-// streams, their first launch on s and the others on the context's side stream, forked from s
-// before the run and joined back into s after it (the joins keep graph capture on s whole): a
-// small P-step run (small_pstep_run) and a decompress with the Gram finish after it
-// (orth_after_recon).  In the latter, `apply` (the next compress's K_APPLY, or null) follows the
-// Gram finish on the side stream, and *applied tells whether it was enqueued.
+// The decompress of ranks 8 to 256 (K_WRECON) runs on the side stream beside the chain that
+// orthogonalises the aggregated factor (its Gram, Cholesky and, as o.apply, the next compress's
+// orthogonal factor): the chain reads the aggregated factor and writes the factor slot, the Gram
+// partials, W, the next orthogonal factor and the raw vectors' part of the output, none of which
+// the decompress reads or writes.  fork_at: the launch before which the side stream is forked (npos:
+// no such run).  Below kSplitRank that is the whole chain; from there on the Gram and its sum come
+// first: beside the decompress, whose matrix-core workgroups fill the CUs, the Gram's tiles ended
+// with its last ones and the rest of the chain came after (rank 64: 380 us, then 115 us alone; the
+// Gram alone takes 85 us; BERT-large two steps 2755 us that way, 2732 us this).
 struct RunOpts {
   bool skip_chol = false;
   bool skip_apply = false;
   const acp::Launch* apply = nullptr;
   bool* applied = nullptr;
 };
+constexpr size_t npos = static_cast<size_t>(-1);
+size_t fork_at(const acp_ctx* c, const std::vector<acp::Launch>& launches, const RunOpts& o) {
+  if (!c->side || !o.apply) return npos;
+  for (size_t i = 0; i < launches.size(); ++i)
+    if (launches[i].kernel == acp::K_WRECON) return c->plan.rank < acp::kSplitRank ? 0 : i;
+  return npos;
+}
+
+// Enqueues `launches` on s; skip_chol leaves out the Gram finish (K_GSUM, K_CHOL), which factor
+// tiles that only copy (KArgs::copy_only) do not need, and skip_apply the orthogonal factor's
+// product (K_APPLY), when the previous decompress formed it.  Two kinds of run are split over two
+// streams, forked from s and joined back into s after it (the joins keep graph capture on s whole):
+// of a small P-step run (small_pstep_run) the launches after the first go to the context's side
+// stream; a decompress with `apply` (the next compress's K_APPLY, or null; *applied tells whether
+// it was enqueued) goes there itself and leaves s to the chain beside it (fork_at), whose few
+// workgroups then start first: behind the decompress's they waited for its slots, and the call
+// ended later (BERT-base rank 32 bucket by bucket 2980 us per two steps, 2660 this way).
 acp_status run(const acp_ctx* c, const std::vector<acp::Launch>& launches, acp::KArgs a,
                hipStream_t s, const RunOpts& o = RunOpts{}) {
   const acp::Tile* tiles = reinterpret_cast<const acp::Tile*>(c->dev + c->plan.off_tiles);
   acp_ctx* mc = const_cast<acp_ctx*>(c);
-  const hipStream_t s0 = s;
-  enum { kNone, kPstep, kOrth } forked = kNone;  // the run whose later launches go to the side
+  bool forked = false, pstep = false;  // the side stream has work; of a P-step run
   if (o.applied) *o.applied = false;
   // one launch of the list (or o.apply) on stream st
   auto enqueue = [&](const acp::Launch& l, hipStream_t st) -> std::string {
@@ -175,47 +179,46 @@ acp_status run(const acp_ctx* c, const std::vector<acp::Launch>& launches, acp::
     }
     return "";
   };
-  // the Gram finish's run ends with o.apply on the side stream; then s0 waits for the side
-  // stream's work (also before an error return)
-  std::string apply_err;
-  auto join = [&](bool with_apply = true) -> bool {
-    if (with_apply && forked == kOrth && o.apply && apply_err.empty()) {
-      apply_err = enqueue(*o.apply, c->side);
-      if (apply_err.empty() && o.applied) *o.applied = true;
-    }
-    forked = kNone;
-    s = s0;
-    const bool ok = hipEventRecord(c->join_ev, c->side) == hipSuccess && hipStreamWaitEvent(s0, c->join_ev, 0) == hipSuccess;
-    return ok && apply_err.empty();
+  auto fork = [&]() -> std::string {
+    if (hipEventRecord(c->fork_ev, s) != hipSuccess || hipStreamWaitEvent(c->side, c->fork_ev, 0) != hipSuccess)
+      return "side stream fork failed";
+    forked = true;
+    return "";
   };
-  auto error = [&](const std::string& msg) {
-    if (forked != kNone) (void)join(false);
-    return fail(c, ACP_E_DEVICE, msg);
+  // s waits for the side stream's work (also before an error return)
+  auto join = [&]() -> std::string {
+    if (!forked) return "";
+    forked = pstep = false;
+    if (hipEventRecord(c->join_ev, c->side) != hipSuccess || hipStreamWaitEvent(s, c->join_ev, 0) != hipSuccess)
+      return "side stream join failed";
+    return "";
   };
-  for (size_t i = 0; i < launches.size(); ++i) {
+  std::string msg;
+  const size_t split = fork_at(c, launches, o);
+  for (size_t i = 0; i < launches.size() && msg.empty(); ++i) {
     const acp::Launch& l = launches[i];
+    if (i == split) msg = fork();
+    if (!msg.empty()) break;
     if (o.skip_chol && (l.kernel == acp::K_GSUM || l.kernel == acp::K_CHOL)) continue;
     if (o.skip_apply && l.kernel == acp::K_APPLY) continue;
-    const bool pstep = l.kernel == acp::K_PFUSED;
-    const bool continues = (forked == kPstep && pstep) || (forked == kOrth && orth_kernel(l.kernel));
-    if (forked != kNone && !continues && !join())
-      return fail(c, ACP_E_DEVICE, apply_err.empty() ? "side stream join failed" : apply_err);
-    const bool fork_p = forked == kNone && pstep && c->side && small_pstep_run(launches, i);
-    const bool fork_o = forked == kNone && !fork_p && c->side && orth_after_recon(c, launches, i);
-    if (fork_p || fork_o) {
-      if (hipEventRecord(c->fork_ev, s0) != hipSuccess || hipStreamWaitEvent(c->side, c->fork_ev, 0) != hipSuccess)
-        return fail(c, ACP_E_DEVICE, "side stream fork failed");  // nothing is on the side yet
-      forked = fork_p ? kPstep : kOrth;
-      s = s0;  // this first launch of the run stays on s, the rest go to the side
-    } else if (forked != kNone) {
-      s = c->side;
+    const bool p = l.kernel == acp::K_PFUSED;
+    if (pstep && !p) msg = join();
+    if (!msg.empty()) break;
+    if (p && !pstep && c->side && small_pstep_run(launches, i)) {
+      msg = fork();
+      pstep = msg.empty();
+      if (msg.empty()) msg = enqueue(l, s);  // this first launch of the run stays on s
+    } else {
+      msg = enqueue(l, pstep || (forked && l.kernel == acp::K_WRECON) ? c->side : s);
     }
-    const std::string msg = enqueue(l, s);
-    if (!msg.empty()) return error(msg);
   }
-  if (forked != kNone && !join())
-    return fail(c, ACP_E_DEVICE, apply_err.empty() ? "side stream join failed" : apply_err);
-  return ACP_OK;
+  if (msg.empty() && forked && !pstep && o.apply) {
+    msg = enqueue(*o.apply, s);
+    if (msg.empty() && o.applied) *o.applied = true;
+  }
+  const std::string jm = join();
+  if (msg.empty()) msg = jm;
+  return msg.empty() ? ACP_OK : fail(c, ACP_E_DEVICE, msg);
 }
 
 void release_side(acp_ctx* c) {

@@ -439,12 +439,22 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       sink.end(l, L);
       qfin_launch(bk, L, true);  // the vectors packed by the finish launch's workgroups
     }
-    // -- decompress: (row block, 1024-column group) tiles, then factor tiles and vectors
+    // -- decompress: factor tiles and vectors, the Gram partials' sum, (row block, 1024-column group)
+    // tiles, and beside those the Cholesky
     const int64_t recon_rows = r < kSplitRank ? 32 : kSplitRecon;
     for (int32_t par = 0; par < 2; ++par) {
       std::vector<Launch>& L = bk.decompress[par];
       const bool q = par == 0;
-      Launch l = sink.begin(K_WRECON, 0);
+      Launch l = sink.begin(K_WFACT, 0);
+      for (int32_t mi : bk.mats) fact_tiles(mi, q);
+      vec_tiles(bk);
+      sink.end(l, L);
+      if (r >= kBlockedRank) {
+        l = sink.begin(K_GSUM, 0);
+        for (int32_t mi : bk.mats) gsum_tiles(mi, q);
+        sink.end(l, L);
+      }
+      l = sink.begin(K_WRECON, 0);
       for (int32_t mi : bk.mats) {
         const MatDesc& d = plan.mats[mi];
         const int32_t nrb = static_cast<int32_t>(cdiv(d.n, recon_rows));
@@ -453,11 +463,9 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
           for (int32_t cg = 0; cg < ncg; ++cg) plan.tiles.push_back(Tile{T_QTILE, mi, rb, cg});
       }
       sink.end(l, L);
-      l = sink.begin(K_WFACT, 0);
-      for (int32_t mi : bk.mats) fact_tiles(mi, q);
-      vec_tiles(bk);
+      l = sink.begin(K_CHOL, 0);
+      for (int32_t mi : bk.mats) chol_tiles(mi, q);
       sink.end(l, L);
-      chol_launches(bk.mats, q, L);
     }
     emat_launch(bk);
   };
@@ -767,12 +775,12 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       case K_PFIN: return 11;
       case K_WPSTEP: return 12;
       case K_WQSTEP: return 22;
-      case K_WRECON: return 40;
-      case K_WFACT: return 41;
+      case K_WFACT: return 40;
       case K_QSTEP: return 20;
       case K_QFIN: return 23;
       case K_RECON4: return 31;
-      case K_GSUM: return 42;
+      case K_GSUM: return 41;
+      case K_WRECON: return 42;
       case K_CHOL: return 43;
       case K_VEC: return 50;
       default: return 60;
