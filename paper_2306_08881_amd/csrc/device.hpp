@@ -233,8 +233,8 @@ template <int RK, bool DIAG, int NB = 4>
 __device__ void gram_band(const float* X, int64_t r0, int64_t r1, float* copy, int I, int J, int nw, int w,
                           v4d (&acc)[NB][NB]);
 
-// Gram of rows [r0, r1) of X (row-major, RK columns) into shared G (RK x RK), by the whole
-// workgroup, in a fixed order; the rows are also copied to `copy` when it is set.
+// Gram of rows [r0, r1) of X (row-major, RK columns) into shared G (RK rows of 2 RK: the left half),
+// by the whole workgroup, in a fixed order; the rows are also copied to `copy` when it is set.
 template <int RK>
 __device__ void gram_rows(const float* X, int64_t r0, int64_t r1, double* G, float* copy) {
   static_assert(RK <= 8 || RK == 16 || RK == 32 || RK == 64, "from kBlockedRank on gram_blocked forms the Gram");
@@ -284,8 +284,8 @@ __device__ void gram_rows(const float* X, int64_t r0, int64_t r1, double* G, flo
       while (rem >= RK - i) rem -= RK - i, ++i;
       const int j = i + rem;
       const double s = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
-      G[i * RK + j] = s;
-      G[j * RK + i] = s;
+      G[i * 2 * RK + j] = s;
+      G[j * 2 * RK + i] = s;
     }
     __syncthreads();
   } else if constexpr (RK == 16 || RK == 32 || RK == 64) {
@@ -304,14 +304,14 @@ __device__ void gram_rows(const float* X, int64_t r0, int64_t r1, double* G, flo
           for (int b = a; b < NB; ++b)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-              double& g = G[(16 * a + 4 * v + k) * RK + 16 * b + i];
+              double& g = G[(16 * a + 4 * v + k) * 2 * RK + 16 * b + i];
               g = q == 0 ? acc[a][b][v] : g + acc[a][b][v];
             }
       __syncthreads();
     }
     for (int e = tid(); e < RK * RK; e += kBlock) {
       const int r = e / RK, c = e % RK;
-      if (r / 16 > c / 16) G[e] = G[c * RK + r];
+      if (r / 16 > c / 16) G[r * 2 * RK + c] = G[c * 2 * RK + r];
     }
     __syncthreads();
   }
@@ -324,64 +324,81 @@ __device__ inline double readlane_d(double v, int src) {
                                               __builtin_amdgcn_readlane(h.y, src)));
 }
 
-// Cholesky G = R^T R and W = R^-1 (dropped columns and rows zero), written to w_out.  G in
-// shared; every thread of the workgroup calls this, the first wave does the work.  Right-looking,
-// one column per lane: lane j keeps column j of the updated G in registers; at pivot k lane k's
-// diagonal decides the drop, each lane forms its entry R[k][j] and stores it to row k of R in
-// LDS, and the trailing update reads R[k][i] back from there (one broadcast read per two entries;
-// the wave's LDS accesses take effect in order).  The subtractions come in the same order as in
-// the left-looking form (pivot 0 first), so R is the same.  W = R^-1 on the kept columns, row by
-// row (lane = row).
-template <int RK>
-__device__ __attribute__((always_inline)) void cholesky_w(const double* G, double* w_out) {
-  __shared__ double R[RK * RK];
-  __shared__ int drop[RK];
+// 1 / sqrt(x) for x > 0: the hardware estimate, then two Newton steps y += y (1 - x y^2) / 2, each
+// of which squares the relative error.
+__device__ inline double rsqrt_newton(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+  return y;
+}
+
+// Cholesky G = R^T R with L^-1 = R^-T beside it, by the first wave, in place in A (shared memory, B
+// rows of 2 B: [G | I] on entry, [R | L^-1] on return; the caller synchronises before and after).
+// At pivot p the updated diagonal decides the drop (against ref(p)), row p is scaled by 1 / sqrt of
+// it and subtracted from the rows after it, in both halves:
+//   row p *= rinv;  row i -= R[p][i] row p  (i > p).
+// L^-1 = W^T, and its entries are those of the back substitution W[a][c] = (delta_ac - sum over
+// i < c of R[i][c] W[a][i]) / R[c][c] in the same order.  A dropped pivot's row is zero in both.
+// Lane j holds column j of A (B = 64: columns j and 64 + j), rows p ... in g[0] ...: each pivot's
+// update also shifts the rows down one register, so that the pivots are one rolled loop.  The
+// chain is bound by latency, and before that by fetching instructions: unrolled over the pivots
+// the code ran once through tens of KB that no cache held (this form unrolled took 53 us a launch
+// at rank 32).  Launch at rank 32 with a second, unrolled pass of dependent divisions for W 22 us,
+// this way 17.7; rank 256, whose eight diagonal blocks come here, 432 and 351 us.
+template <int B, typename Ref>
+__device__ inline void chol_inverse(double* A, Ref ref) {
+  constexpr int LD = 2 * B, NC = B > 32 ? 2 : 1;  // columns per lane
   if (tid() >= kWave) return;
   const int j = tid();
-  const bool col = j < RK;
-  double g[RK];
+  const bool on = j < LD;
+  double g[NC][B];
 #pragma unroll
-  for (int i = 0; i < RK; ++i) g[i] = col ? G[i * RK + j] : 0.0;
+  for (int q = 0; q < NC; ++q)
 #pragma unroll
-  for (int k = 0; k < RK; ++k) {
-    const double gkk = G[k * RK + k];
-    const double dk = readlane_d(g[k], k);
-    const bool keep = gkk > 0.0 && dk > kTau * kTau * gkk;
-    const double rkk = keep ? sqrt(dk) : 0.0;
-    double rkj = 0.0;
-    if (keep) rkj = j > k ? g[k] / rkk : (j == k ? rkk : 0.0);
-    if (col) R[k * RK + j] = rkj;
-    if (j == 0) drop[k] = keep ? 0 : 1;
-    __builtin_amdgcn_wave_barrier();
-    if (keep)
+    for (int a = 0; a < B; ++a) g[q][a] = A[a * LD + (on ? j : 0) + kWave * q];
+  const double refl = ref(j < B ? j : 0);
+#pragma unroll 1
+  for (int p = 0; p < B; ++p) {
+    const double dk = readlane_d(g[0][0], p), rf = readlane_d(refl, p);
+    const bool keep = rf > 0.0 && dk > kTau * kTau * rf;
+    const double rinv = keep ? rsqrt_newton(dk) : 0.0;
+    double* row = A + p * LD;
+    double y[NC];
 #pragma unroll
-      for (int i = k + 1; i < RK; ++i) g[i] -= R[k * RK + i] * rkj;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  // W = R^-1 by rows (lane = row a), right-looking: once W[a][i] is final it is subtracted
-  // from every later column at once, so the loads of R and the products of a step are
-  // independent and only the divisions form a chain.  W[a][c] = (delta_ac - sum over i < c of
-  // R[i][c] W[a][i]) / R[c][c], the sum in increasing i (the terms i < a are zero); zero for a
-  // dropped pivot c or c < a.
-  const int arow = j;
-  if (arow < RK) {
-    double acc[RK];
-#pragma unroll
-    for (int c = 0; c < RK; ++c) acc[c] = (arow == c) ? 1.0 : 0.0;
-#pragma unroll
-    for (int i = 0; i < RK; ++i) {
-      asm volatile("" ::: "memory");  // this step's loads of R only (the registers stay few)
-      // no branch: a dropped pivot divides by one and is then discarded
-      const bool use = drop[i] == 0 && arow <= i;
-      const double q = acc[i] / (use ? R[i * RK + i] : 1.0);
-      const double wi = use ? q : 0.0;
-      acc[i] = wi;
-#pragma unroll
-      for (int c = i + 1; c < RK; ++c) acc[c] -= R[i * RK + c] * wi;
+    for (int q = 0; q < NC; ++q) {
+      // G's columns left of the pivot hold nothing of R's row
+      y[q] = keep && (q > 0 || j >= p) ? g[q][0] * rinv : 0.0;
+      if (on) row[j + kWave * q] = y[q];
     }
+    asm volatile("" ::: "memory");  // one wave: its LDS accesses keep their order
 #pragma unroll
-    for (int c = 0; c < RK; ++c) w_out[arow * RK + c] = acc[c];
+    for (int a = 0; a < B - 1; ++a) {
+      const double r = row[p + 1 + a];  // past R's row: a row that does not exist
+#pragma unroll
+      for (int q = 0; q < NC; ++q) g[q][a] = fma(-r, y[q], g[q][a + 1]);
+    }
+    asm volatile("" ::: "memory");
   }
+}
+
+// A = [G | I] for chol_inverse, G in its left half already; by the whole workgroup.
+template <int B>
+__device__ inline void beside_identity(double* A) {
+  for (int e = tid(); e < B * B; e += kBlock) A[e / B * 2 * B + B + e % B] = e / B == e % B ? 1.0 : 0.0;
+}
+
+// W = R^-1 of the Gram matrix in the left half of A (shared memory, RK rows of 2 RK) into w_out, by
+// the whole workgroup; every entry of A is in place on entry.
+template <int RK>
+__device__ inline void cholesky_w(double* A, double* w_out) {
+  __shared__ double diag[RK];
+  beside_identity<RK>(A);
+  if (tid() < RK) diag[tid()] = A[tid() * (2 * RK + 1)];
+  __syncthreads();
+  chol_inverse<RK>(A, [&](int p) { return diag[p]; });
+  __syncthreads();
+  for (int e = tid(); e < RK * RK; e += kBlock) w_out[e] = A[e % RK * 2 * RK + RK + e / RK];
 }
 
 // Band block X_I^T X_J of rows [r0, r1) of X (row-major, RK columns; 64-column bands I <= J)
@@ -519,13 +536,13 @@ __device__ void fact_tile(const KArgs& a, const Tile& t, const float* src, float
   } else {
     const int64_t r0 = static_cast<int64_t>(t.a) * d.fact_rows;
     const int64_t r1 = r0 + d.fact_rows < rows ? r0 + d.fact_rows : rows;
-    __shared__ double G[RK * RK];
+    __shared__ double G[RK * 2 * RK];
     gram_rows<RK>(src, r0, r1, G, dst);
     if (t.b == 1) {
       cholesky_w<RK>(G, a.w + d.w_slot);
     } else {
       double* part = a.gpart + d.gpart + static_cast<int64_t>(t.a) * RK * RK;
-      for (int e = tid(); e < RK * RK; e += kBlock) part[e] = G[e];
+      for (int e = tid(); e < RK * RK; e += kBlock) part[e] = G[e / RK * 2 * RK + e % RK];
     }
   }
 }

@@ -78,9 +78,7 @@ __global__ __launch_bounds__(kBlock) void k_draw(KArgs a) {
 // Cholesky G = R^T R and W = R^-1 of a Gram matrix in shared memory (RK = 128, row-major; only
 // the upper triangle is read) for ranks from kBlockedRank on, by the whole workgroup, in blocks
 // of 32.  For each diagonal block K in order:
-//   (i)   one wave factors the block (lane j keeps column j in registers; at pivot p every lane
-//         takes the drop test, forms R[p][j] and updates its column with row p of R, which the
-//         lanes pass through LDS) and forms W_KK = R_KK^-1 by rows (lane j, row j);
+//   (i)   one wave factors the block and forms W_KK = R_KK^-1 beside it (chol_inverse);
 //   (ii)  the block row right of it: R_KJ = W_KK^T G_KJ (with dropped pivots W_KK's zero columns
 //         give R's zero rows, as forward substitution over the kept pivots would);
 //   (iii) the trailing upper triangle: G_IJ -= R_KI^T R_KJ.
@@ -96,58 +94,30 @@ __device__ __attribute__((always_inline)) void cholesky_w_blocked(double* G, dou
                                                                 const double* gref = nullptr, int gstride = 0) {
   static_assert(RK == 128 && kBlock == 256, "4 x 4 blocks of 32 on 256 threads");
   constexpr int B = 32, NBK = RK / B;
-  __shared__ double g0[RK], wdiag[RK], rowb[B];
-  __shared__ double T[(RK - B) * B];  // one block column's W[0:k0][.] R[.][block] products
+  __shared__ double g0[RK], wdiag[RK];
+  // a diagonal block beside the identity, then one block column's W[0:k0][.] R[.][block] products
+  __shared__ double T[(RK - B) * B];
+  static_assert((RK - B) * B >= 2 * B * B, "the diagonal block and the identity");
   auto wl = [&](int i, int c) -> double& { return G[(RK - 1 - i) * RK + (RK - 1 - c)]; };  // W[i][c], i < c
   for (int i = tid(); i < RK; i += kBlock) g0[i] = gref ? gref[i * gstride] : G[i * RK + i];
   __syncthreads();
   const int lane = tid() & 63;
   for (int K = 0; K < NBK; ++K) {
     const int k0 = K * B, nc = RK - k0 - B;  // columns right of the block
-    // (i) the diagonal block on the first wave
-    if (tid() < B) {
-      const int j = lane;
-      double g[B];
-#pragma unroll
-      for (int a = 0; a < B; ++a) g[a] = a <= j ? G[(k0 + a) * RK + k0 + j] : 0.0;
-      const double refl = g0[k0 + j];  // pivot j's reference diagonal, read by lane
-#pragma unroll
-      for (int p = 0; p < B; ++p) {
-        asm volatile("" ::: "memory");  // one pivot at a time
-        const double dk = readlane_d(g[p], p);
-        const double ref = readlane_d(refl, p);
-        const bool keep = ref > 0.0 && dk > kTau * kTau * ref;
-        const double rkk = keep ? sqrt(dk) : 0.0, rinv = keep ? 1.0 / rkk : 0.0;
-        const double rpj = j > p ? g[p] * rinv : (j == p ? rkk : 0.0);
-        g[p] = rpj;  // row p of R
-        if (j == 0) wdiag[k0 + p] = rinv;  // W's diagonal: 1 / R[p][p], zero when dropped
-        if (keep) {
-          // row p goes to every lane through LDS (one wave: its LDS accesses keep their order)
-          rowb[j] = rpj;
-          asm volatile("" ::: "memory");
-#pragma unroll
-          for (int a = p + 1; a < B; ++a) g[a] -= rowb[a] * rpj;
-        }
-      }
-#pragma unroll
-      for (int a = 0; a < B; ++a)
-        if (a <= j) G[(k0 + a) * RK + k0 + j] = g[a];
-      // W_KK row a = j: W[a][c] = -(sum_{l < c} W[a][l] R[l][c]) / R[c][c] for c > a (zero for
-      // l < a), read back from LDS one column of R at a time
-      const double* R = G + k0 * RK + k0;
-      double w[B];
-#pragma unroll
-      for (int c = 0; c < B; ++c) {
-        asm volatile("" ::: "memory");  // this column's loads only
-        double s = 0.0;
-#pragma unroll
-        for (int l = 0; l < c; ++l) s += w[l] * R[l * RK + c];
-        const double rinv = wdiag[k0 + c];
-        w[c] = c < j ? 0.0 : (c == j ? rinv : -s * rinv);
-      }
-#pragma unroll
-      for (int c = 0; c < B; ++c)
-        if (c > j) wl(k0 + j, k0 + c) = w[c];
+    // (i) the diagonal block and W_KK (chol_inverse in T, which is free here)
+    for (int e = tid(); e < B * B; e += kBlock) {
+      const int a = e / B, c = e % B;
+      T[a * 2 * B + c] = G[(k0 + (a < c ? a : c)) * RK + k0 + (a < c ? c : a)];
+    }
+    beside_identity<B>(T);
+    __syncthreads();
+    chol_inverse<B>(T, [&](int p) { return g0[k0 + p]; });
+    __syncthreads();
+    for (int e = tid(); e < B * B; e += kBlock) {
+      const int a = e / B, c = e % B;
+      if (a <= c) G[(k0 + a) * RK + k0 + c] = T[a * 2 * B + c];
+      if (a < c) wl(k0 + a, k0 + c) = T[c * 2 * B + B + a];
+      if (a == c) wdiag[k0 + a] = T[a * 2 * B + B + a];
     }
     __syncthreads();
     if (nc == 0) break;
@@ -391,7 +361,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RK <= 32
   const Tile t = a.tiles[blockIdx.x];
   const MatDesc d = a.mats[t.idx];
   constexpr bool SPLIT = RK >= kCholBlockRank;
-  __shared__ double Gs[SPLIT ? 128 * 128 : RK * RK];
+  __shared__ double Gs[SPLIT ? 128 * 128 : RK >= kBlockedRank ? RK * RK : RK * 2 * RK];
   double* gp = a.gpart + d.gpart;
   if constexpr (RK >= kBlockedRank) {
     if constexpr (SPLIT) {
@@ -426,7 +396,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RK <= 32
     }
 #pragma unroll
     for (int q = 0; q < EPT; ++q)
-      if (tid() + q * kBlock < RK * RK) Gs[tid() + q * kBlock] = acc[q];
+    {
+      const int e = tid() + q * kBlock;
+      if (e < RK * RK) Gs[e / RK * 2 * RK + e % RK] = acc[q];
+    }
     __syncthreads();
     cholesky_w<RK>(Gs, a.w + d.w_slot);
   }
