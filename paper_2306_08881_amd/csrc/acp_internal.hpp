@@ -18,6 +18,7 @@
 //             slice only).
 //   qpart     fp32 Q-step partial products, per row chunk: m_pad x r (in a P-step of rows longer
 //             than kFusedCols, the column blocks' shares of P: n x r each).
+//   fpart     fp32, ranks 8..32: Q-step partials of the lists that split row chunks further.
 //   tables    MatDesc[], VecDesc[], Tile[] for every launch.
 // No kernel communicates across workgroups: every reduction that spans workgroups is
 // finished by a later kernel in the same stream.
@@ -57,6 +58,7 @@ struct MatDesc {
   int64_t w_slot;     // double offset in the W region
   int64_t gpart;      // double offset in the Gram-partial region
   int64_t qpart;      // float offset in the Q-partial region
+  int64_t fpart;      // float offset in the fine-partial region (Q-step, ranks 8..32)
   int32_t n, m;
   int32_t q_rows;     // rows per Q-step row chunk
   int32_t q_chunks;   // number of Q-step row chunks
@@ -140,6 +142,7 @@ enum KernelId : int32_t {
   K_VEC,         // pack raw vectors only
   K_WPSTEP,      // P-step, ranks 8..32 (MFMA): X = M' written, P_loc = X Qh per 32-row tile
   K_WQSTEP,      // Q-step, ranks 8..32 (MFMA): F = M' written, per-chunk partials of F^T Ph
+  K_WPFIN,       // P-step, ranks 8..32: P_loc = sum of K_WPSTEP's column chunks -> factor buffer and Pl
   K_WRECON,      // decompress, ranks 8..32 (MFMA): M_hat = A B^T / p
   K_WFACT,       // decompress, ranks 8..32: factor tiles and vectors / p
   // tile-size classes of the narrow-row tiles up to rank 4 (rows of at most 512 columns: several
@@ -182,6 +185,13 @@ constexpr int kWidePWaves = 4;     // ranks 8..32: waves of a K_WPSTEP workgroup
 constexpr int kWideQWaves = 4;     // ranks 8..32: waves of a K_WQSTEP workgroup (adjacent column blocks)
 constexpr int kWideQRows = 512;    // K_WQSTEP rows per chunk (at most)
 constexpr int kWideRCols = 1024;   // K_WRECON columns per tile: 32 blocks of 32
+constexpr int kWideChunk = 1024;   // K_WPSTEP columns per tile (longer rows: K_WPFIN adds the chunks' sums)
+// Ranks 8..32: a Q-step chunk's sum is that of its parts of kWideSubRows rows, in order; a list with
+// fewer than kWideFullTiles tiles (the workgroups that 256 CUs hold, three each, and a third more)
+// takes one tile per part (variant kWideFine of K_WQSTEP and K_QFIN)
+constexpr int kWideSubRows = 256;
+constexpr int32_t kWideFine = 1;
+constexpr int64_t kWideFullTiles = 1024;
 constexpr int kDrawRows = 256;     // K_DRAW factor rows per tile
 // K_PFUSED variant bits: S = 1 on three waves, for rows of 516 to 768 columns; S = 2 on eight
 // waves, for rows of 3076 to 4096 columns
@@ -217,6 +227,7 @@ struct KArgs {
   double* w;            // W region
   double* gpart;        // Gram partials
   float* qpart;         // Q-step partials
+  float* fpart;         // fine partials
   const MatDesc* mats;
   const VecDesc* vecs;
   const Tile* tiles;    // this launch's tiles

@@ -94,6 +94,7 @@ acp::KArgs base_args(const acp_ctx* c) {
   a.w = reinterpret_cast<double*>(d + p.off_w);
   a.gpart = reinterpret_cast<double*>(d + p.off_gpart);
   a.qpart = reinterpret_cast<float*>(d + p.off_qpart);
+  a.fpart = reinterpret_cast<float*>(d + p.off_fpart);
   a.mats = reinterpret_cast<const acp::MatDesc*>(d + p.off_mats);
   a.vecs = reinterpret_cast<const acp::VecDesc*>(d + p.off_vecs);
   a.ef = p.ef ? 1 : 0;
@@ -248,10 +249,13 @@ const acp::Launch* leading_apply(const acp_ctx* c, const std::vector<acp::Launch
   return &compress[0];
 }
 
-// acp_compress and acp_compress_noalloc: checks, then the bucket's compress launches.  `qpart`,
-// when not null, replaces the state block's Q-step partial region as the kernels' base.
+// acp_compress and acp_compress_noalloc: checks, then the bucket's compress launches.  `scratch`,
+// when not null, takes the Q-step partials instead of the state block: the kernels address partial
+// k of a matrix as qpart + MatDesc::qpart + k (fine ones likewise) and the bucket's start at
+// qpart_base, so the base handed to them puts those at the start of the scratch.  Fine partials
+// that do not fit it leave the bucket to the coarse list, which gives the same bits.
 acp_status compress_bucket(acp_ctx* c, int64_t step, int32_t b, const float* grad, float* factor_buf,
-                           void* stream, float* qpart) {
+                           void* stream, float* scratch) {
   if (!c) return ACP_E_INVALID;
   if (c->plan.psgd) return fail(c, ACP_E_UNSUPPORTED, "this context runs Power-SGD (acp_powersgd_*)");
   if (!c->dev) return fail(c, ACP_E_STATE, "state not bound");
@@ -275,7 +279,15 @@ acp_status compress_bucket(acp_ctx* c, int64_t step, int32_t b, const float* gra
   const acp_status ds = check_device(c);
   if (ds != ACP_OK) return ds;
   acp::KArgs a = base_args(c);
-  if (qpart) a.qpart = qpart;
+  const std::vector<acp::Launch>* list = &bk.compress[step & 1];
+  if (scratch) {
+    auto based = [&](int64_t base) {
+      return reinterpret_cast<float*>(reinterpret_cast<uintptr_t>(scratch) - static_cast<uintptr_t>(base) * sizeof(float));
+    };
+    a.qpart = based(bk.qpart_base);
+    a.fpart = based(bk.fpart_base);
+    if (!(step & 1) && bk.is_fine && bk.fpart_floats * 4 > acp::kScratchBytes) list = &bk.coarse;
+  }
   a.base = b;
   a.src[0] = grad;
   a.dst[0] = factor_buf;
@@ -288,7 +300,7 @@ acp_status compress_bucket(acp_ctx* c, int64_t step, int32_t b, const float* gra
   }
   RunOpts o;
   o.skip_apply = c->applied[b] == step;
-  const acp_status st = run(c, bk.compress[step & 1], a, static_cast<hipStream_t>(stream), o);
+  const acp_status st = run(c, *list, a, static_cast<hipStream_t>(stream), o);
   if (st != ACP_OK) return st;
   c->pending[b] = step;
   c->deferred[b] = form_after_compress(c, b, step);
@@ -579,11 +591,7 @@ acp_status acp_compress_noalloc(acp_ctx* c, int64_t step, int32_t b, const float
                                           std::to_string(acp::kScratchBytes));
   if (!c->dev) return fail(c, ACP_E_STATE, "state not bound");
   if (!c->scratch) return fail(c, ACP_E_DEVICE, c->scratch_err);
-  // the kernels address partial k of a matrix as qpart + MatDesc::qpart + k; the bucket's
-  // partials start at qpart_base, so this base puts them at the start of the scratch
-  float* base = reinterpret_cast<float*>(reinterpret_cast<uintptr_t>(c->scratch) -
-                                         static_cast<uintptr_t>(bk.qpart_base) * sizeof(float));
-  return compress_bucket(c, step, b, grad, factor_buf, stream, base);
+  return compress_bucket(c, step, b, grad, factor_buf, stream, c->scratch);
 }
 
 acp_status acp_decompress(acp_ctx* c, int64_t step, int32_t b, const float* agg_factor, float* out,

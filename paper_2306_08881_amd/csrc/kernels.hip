@@ -579,10 +579,10 @@ __global__ __launch_bounds__(kBlock) void k_emat(KArgs a) {
 // Q-step finish: Q_loc = sum over the row chunks' partials.  A tile covers the NE entries
 // [t.a * NE, t.a * NE + NE) of the matrix (entry e = column * r + rank, NE = qfin_entries):
 // with NE > 256 each thread takes NE / 256 entries 256 apart, otherwise 256 / NE threads share
-// an entry.  Each thread adds a contiguous share of the chunks in chunk order, eight chunks
+// an entry.  FINE: the partials are those of the chunks' parts (kWideSubRows rows), added first.  Each thread adds a contiguous share of the chunks in chunk order, eight chunks
 // requested at a time, and the shares are added in thread order.  The result goes to the factor
 // buffer and to the Ql slot.
-template <int RK>
+template <int RK, bool FINE>
 __global__ __launch_bounds__(kBlock) void k_qfin(KArgs a) {
   const Tile t = a.tiles[blockIdx.x];
   if (t.kind == T_VEC) {  // from kWideRank on the finish launch packs the raw vectors too
@@ -594,7 +594,16 @@ __global__ __launch_bounds__(kBlock) void k_qfin(KArgs a) {
   const int64_t ncb = (m + d.q_cb - 1) / d.q_cb;
   const int64_t stride = ncb * d.q_cb * RK;  // one row chunk of partials
   const int ne = qfin_entries(d.q_chunks);   // entries per tile
-  const float* part = a.qpart + d.qpart;
+  const float* part = FINE ? a.fpart + d.fpart : a.qpart + d.qpart;
+  const int parts = FINE ? (d.q_rows + kWideSubRows - 1) / kWideSubRows : 1;  // 1 or 2
+  // chunk c's sum at entry offset o
+  auto chunk = [&](int64_t c, int64_t o) {
+    if constexpr (!FINE) return part[c * stride + o];
+    const float* p = part + c * parts * stride + o;
+    // the chunk's second part has rows
+    const bool two = parts > 1 && c * d.q_rows + kWideSubRows < d.n;
+    return two ? p[0] + p[stride] : p[0];
+  };
   float* out = dst_of(a, d.bucket) + d.fac_off_q;
   float* ql = a.fac + d.ql_slot;
   constexpr int U = 8;
@@ -614,7 +623,7 @@ __global__ __launch_bounds__(kBlock) void k_qfin(KArgs a) {
       for (int k = 0; k < EPT; ++k)
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-          v[k][u] = (e[k] < m * RK && u < d.q_chunks) ? part[u * stride + e[k]] : 0.f;
+          v[k][u] = (e[k] < m * RK && u < d.q_chunks) ? chunk(u, e[k]) : 0.f;
 #pragma unroll
       for (int k = 0; k < EPT; ++k)
 #pragma unroll
@@ -637,19 +646,18 @@ __global__ __launch_bounds__(kBlock) void k_qfin(KArgs a) {
   const int ch0 = gq * per, ch1 = (ch0 + per < d.q_chunks) ? ch0 + per : d.q_chunks;
   float s = 0.f;
   if (on) {
-    const float* base = part + e;
     int ch = ch0;
     for (; ch + U <= ch1; ch += U) {
       float v[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = base[(ch + u) * stride];
+      for (int u = 0; u < U; ++u) v[u] = chunk(ch + u, e);
 #pragma unroll
       for (int u = 0; u < U; ++u) s += v[u];
     }
     if (ch < ch1) {  // the rest (fewer than U chunks) requested together too, added in order
       float v[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = ch + u < ch1 ? base[(ch + u) * stride] : 0.f;
+      for (int u = 0; u < U; ++u) v[u] = ch + u < ch1 ? chunk(ch + u, e) : 0.f;
 #pragma unroll
       for (int u = 0; u < U; ++u)
         if (ch + u < ch1) s += v[u];
@@ -693,7 +701,15 @@ hipError_t launch_rank(const Launch& l, const KArgs& args, hipStream_t s) {
     case K_EMAT: hipLaunchKernelGGL(k_emat<RK>, grid, block, 0, s, args); break;
     case K_FACT: hipLaunchKernelGGL(k_fact<RK>, grid, block, 0, s, args); break;
     case K_CHOL: hipLaunchKernelGGL(k_chol<RK>, grid, block, 0, s, args); break;
-    case K_QFIN: hipLaunchKernelGGL(k_qfin<RK>, grid, block, 0, s, args); break;
+    case K_QFIN:
+      if constexpr (RK >= kWideRank && RK < kSplitRank) {
+        if (l.variant == kWideFine) {
+          hipLaunchKernelGGL((k_qfin<RK, true>), grid, block, 0, s, args);
+          break;
+        }
+      }
+      hipLaunchKernelGGL((k_qfin<RK, false>), grid, block, 0, s, args);
+      break;
     case K_VEC: hipLaunchKernelGGL(k_vec, grid, block, 0, s, args); break;
     case K_DRAW: hipLaunchKernelGGL(k_draw<RK>, grid, block, 0, s, args); break;
     default: return hipErrorInvalidValue;
@@ -705,7 +721,7 @@ hipError_t launch_rank(const Launch& l, const KArgs& args, hipStream_t s) {
 
 hipError_t launch(const Launch& l, int32_t rank, const KArgs& args, hipStream_t s) {
   if (l.ntiles <= 0) return hipSuccess;
-  if (l.kernel == K_WPSTEP || l.kernel == K_WQSTEP || l.kernel == K_WRECON || l.kernel == K_WFACT)
+  if (l.kernel == K_WPSTEP || l.kernel == K_WPFIN || l.kernel == K_WQSTEP || l.kernel == K_WRECON || l.kernel == K_WFACT)
     return launch_wide(l, rank, args, s);
   if (l.kernel == K_PFUSED || l.kernel == K_PWIDE || l.kernel == K_PFIN || l.kernel == K_QSTEP || l.kernel == K_RECON4)
     return launch_low(l, rank, args, s);

@@ -189,7 +189,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
   };
 
   // ---- per-tensor device descriptors and state regions
-  int64_t e_floats = 0, fac_floats = 0, gpart = 0, qpart = 0;
+  int64_t e_floats = 0, fac_floats = 0, gpart = 0, qpart = 0, fpart = 0;
   for (int32_t b = 0; b < static_cast<int32_t>(plan.buckets.size()); ++b) {
     BucketPlan& bk = plan.buckets[b];
     bk.e_base = e_floats;
@@ -251,6 +251,11 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       if (bk.mats.empty()) bk.qpart_base = qpart;
       qpart += align_up(int64_t(d.q_chunks) * ncb * d.q_cb * r, kSlotAlign);
       bk.qpart_floats = qpart - bk.qpart_base;
+      d.fpart = fpart;
+      if (bk.mats.empty()) bk.fpart_base = fpart;
+      if (wide && r < kSplitRank)
+        fpart += align_up(int64_t(d.q_chunks) * cdiv(d.q_rows, kWideSubRows) * ncb * d.q_cb * r, kSlotAlign);
+      bk.fpart_floats = fpart - bk.fpart_base;
       d.bucket = b;
       // factor rows per Gram slice: at r <= 8 up to 8192 (one slice, and no K_CHOL, for
       // factors of at most 8192 rows); at r >= 16 at least 256 and at most 32 slices per factor
@@ -392,8 +397,8 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
   };
 
   // Q-step finish tiles: entry blocks of each matrix's column blocks
-  auto qfin_launch = [&](const BucketPlan& bk, std::vector<Launch>& L, bool with_vecs) {
-    Launch l = sink.begin(K_QFIN, 0);
+  auto qfin_launch = [&](const BucketPlan& bk, std::vector<Launch>& L, bool with_vecs, int32_t variant) {
+    Launch l = sink.begin(K_QFIN, variant);
     for (int32_t mi : bk.mats) {
       const MatDesc& d = plan.mats[mi];
       const int64_t nblk = cdiv(int64_t(d.m) * r, qfin_entries(d.q_chunks));
@@ -408,36 +413,70 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
     for (int32_t mi : bk.mats) row_tiles(mi, std::max<int64_t>(1, kTileElems / plan.mats[mi].m));
     sink.end(l, bk.emat);
   };
-  // ranks 8..32: every matrix of the bucket takes the MFMA kernels
+  // tiles of a Q-step list's main launch
+  auto q_tiles = [&](const std::vector<Launch>& L) {
+    int64_t n = 0;
+    for (const Launch& l : L)
+      if (l.kernel == K_WQSTEP) n += l.ntiles;
+    return n;
+  };
+  // ranks 8..256: every matrix of the bucket takes the MFMA kernels
   auto wide_lists = [&](BucketPlan& bk) {
     // The compress kernels take matrix tiles, and the raw vectors ride along in the P-step and
     // Q-finish launches; factor tiles go to launches of their own.
-    // -- P-step (odd t): Qh = Q W, then 32-row tiles
+    // -- P-step (odd t): Qh = Q W, then row tiles (below kSplitRank one per kWideChunk columns, then
+    // the sum of a row's chunks)
     {
       std::vector<Launch>& L = bk.compress[1];
       Launch l = sink.begin(K_APPLY, 1);
       apply_tiles(bk.mats, true);
       sink.end(l, L);
       l = sink.begin(K_WPSTEP, 0);
-      for (int32_t mi : bk.mats) row_tiles(mi, r < kSplitRank ? 32 : split_fix(static_cast<int>(r)));
+      for (int32_t mi : bk.mats) {
+        const int64_t nc = r < kSplitRank ? cdiv(plan.mats[mi].m, kWideChunk) : 1;
+        if (nc == 1) {
+          row_tiles(mi, r < kSplitRank ? 32 : split_fix(static_cast<int>(r)));
+          continue;
+        }
+        const MatDesc& d = plan.mats[mi];
+        for (int64_t s = 0; s < d.n; s += 32)
+          for (int64_t c = 0; c < nc; ++c)
+            plan.tiles.push_back(Tile{T_ROWS, mi, static_cast<int32_t>(s),
+                                      static_cast<int32_t>(std::min<int64_t>(32, d.n - s) | ((c + 1) << 8))});
+      }
       vec_tiles(bk);  // packed by the P-step launch's workgroups
       sink.end(l, L);
+      l = sink.begin(K_WPFIN, 0);
+      for (int32_t mi : bk.mats)
+        if (r < kSplitRank && plan.mats[mi].m > kWideChunk) row_tiles(mi, 4 * kBlock / r);
+      sink.end(l, L);
     }
-    // -- Q-step (even t): Ph = P W, (row chunk, 32-column block) tiles, vectors, finish
-    {
-      std::vector<Launch>& L = bk.compress[0];
+    // -- Q-step (even t): Ph = P W, (row chunk, column block) tiles (fine: of the chunks' parts),
+    // vectors, finish
+    auto q_list = [&](std::vector<Launch>& L, bool fine) {
       Launch l = sink.begin(K_APPLY, 0);
       apply_tiles(bk.mats, false);
       sink.end(l, L);
-      l = sink.begin(K_WQSTEP, 0);
+      l = sink.begin(K_WQSTEP, fine ? kWideFine : 0);
       for (int32_t mi : bk.mats) {
         const MatDesc& d = plan.mats[mi];
         const int32_t ncb = static_cast<int32_t>(cdiv(d.m, q_tile_cols));
-        for (int32_t c = 0; c < d.q_chunks; ++c)
+        const int32_t parts = fine ? static_cast<int32_t>(cdiv(d.q_rows, kWideSubRows)) : 1;
+        for (int32_t c = 0; c < d.q_chunks * parts; ++c) {
+          if (int64_t(c / parts) * d.q_rows + int64_t(c % parts) * kWideSubRows >= d.n) continue;  // no rows
           for (int32_t cb = 0; cb < ncb; ++cb) plan.tiles.push_back(Tile{T_QTILE, mi, c, cb});
+        }
       }
       sink.end(l, L);
-      qfin_launch(bk, L, true);  // the vectors packed by the finish launch's workgroups
+      qfin_launch(bk, L, true, fine ? kWideFine : 0);  // the vectors packed by the finish launch's workgroups
+    };
+    if (r >= kSplitRank) {
+      q_list(bk.compress[0], false);
+    } else {
+      q_list(bk.coarse, false);
+      q_list(bk.fine, true);
+      bk.is_fine = q_tiles(bk.coarse) < kWideFullTiles;
+      bk.compress[0] = bk.is_fine ? bk.fine : bk.coarse;
     }
     // -- decompress: factor tiles and vectors, the Gram partials' sum, (row block, 1024-column group)
     // tiles, and beside those the Cholesky
@@ -592,7 +631,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       for (int32_t mi : xwide) qtiles(mi);
       if (static_cast<int64_t>(plan.tiles.size()) > l.tile_off && !vec_done) vec_tiles(bk), vec_done = true;
       sink.end(l, L);
-      qfin_launch(bk, L, false);
+      qfin_launch(bk, L, false, 0);
       if (!vec_done) {
         l = sink.begin(K_VEC, 0);
         vec_tiles(bk);
@@ -694,11 +733,17 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
           return rows * cols * 4.0 + rows * rr * 4.0 + (t.a == 0 ? cols * rr * 4.0 : 0.0);
         }
         return t.b * m * 4.0 + t.b * rr * 4.0 + (t.a == 0 ? m * rr * 4.0 : 0.0);
-      case K_WPSTEP:
-        return t.b * m * eb + t.b * rr * 8.0 + (t.a == 0 ? m * rr * 8.0 : 0.0);
+      case K_WPSTEP: {
+        const double rows = t.b & 0xff, c = (t.b >> 8) - 1;
+        const double cols = c < 0 ? m : std::min<double>(kWideChunk, m - c * kWideChunk);
+        return rows * cols * eb + rows * rr * 8.0 + (t.a == 0 ? cols * rr * 8.0 : 0.0);
+      }
+      case K_WPFIN:
+        return t.b * rr * 4.0 * (std::ceil(m / kWideChunk) + 2.0);
       case K_WQSTEP: {
-        const double r0 = double(t.a) * d.q_rows;
-        const double rows = std::min<double>(d.q_rows, n - r0);
+        const int32_t parts = l.variant == kWideFine ? static_cast<int32_t>(cdiv(d.q_rows, kWideSubRows)) : 1;
+        const double r0 = double(t.a / parts) * d.q_rows + double(t.a % parts) * kWideSubRows;
+        const double rows = std::min<double>(parts > 1 ? kWideSubRows : d.q_rows, n - r0);
         const double cw = double(q_tile_cols);  // a tile's columns
         const double cols = std::min<double>(cw, m - double(t.b) * cw);
         return rows * cols * eb + (t.b == 0 ? rows * rr * 8.0 : 0.0);
@@ -732,7 +777,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
   };
   auto family_of = [](int32_t kernel) -> int32_t {
     switch (kernel) {
-      case K_PFUSED: case K_PWIDE: case K_PFIN: case K_WPSTEP:
+      case K_PFUSED: case K_PWIDE: case K_PFIN: case K_WPSTEP: case K_WPFIN:
         return 1;  // ACP_KERNEL_P_STEP
       case K_QSTEP: case K_WQSTEP:
         return 2;  // ACP_KERNEL_Q_STEP
@@ -753,6 +798,8 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
   };
   for (BucketPlan& bk : plan.buckets) {
     annotate(bk.compress[0], false);
+    annotate(bk.coarse, false);
+    annotate(bk.fine, false);
     annotate(bk.compress[1], true);
     annotate(bk.decompress[0], false);
     annotate(bk.decompress[1], true);
@@ -774,6 +821,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       case K_PWIDE: return 10;
       case K_PFIN: return 11;
       case K_WPSTEP: return 12;
+      case K_WPFIN: return 13;
       case K_WQSTEP: return 22;
       case K_WFACT: return 40;
       case K_QSTEP: return 20;
@@ -830,7 +878,13 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       const int32_t b1 = std::min(nb, b0 + kMaxGroup);
       std::array<std::vector<Launch>, 2> gc, gd;
       for (int32_t par = 0; par < 2; ++par) {
-        gc[par] = merge(b0, b1, [par](const BucketPlan& bk) -> const std::vector<Launch>& { return bk.compress[par]; }, par == 1);
+        // Q-step of ranks 8..32: the whole group's tiles decide whether its chunks are split further
+        int64_t nt = 0;
+        for (int32_t b = b0; b < b1; ++b) nt += q_tiles(plan.buckets[b].coarse);
+        const bool pick = wide && r < kSplitRank && par == 0, fine = nt < kWideFullTiles;
+        gc[par] = merge(b0, b1, [par, pick, fine](const BucketPlan& bk) -> const std::vector<Launch>& {
+          return !pick ? bk.compress[par] : fine ? bk.fine : bk.coarse;
+        }, par == 1);
         gd[par] = merge(b0, b1, [par](const BucketPlan& bk) -> const std::vector<Launch>& { return bk.decompress[par]; }, par == 1);
       }
       plan.group_compress.push_back(gc);
@@ -851,12 +905,14 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
   plan.w_doubles = static_cast<int64_t>(plan.mats.size()) * r * r;
   plan.gpart_doubles = gpart;
   plan.qpart_floats = qpart;
+  plan.fpart_floats = fpart;
   int64_t off = 0;
   plan.off_e = off;     off = a256(off + e_floats * 4);
   plan.off_fac = off;   off = a256(off + fac_floats * 4);
   plan.off_w = off;     off = a256(off + plan.w_doubles * 8);
   plan.off_gpart = off; off = a256(off + gpart * 8);
   plan.off_qpart = off; off = a256(off + qpart * 4);
+  plan.off_fpart = off; off = a256(off + fpart * 4);
   plan.off_mats = off;  off = a256(off + static_cast<int64_t>(plan.mats.size() * sizeof(MatDesc)));
   plan.off_vecs = off;  off = a256(off + static_cast<int64_t>(plan.vecs.size() * sizeof(VecDesc)));
   plan.off_tiles = off; off = a256(off + static_cast<int64_t>(plan.tiles.size() * sizeof(Tile)));

@@ -29,9 +29,14 @@ struct BucketPlan {
   int64_t e_base = 0;                 // E arena offset of the bucket (floats)
   int64_t qpart_base = 0;             // first Q-step partial of the bucket's matrices (floats)
   int64_t qpart_floats = 0;           // Q-step partials of the bucket's matrices (floats)
+  int64_t fpart_base = 0, fpart_floats = 0;  // the same of its fine partials
   std::vector<int32_t> mats, vecs;    // members by kind
   bool xhold = false;                 // it has a matrix whose P-step leaves X in the arena
   std::vector<Launch> compress[2];    // [0] even step (Q-step), [1] odd step (P-step)
+  // ranks 8..32: the Q-step lists of whole row chunks, and split further; compress[0] is one of the
+  // two (is_fine)
+  std::vector<Launch> coarse, fine;
+  bool is_fine = false;
   std::vector<Launch> decompress[2];
   std::vector<Launch> emat;
   std::vector<Launch> draw[2];        // no reuse: the fresh reused factor and its W, before compress
@@ -56,9 +61,9 @@ struct Plan {
   std::vector<std::vector<Launch>> group_psgd_fact;
 
   // device state regions (byte offsets from the block base)
-  int64_t off_e = 0, off_fac = 0, off_w = 0, off_gpart = 0, off_qpart = 0;
+  int64_t off_e = 0, off_fac = 0, off_w = 0, off_gpart = 0, off_qpart = 0, off_fpart = 0;
   int64_t off_mats = 0, off_vecs = 0, off_tiles = 0, total_bytes = 0;
-  int64_t e_floats = 0, fac_floats = 0, w_doubles = 0, gpart_doubles = 0, qpart_floats = 0;
+  int64_t e_floats = 0, fac_floats = 0, w_doubles = 0, gpart_doubles = 0, qpart_floats = 0, fpart_floats = 0;
 };
 
 // Builds the plan; returns "" on success or an error text.

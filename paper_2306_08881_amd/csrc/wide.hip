@@ -42,25 +42,18 @@ __device__ inline v16f zero16() {
 }
 __device__ inline uint32_t u32(int64_t x) { return static_cast<uint32_t>(x); }
 
-// KH consecutive floats of a factor row starting at byte offset off (kOut: zeros); with
-// vec, four at a time (the resource base and off are 16-byte aligned).
+// KH consecutive floats of a factor row starting at byte offset off (kOut: zeros).
 template <int KH>
-__device__ inline void load_run(Rsrc r, uint32_t off, bool vec, float* out) {
-  if (vec) {
+__device__ inline void load_run(Rsrc r, uint32_t off, float* out) {
 #pragma unroll
-    for (int i = 0; i < KH / 4; ++i) {
-      const float4 f = bld4(r, off == kOut ? kOut : off + 16u * i);
-      out[4 * i + 0] = f.x;
-      out[4 * i + 1] = f.y;
-      out[4 * i + 2] = f.z;
-      out[4 * i + 3] = f.w;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < KH; ++i) out[i] = bld1(r, off == kOut ? kOut : off + 4u * i);
+  for (int i = 0; i < KH / 4; ++i) {
+    const float4 f = bld4(r, off == kOut ? kOut : off + 16u * i);
+    out[4 * i + 0] = f.x;
+    out[4 * i + 1] = f.y;
+    out[4 * i + 2] = f.z;
+    out[4 * i + 3] = f.w;
   }
 }
-__device__ inline bool aligned16(const float* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // P-step over a tile of at most 32 rows and all m columns on four waves: wave w walks the
 // 32-column blocks w, w + 4, ... in step with the others, so that the workgroup reads 512
@@ -77,6 +70,10 @@ __device__ inline bool aligned16(const float* p) { return (reinterpret_cast<uint
 // from the four waves' tiles and stores them as 16-byte vectors.  The four shares of P are added
 // in wave order through LDS at the end.  The next step's M and E are requested before the
 // current block's MFMAs, its factor rows after them.
+// A row longer than kWideChunk columns is cut into tiles of that many (t.b >> 8 is the chunk + 1),
+// whose sums of P go to the partial region for k_wpfin: a row walked whole is a serial chain of
+// steps of 2.2 us of latency each, and a bucket of 25 MiB at rank 32 has about 200 row tiles for
+// the GPU's 768 workgroup slots (BERT-base, rows of 3072 columns: 55 us a bucket, 30 by chunks).
 template <int RK>
 __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a) {
   constexpr int KH = RK / 2;
@@ -92,7 +89,9 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
   const int wave = __builtin_amdgcn_readfirstlane(tid() >> 6);
   const int lane = tid() & 63, h = lane >> 5, li = lane & 31;
   const int64_t m = d.m, r0 = t.a;
-  const int rows = t.b;
+  const int rows = t.b & 0xff, chunk = (t.b >> 8) - 1;  // chunk -1: all columns
+  const int64_t cbeg = chunk > 0 ? static_cast<int64_t>(chunk) * kWideChunk : 0;
+  const int64_t cend = chunk >= 0 && cbeg + kWideChunk < m ? cbeg + kWideChunk : m;
   const bool fform = deferred_of(a, d.bucket);
   const uint32_t row_bytes = u32(m) * 4u;
   const uint32_t ext = u32(rows) * row_bytes;
@@ -101,21 +100,21 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
   const Rsrc Phr = tile_rsrc(a.fac + d.ph_slot + r0 * RK, fform ? u32(rows) * RK * 4u : 0u);
   const Rsrc Qlr = tile_rsrc(a.fac + d.ql_slot, fform ? u32(m) * RK * 4u : 0u);
   const Rsrc Qhr = tile_rsrc(a.fac + (a.image ? d.q_slot : d.qh_slot), u32(m) * RK * 4u);
-  const bool ph4 = aligned16(a.fac + d.ph_slot), ql4 = aligned16(a.fac + d.ql_slot);
   static_assert(RK < kSplitRank, "from kSplitRank on the rank-split kernel takes the P-step");
   float pa[KH];  // correction A operand: -Ph[r0 + l % 32][KH h + s]
-  load_run<KH>(Phr, u32(li * RK + KH * h) * 4u, ph4, pa);
+  load_run<KH>(Phr, u32(li * RK + KH * h) * 4u, pa);
 #pragma unroll
   for (int s = 0; s < KH; ++s) pa[s] = -pa[s];
 
   // M and E of the step from column cs: the lane's four rows 8 w + 2 i + h, columns cs + 4 li ...
-  // (past m: zeros); as 16-byte vectors when rows and tile starts are 16-byte aligned, else
-  // float by float in the same layout
-  const bool vec = (m & 3) == 0 && aligned16(src_of(a, d.bucket) + d.grad_off + r0 * m) &&
-                   aligned16(a.e + d.e_off + r0 * m);
+  // (past cend: zeros); as 16-byte vectors, which need 4-byte alignment only, except where the
+  // last of them would reach into the next row: that step moves float by float
+  const bool m4 = (m & 3) == 0;
+  auto whole = [&](int64_t cs) { return m4 || cs + CS <= m; };
   const int vr = 8 * wave + h, vc = 4 * li;
   auto load_block = [&](int64_t cs, float4* g, float4* e) {
-    const int64_t col = cs + vc;
+    const int64_t col = cs < cend ? cs + vc : m;
+    const bool vec = whole(cs);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const uint32_t o = u32(vr + 2 * i) * row_bytes + u32(col) * 4u;
@@ -133,7 +132,7 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
   // the block's factor operands: Ql rows (correction B) and Qh rows (product B, rank block kb)
   auto load_ops = [&](int64_t c0, float* qa, float (*qb)[16]) {
     const int64_t qcol = c0 + li;
-    if (fform) load_run<KH>(Qlr, qcol < m ? u32(qcol * RK + KH * h) * 4u : kOut, ql4, qa);
+    if (fform) load_run<KH>(Qlr, qcol < m ? u32(qcol * RK + KH * h) * 4u : kOut, qa);
 #pragma unroll
     for (int kb = 0; kb < NR; ++kb)
 #pragma unroll
@@ -152,15 +151,15 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
   __shared__ __attribute__((aligned(16))) float st[32 * SP];
   float4 g[4], e[4];
   float qa[KH], qb[NR][16];
-  load_block(0, g, e);
-  load_ops(32 * wave, qa, qb);
+  load_block(cbeg, g, e);
+  load_ops(cbeg + 32 * wave, qa, qb);
 
   v16f p[NR];
 #pragma unroll
   for (int kb = 0; kb < NR; ++kb) p[kb] = zero16();
   int buf = 0;
   // every wave takes the same number of steps (blocks past m: zero loads, dropped stores)
-  for (int64_t cs = 0; cs < m; cs += CS, buf ^= 1) {
+  for (int64_t cs = cbeg; cs < cend; cs += CS, buf ^= 1) {
     const int64_t c0 = cs + 32 * wave;
     // M + E to the staging tile (the previous step's readers have passed its second barrier)
 #pragma unroll
@@ -183,6 +182,7 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
     {
       const float* xs = xtile(li >> 3, buf) + (vc & 31);
       const int64_t col = cs + vc;
+      const bool vec = whole(cs);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = vr + 2 * i;
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
 
   // the waves' shares of P, added in wave order: entry (v, lane) of rank block kb
   float* red = xt;  // kWidePWaves x 1024 floats per rank block (the transposing tiles are free)
-  float* P = dst_of(a, d.bucket) + d.fac_off_p;
+  float* P = chunk < 0 ? dst_of(a, d.bucket) + d.fac_off_p : a.qpart + d.qpart + static_cast<int64_t>(chunk) * d.n * RK;
   float* Pl = a.fac + d.pl_slot;
 #pragma unroll
   for (int kb = 0; kb < NR; ++kb) {
@@ -225,10 +225,39 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
       const int row = drow(v, ln >> 5), rank = kb * 32 + (ln & 31);
       if (rank < RK && row < rows) {
         P[(r0 + row) * RK + rank] = sum;
-        Pl[(r0 + row) * RK + rank] = sum;
+        if (chunk < 0) Pl[(r0 + row) * RK + rank] = sum;
       }
     }
   }
+}
+
+// P of the rows whose P-step ran by column chunks: the chunks' sums added in order, to the factor
+// buffer and the P_loc slot.  Tile: rows [t.a, t.a + t.b), one thread per four ranks of a row.
+template <int RK>
+__global__ __launch_bounds__(kBlock) void k_wpfin(KArgs a) {
+  const Tile t = a.tiles[blockIdx.x];
+  const MatDesc d = a.mats[t.idx];
+  if (tid() >= t.b * (RK / 4)) return;
+  const int64_t e = static_cast<int64_t>(t.a) * RK + tid() * 4;
+  const int nc = (d.m + kWideChunk - 1) / kWideChunk;
+  const int64_t stride = static_cast<int64_t>(d.n) * RK;  // one chunk's sums
+  const float* part = a.qpart + d.qpart + e;
+  constexpr int U = 4;  // sums requested at a time
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int c = 0; c < nc; c += U) {
+    float4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const float4*>(part + (c + u < nc ? c + u : nc - 1) * stride);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c + u < nc) s = s + v[u];
+  }
+  float* P = dst_of(a, d.bucket) + d.fac_off_p + e;
+  P[0] = s.x;
+  P[1] = s.y;
+  P[2] = s.z;
+  P[3] = s.w;
+  *reinterpret_cast<float4*>(a.fac + d.pl_slot + e) = s;
 }
 
 // Q-step over a tile (row chunk t.a of q_rows rows, column blocks 4 t.b ... 4 t.b + 3 of 32
@@ -242,7 +271,9 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
 // (row, column); F then is the A operand of Q += F^T Ph with the rows as K, and goes back into
 // the wave's block of the tile, from which every wave stores its rows of F as 16-byte vectors
 // after the block's last barrier.  Lane l's partial Q of column c0 + drow(v, l / 32), rank
-// l % 32, goes to the chunk's partial block for K_QFIN.
+// l % 32, goes to the chunk's partial block for K_QFIN.  A chunk's sum is that of its parts of
+// kWideSubRows rows, in order; a launch with too few tiles (kWideFine, as in the P-step) takes one
+// tile per part (t.a = chunk * parts + part) and leaves their addition to K_QFIN.
 template <int RK>
 __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a) {
   constexpr int KH = RK / 2;
@@ -252,8 +283,12 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
   const int wave = __builtin_amdgcn_readfirstlane(tid() >> 6);
   const int lane = tid() & 63, h = lane >> 5, li = lane & 31;
   const int64_t n = d.n, m = d.m;
-  const int64_t r0 = static_cast<int64_t>(t.a) * d.q_rows;
-  const int rows = static_cast<int>((r0 + d.q_rows < n) ? d.q_rows : n - r0);
+  const bool fine = a.variant == kWideFine;
+  const int parts = (d.q_rows + kWideSubRows - 1) / kWideSubRows;
+  const int64_t r0 = fine ? static_cast<int64_t>(t.a / parts) * d.q_rows + t.a % parts * kWideSubRows
+                          : static_cast<int64_t>(t.a) * d.q_rows;
+  const int64_t cap = fine ? (t.a % parts + 1 < parts ? kWideSubRows : d.q_rows - (parts - 1) * kWideSubRows) : d.q_rows;
+  const int rows = static_cast<int>((r0 + cap < n) ? cap : n - r0);
   const int64_t c0 = (static_cast<int64_t>(t.b) * kWideQWaves + wave) * d.q_cb;
   // valid columns of the wave's block: none for a block past m (its wave loads zeros, stores
   // nothing and keeps the others' barriers)
@@ -268,7 +303,7 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
   const float* ebase = a.e + d.e_off + r0 * m + ct;
   const Rsrc Gw = tile_rsrc(gbase, extw);
   const Rsrc Ew = tile_rsrc(ebase, a.ef ? extw : 0u);
-  const bool vec = (m & 3) == 0 && aligned16(gbase) && aligned16(ebase);
+  const bool vec = (m & 3) == 0 || wt == 32 * kWideQWaves;  // no 16-byte word reaches into the next row
   const Rsrc Qhr = tile_rsrc(a.fac + d.qh_slot + c0 * RK, xform ? u32(w) * RK * 4u : 0u);
   const Rsrc Plr = tile_rsrc(a.fac + d.pl_slot + r0 * RK, xform ? u32(rows) * RK * 4u : 0u);
   const Rsrc Phr = tile_rsrc(a.fac + d.ph_slot + r0 * RK, u32(rows) * RK * 4u);
@@ -278,8 +313,9 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
   for (int s = 0; s < KH; ++s) qv[s] = bld1(Qhr, u32(li * RK + KH * h + s) * 4u);
 
   // M and E of the 32-row block from row rb: the lane's rows rb + 8 w + 2 i + h, columns
-  // 4 li ... 4 li + 3 of the workgroup's (past wt or the chunk: zeros); 16-byte vectors when the
-  // rows and the first column are 16-byte aligned, else float by float in the same layout
+  // 4 li ... 4 li + 3 of the workgroup's (past wt or the chunk: zeros); 16-byte vectors (4-byte
+  // alignment is enough), except in a last column block of a row length that is not a multiple of
+  // four, which moves float by float
   const int vr = 8 * wave + h, vc = 4 * li;
   auto load_block = [&](int rb, float4* g, float4* e) {
 #pragma unroll
@@ -317,9 +353,12 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
   float4 g[4], e[4], fl, fh;
   load_block(0, g, e);
   load_fac(0, fl, fh);
-  v16f q[NR];
+  v16f q[NR], tot[NR];  // the sum of the current part, of the parts before it
 #pragma unroll
-  for (int kb = 0; kb < NR; ++kb) q[kb] = zero16();
+  for (int kb = 0; kb < NR; ++kb) {
+    q[kb] = zero16();
+    tot[kb] = zero16();
+  }
   int buf = 0;
   for (int rb = 0; rb < rows; rb += 32, buf ^= 1) {
     float* sb = st[buf];
@@ -372,11 +411,20 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
         bst1_nt(Ew, vc + 3 < wt ? o + 12u : kOut, f.w);
       }
     }
+    if ((rb + 32) % kWideSubRows == 0 && rb + 32 < rows) {  // the part ends and another follows
+#pragma unroll
+      for (int kb = 0; kb < NR; ++kb) {
+        tot[kb] += q[kb];
+        q[kb] = zero16();
+      }
+    }
   }
   if (w == 0) return;  // a block past m has no partials
+#pragma unroll
+  for (int kb = 0; kb < NR; ++kb) q[kb] = tot[kb] + q[kb];
   const int64_t ncb = (m + d.q_cb - 1) / d.q_cb;
   const int64_t stride = ncb * d.q_cb * RK;  // one row chunk of partials
-  float* part = a.qpart + d.qpart + static_cast<int64_t>(t.a) * stride + c0 * RK;
+  float* part = (fine ? a.fpart + d.fpart : a.qpart + d.qpart) + static_cast<int64_t>(t.a) * stride + c0 * RK;
 #pragma unroll
   for (int kb = 0; kb < NR; ++kb) {
     const int rank = kb * 32 + li;
@@ -393,8 +441,8 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
 // 4 (t % 32) ... of rows t / 32 + 8 i, so one store instruction writes 512 contiguous bytes of
 // each of two rows (the one-wave kernel's stores write 128 bytes of a row at a time).  Two LDS
 // tiles alternate, one barrier per step.  Rows past the tile fall outside the output resource;
-// columns past m are masked per float (16-byte stores need m and the tile start 16-byte aligned,
-// otherwise the same layout is stored float by float).
+// columns past m are masked (the last step of a row length that is not a multiple of four stores
+// float by float: its last 16-byte word would reach into the next row).
 template <int RK>
 __global__ __launch_bounds__(kBlock) void k_wrecon4w(KArgs a) {
   constexpr int KH = RK / 2;
@@ -412,27 +460,26 @@ __global__ __launch_bounds__(kBlock) void k_wrecon4w(KArgs a) {
   const float* B = odd ? a.fac + d.qh_slot : agg + d.fac_off_q;
   const Rsrc Ar = tile_rsrc(A + r0 * RK, u32(rows) * RK * 4u);
   const Rsrc Br = tile_rsrc(B, u32(m) * RK * 4u);
-  const bool a4 = aligned16(A), b4 = aligned16(B);
   float av[KH];  // A operand: A[r0 + l % 32][KH h + s] / p
-  load_run<KH>(Ar, u32(li * RK + KH * h) * 4u, a4, av);
+  load_run<KH>(Ar, u32(li * RK + KH * h) * 4u, av);
 #pragma unroll
   for (int s = 0; s < KH; ++s) av[s] *= a.inv_p;
   float* O = dst_of(a, d.bucket) + d.grad_off + r0 * m;
   const uint32_t row_bytes = u32(m) * 4u;
   const Rsrc Or = tile_rsrc(O, u32(rows) * row_bytes);
-  const bool vec = (m & 3) == 0 && aligned16(O);
+  const bool m4 = (m & 3) == 0;
   const int64_t c0 = static_cast<int64_t>(t.b) * kWideRCols;
   constexpr int NS = kWideRCols / 128;  // steps of four blocks
   auto bcol = [&](int k) { return c0 + k * 128 + wave * 32; };  // the wave's block at step k
   auto boff = [&](int k) { return bcol(k) + li < m ? u32((bcol(k) + li) * RK + KH * h) * 4u : kOut; };
   __shared__ __attribute__((aligned(16))) float tile[2][32 * LP];
   float bv[2][KH];
-  load_run<KH>(Br, boff(0), b4, bv[0]);
+  load_run<KH>(Br, boff(0), bv[0]);
   const int sc = tid() & 31, sr = tid() >> 5;  // store side: float4 column sc of rows sr + 8 i
   for (int k = 0; k < NS; ++k) {
     const int64_t cs = c0 + k * 128;  // the step's first column
     if (cs >= m) break;
-    if (k + 1 < NS) load_run<KH>(Br, boff(k + 1), b4, bv[(k + 1) & 1]);
+    if (k + 1 < NS) load_run<KH>(Br, boff(k + 1), bv[(k + 1) & 1]);
     v16f o = zero16();
 #pragma unroll
     for (int s = 0; s < KH; ++s) o = mfma(av[s], bv[k & 1][s], o);
@@ -441,6 +488,7 @@ __global__ __launch_bounds__(kBlock) void k_wrecon4w(KArgs a) {
     for (int v = 0; v < 16; ++v) tl[drow(v, h) * LP + wave * 32 + li] = o[v];
     __syncthreads();
     const int64_t col = cs + 4 * sc;
+    const bool vec = m4 || cs + 128 <= m;  // no 16-byte word reaches into the next row
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int r = sr + 8 * i;
@@ -484,6 +532,7 @@ hipError_t launch_wide_rank(const Launch& l, const KArgs& args, hipStream_t s) {
       case K_WPSTEP: hipLaunchKernelGGL(k_wpstep<RK>, grid, dim3(kWideBlock * kWidePWaves), 0, s, args); break;
       case K_WQSTEP: hipLaunchKernelGGL(k_wqstep<RK>, grid, dim3(kWideBlock * kWideQWaves), 0, s, args); break;
       case K_WRECON: hipLaunchKernelGGL(k_wrecon4w<RK>, grid, dim3(kBlock), 0, s, args); break;
+      case K_WPFIN: hipLaunchKernelGGL(k_wpfin<RK>, grid, dim3(kBlock), 0, s, args); break;
       default: return hipErrorInvalidValue;
     }
   } else {
