@@ -169,6 +169,16 @@ constexpr int32_t kCholBlockRank = 256;
 // rows (P-step) or columns (Q-step) of a tile from kSplitRank on, and rows of a decompress tile
 constexpr int split_fix(int r) { return r >= 256 ? 64 : 128; }
 constexpr int kSplitRecon = 128;
+// From kSplitRank on both steps' sums are those of parts of split_part(r) columns (P-step) or rows
+// (Q-step): a part's partial sum then costs 4 r / split_part(r) = 1 byte per element.  Lists with
+// fewer tiles than split_full_tiles (twice the workgroups that 256 CUs hold) take one tile per part.
+// At rank 256 the sum of the earlier parts would not fit the registers (P-step of BERT-base 0.96 ms
+// without it, 1.23 with): there every list takes one tile per part, and a Q-step chunk is one part
+constexpr int split_part(int r) { return 4 * r; }
+constexpr bool split_nested(int r) { return r < 256; }
+constexpr int64_t split_full_tiles(int r) { return r >= 128 ? 512 : 1024; }
+constexpr int part_rows(int r) { return r >= kSplitRank ? split_part(r) : 256; }  // of a Q-step part
+constexpr int kMaxParts = 4;  // parts of a Q-step chunk, at most
 // ranks whose orthogonal factor X W is formed on the fp64 matrix cores (one block of
 // min(r, 64) columns per tile; below kBlockedRank a factor has one such block)
 constexpr int32_t kApplyMfmaRank = 32;
@@ -184,12 +194,15 @@ constexpr int kWideQCols = 32;     // K_WQSTEP column block (one MFMA block)
 constexpr int kWidePWaves = 4;     // ranks 8..32: waves of a K_WPSTEP workgroup (adjacent column blocks)
 constexpr int kWideQWaves = 4;     // ranks 8..32: waves of a K_WQSTEP workgroup (adjacent column blocks)
 constexpr int kWideQRows = 512;    // K_WQSTEP rows per chunk (at most)
-constexpr int kWideRCols = 1024;   // K_WRECON columns per tile: 32 blocks of 32
+// K_WRECON columns per tile (its variant): a list with fewer than kWideRFull tiles of the wider one
+// takes the narrower
+constexpr int kWideRCols = 1024, kWideRNarrow = 256;
+constexpr int64_t kWideRFull = 128;
 constexpr int kWideChunk = 1024;   // K_WPSTEP columns per tile (longer rows: K_WPFIN adds the chunks' sums)
 // Ranks 8..32: a Q-step chunk's sum is that of its parts of kWideSubRows rows, in order; a list with
 // fewer than kWideFullTiles tiles (the workgroups that 256 CUs hold, three each, and a third more)
 // takes one tile per part (variant kWideFine of K_WQSTEP and K_QFIN)
-constexpr int kWideSubRows = 256;
+constexpr int kWideSubRows = part_rows(32);
 constexpr int32_t kWideFine = 1;
 constexpr int64_t kWideFullTiles = 1024;
 constexpr int kDrawRows = 256;     // K_DRAW factor rows per tile

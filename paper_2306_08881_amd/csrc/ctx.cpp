@@ -286,7 +286,7 @@ acp_status compress_bucket(acp_ctx* c, int64_t step, int32_t b, const float* gra
     };
     a.qpart = based(bk.qpart_base);
     a.fpart = based(bk.fpart_base);
-    if (!(step & 1) && bk.is_fine && bk.fpart_floats * 4 > acp::kScratchBytes) list = &bk.coarse;
+    if (bk.is_fine[step & 1] && bk.fpart_floats * 4 > acp::kScratchBytes) list = &bk.coarse[step & 1];
   }
   a.base = b;
   a.src[0] = grad;

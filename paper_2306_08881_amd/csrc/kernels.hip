@@ -579,7 +579,7 @@ __global__ __launch_bounds__(kBlock) void k_emat(KArgs a) {
 // Q-step finish: Q_loc = sum over the row chunks' partials.  A tile covers the NE entries
 // [t.a * NE, t.a * NE + NE) of the matrix (entry e = column * r + rank, NE = qfin_entries):
 // with NE > 256 each thread takes NE / 256 entries 256 apart, otherwise 256 / NE threads share
-// an entry.  FINE: the partials are those of the chunks' parts (kWideSubRows rows), added first.  Each thread adds a contiguous share of the chunks in chunk order, eight chunks
+// an entry.  FINE: the partials are those of the chunks' parts (part_rows(r) rows), added first.  Each thread adds a contiguous share of the chunks in chunk order, eight chunks
 // requested at a time, and the shares are added in thread order.  The result goes to the factor
 // buffer and to the Ql slot.
 template <int RK, bool FINE>
@@ -595,14 +595,20 @@ __global__ __launch_bounds__(kBlock) void k_qfin(KArgs a) {
   const int64_t stride = ncb * d.q_cb * RK;  // one row chunk of partials
   const int ne = qfin_entries(d.q_chunks);   // entries per tile
   const float* part = FINE ? a.fpart + d.fpart : a.qpart + d.qpart;
-  const int parts = FINE ? (d.q_rows + kWideSubRows - 1) / kWideSubRows : 1;  // 1 or 2
+  constexpr int PR = part_rows(RK), MP = kMaxParts;
+  const int parts = FINE ? (d.q_rows + PR - 1) / PR : 1;  // at most MP
   // chunk c's sum at entry offset o
   auto chunk = [&](int64_t c, int64_t o) {
     if constexpr (!FINE) return part[c * stride + o];
     const float* p = part + c * parts * stride + o;
-    // the chunk's second part has rows
-    const bool two = parts > 1 && c * d.q_rows + kWideSubRows < d.n;
-    return two ? p[0] + p[stride] : p[0];
+    float v[MP];  // a part past the chunk or the matrix has no rows
+#pragma unroll
+    for (int k = 0; k < MP; ++k) v[k] = k < parts && c * d.q_rows + k * PR < d.n ? p[k * stride] : 0.f;
+    float s = v[0];
+#pragma unroll
+    for (int k = 1; k < MP; ++k)
+      if (k < parts && c * d.q_rows + k * PR < d.n) s += v[k];
+    return s;
   };
   float* out = dst_of(a, d.bucket) + d.fac_off_q;
   float* ql = a.fac + d.ql_slot;
@@ -702,7 +708,7 @@ hipError_t launch_rank(const Launch& l, const KArgs& args, hipStream_t s) {
     case K_FACT: hipLaunchKernelGGL(k_fact<RK>, grid, block, 0, s, args); break;
     case K_CHOL: hipLaunchKernelGGL(k_chol<RK>, grid, block, 0, s, args); break;
     case K_QFIN:
-      if constexpr (RK >= kWideRank && RK < kSplitRank) {
+      if constexpr (RK >= kWideRank) {
         if (l.variant == kWideFine) {
           hipLaunchKernelGGL((k_qfin<RK, true>), grid, block, 0, s, args);
           break;

@@ -233,7 +233,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       // rows per chunk: kQRows (kWideQRows), fewer when a chunk's byte extent would pass 2^30
       // (the kernels address a tile with 32-bit offsets from the tile's first element)
       d.q_rows = static_cast<int32_t>(std::max<int64_t>(
-          1, std::min<int64_t>(wide ? (r >= kBlockedRank ? 4 * kWideQRows : kWideQRows) : kQRows,
+          1, std::min<int64_t>(wide ? (!split_nested(static_cast<int>(r)) ? split_part(static_cast<int>(r)) : r >= kBlockedRank ? 4 * kWideQRows : kWideQRows) : kQRows,
                                (int64_t(1) << 30) / (t.m * 4))));
       if (!wide) {
         // chunk rows of a multiple of 16 holding about the class's elements per tile
@@ -253,8 +253,11 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       bk.qpart_floats = qpart - bk.qpart_base;
       d.fpart = fpart;
       if (bk.mats.empty()) bk.fpart_base = fpart;
-      if (wide && r < kSplitRank)
-        fpart += align_up(int64_t(d.q_chunks) * cdiv(d.q_rows, kWideSubRows) * ncb * d.q_cb * r, kSlotAlign);
+      if (wide) {  // the Q-step's parts; from kSplitRank on the P-step's (a row of one part has none)
+        const int64_t pp = r >= kSplitRank ? cdiv(t.m, split_part(static_cast<int>(r))) : 1;
+        fpart += align_up(std::max(pp > 1 ? pp * t.n * r : 0, int64_t(d.q_chunks) * cdiv(d.q_rows, part_rows(static_cast<int>(r))) * ncb * d.q_cb * r),
+                          kSlotAlign);
+      }
       bk.fpart_floats = fpart - bk.fpart_base;
       d.bucket = b;
       // factor rows per Gram slice: at r <= 8 up to 8192 (one slice, and no K_CHOL, for
@@ -413,76 +416,83 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
     for (int32_t mi : bk.mats) row_tiles(mi, std::max<int64_t>(1, kTileElems / plan.mats[mi].m));
     sink.end(l, bk.emat);
   };
-  // tiles of a Q-step list's main launch
-  auto q_tiles = [&](const std::vector<Launch>& L) {
+  // matrix tiles of a compress list's main launch (ranks 8 and up), and how many fill the GPU
+  const int64_t full_tiles = r < kSplitRank ? kWideFullTiles : split_full_tiles(static_cast<int>(r));
+  auto main_tiles = [&](const std::vector<Launch>& L) {
     int64_t n = 0;
     for (const Launch& l : L)
-      if (l.kernel == K_WQSTEP) n += l.ntiles;
+      if (l.kernel == K_WPSTEP || l.kernel == K_WQSTEP)
+        for (int32_t i = 0; i < l.ntiles; ++i) n += plan.tiles[l.tile_off + i].kind != T_VEC;
+    return n;
+  };
+  auto recon_tiles = [&](const BucketPlan& bk) {  // decompress tiles of kWideRCols columns
+    int64_t n = 0;
+    for (const Launch& l : bk.recon[0][0])
+      if (l.kernel == K_WRECON) n += l.ntiles;
     return n;
   };
   // ranks 8..256: every matrix of the bucket takes the MFMA kernels
   auto wide_lists = [&](BucketPlan& bk) {
     // The compress kernels take matrix tiles, and the raw vectors ride along in the P-step and
     // Q-finish launches; factor tiles go to launches of their own.
-    // -- P-step (odd t): Qh = Q W, then row tiles (below kSplitRank one per kWideChunk columns, then
-    // the sum of a row's chunks)
-    {
-      std::vector<Launch>& L = bk.compress[1];
+    // -- P-step (odd t): Qh = Q W, then row tiles (below kSplitRank one per kWideChunk columns, from
+    // there on, fine, one per part), then the sum of a row's chunks or parts
+    const int32_t rk = static_cast<int32_t>(r);
+    auto p_list = [&](std::vector<Launch>& L, bool fine) {
       Launch l = sink.begin(K_APPLY, 1);
       apply_tiles(bk.mats, true);
       sink.end(l, L);
+      const int64_t cw = r < kSplitRank ? kWideChunk : fine || !split_nested(rk) ? split_part(rk) : kMaxCols;
+      const int64_t rows = r < kSplitRank ? 32 : split_fix(rk);
       l = sink.begin(K_WPSTEP, 0);
       for (int32_t mi : bk.mats) {
-        const int64_t nc = r < kSplitRank ? cdiv(plan.mats[mi].m, kWideChunk) : 1;
-        if (nc == 1) {
-          row_tiles(mi, r < kSplitRank ? 32 : split_fix(static_cast<int>(r)));
-          continue;
-        }
         const MatDesc& d = plan.mats[mi];
-        for (int64_t s = 0; s < d.n; s += 32)
+        const int64_t nc = cdiv(d.m, cw);
+        for (int64_t s = 0; s < d.n; s += rows)
           for (int64_t c = 0; c < nc; ++c)
             plan.tiles.push_back(Tile{T_ROWS, mi, static_cast<int32_t>(s),
-                                      static_cast<int32_t>(std::min<int64_t>(32, d.n - s) | ((c + 1) << 8))});
+                                      static_cast<int32_t>(std::min(rows, d.n - s) | (nc > 1 ? (c + 1) << 8 : 0))});
       }
       vec_tiles(bk);  // packed by the P-step launch's workgroups
       sink.end(l, L);
       l = sink.begin(K_WPFIN, 0);
       for (int32_t mi : bk.mats)
-        if (r < kSplitRank && plan.mats[mi].m > kWideChunk) row_tiles(mi, 4 * kBlock / r);
+        if (plan.mats[mi].m > cw) row_tiles(mi, 4 * kBlock / r);
       sink.end(l, L);
-    }
+    };
     // -- Q-step (even t): Ph = P W, (row chunk, column block) tiles (fine: of the chunks' parts),
     // vectors, finish
     auto q_list = [&](std::vector<Launch>& L, bool fine) {
       Launch l = sink.begin(K_APPLY, 0);
       apply_tiles(bk.mats, false);
       sink.end(l, L);
+      const int64_t pr = part_rows(rk);
       l = sink.begin(K_WQSTEP, fine ? kWideFine : 0);
       for (int32_t mi : bk.mats) {
         const MatDesc& d = plan.mats[mi];
         const int32_t ncb = static_cast<int32_t>(cdiv(d.m, q_tile_cols));
-        const int32_t parts = fine ? static_cast<int32_t>(cdiv(d.q_rows, kWideSubRows)) : 1;
+        const int32_t parts = fine ? static_cast<int32_t>(cdiv(d.q_rows, pr)) : 1;
         for (int32_t c = 0; c < d.q_chunks * parts; ++c) {
-          if (int64_t(c / parts) * d.q_rows + int64_t(c % parts) * kWideSubRows >= d.n) continue;  // no rows
+          if (int64_t(c / parts) * d.q_rows + (c % parts) * pr >= d.n) continue;  // no rows
           for (int32_t cb = 0; cb < ncb; ++cb) plan.tiles.push_back(Tile{T_QTILE, mi, c, cb});
         }
       }
       sink.end(l, L);
       qfin_launch(bk, L, true, fine ? kWideFine : 0);  // the vectors packed by the finish launch's workgroups
     };
-    if (r >= kSplitRank) {
-      q_list(bk.compress[0], false);
-    } else {
-      q_list(bk.coarse, false);
-      q_list(bk.fine, true);
-      bk.is_fine = q_tiles(bk.coarse) < kWideFullTiles;
-      bk.compress[0] = bk.is_fine ? bk.fine : bk.coarse;
+    for (const bool fine : {false, true}) {
+      p_list((fine ? bk.fine : bk.coarse)[1], fine);
+      q_list((fine ? bk.fine : bk.coarse)[0], fine);
+    }
+    for (int32_t par = 0; par < 2; ++par) {
+      bk.is_fine[par] = main_tiles(bk.coarse[par]) < full_tiles;
+      bk.compress[par] = (bk.is_fine[par] ? bk.fine : bk.coarse)[par];
     }
     // -- decompress: factor tiles and vectors, the Gram partials' sum, (row block, 1024-column group)
     // tiles, and beside those the Cholesky
     const int64_t recon_rows = r < kSplitRank ? 32 : kSplitRecon;
     for (int32_t par = 0; par < 2; ++par) {
-      std::vector<Launch>& L = bk.decompress[par];
+      std::vector<Launch>& L = bk.recon[0][par];
       const bool q = par == 0;
       Launch l = sink.begin(K_WFACT, 0);
       for (int32_t mi : bk.mats) fact_tiles(mi, q);
@@ -493,18 +503,28 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
         for (int32_t mi : bk.mats) gsum_tiles(mi, q);
         sink.end(l, L);
       }
-      l = sink.begin(K_WRECON, 0);
-      for (int32_t mi : bk.mats) {
-        const MatDesc& d = plan.mats[mi];
-        const int32_t nrb = static_cast<int32_t>(cdiv(d.n, recon_rows));
-        const int32_t ncg = static_cast<int32_t>(cdiv(d.m, kWideRCols));
-        for (int32_t rb = 0; rb < nrb; ++rb)
-          for (int32_t cg = 0; cg < ncg; ++cg) plan.tiles.push_back(Tile{T_QTILE, mi, rb, cg});
-      }
-      sink.end(l, L);
+      auto recon_list = [&](std::vector<Launch>& R, int32_t width) {
+        Launch w = sink.begin(K_WRECON, width);
+        for (int32_t mi : bk.mats) {
+          const MatDesc& d = plan.mats[mi];
+          const int32_t nrb = static_cast<int32_t>(cdiv(d.n, recon_rows));
+          const int32_t ncg = static_cast<int32_t>(cdiv(d.m, width));
+          for (int32_t rb = 0; rb < nrb; ++rb)
+            for (int32_t cg = 0; cg < ncg; ++cg) plan.tiles.push_back(Tile{T_QTILE, mi, rb, cg});
+        }
+        sink.end(w, R);
+      };
+      recon_list(L, kWideRCols);
       l = sink.begin(K_CHOL, 0);
       for (int32_t mi : bk.mats) chol_tiles(mi, q);
       sink.end(l, L);
+      // the same with narrower decompress tiles
+      std::vector<Launch> narrow;
+      recon_list(narrow, kWideRNarrow);
+      bk.recon[1][par] = L;
+      for (Launch& x : bk.recon[1][par])
+        if (x.kernel == K_WRECON) x = narrow[0];
+      bk.decompress[par] = bk.recon[recon_tiles(bk) < kWideRFull ? 1 : 0][par];
     }
     emat_launch(bk);
   };
@@ -735,15 +755,17 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
         return t.b * m * 4.0 + t.b * rr * 4.0 + (t.a == 0 ? m * rr * 4.0 : 0.0);
       case K_WPSTEP: {
         const double rows = t.b & 0xff, c = (t.b >> 8) - 1;
-        const double cols = c < 0 ? m : std::min<double>(kWideChunk, m - c * kWideChunk);
+        const double cw = r < kSplitRank ? kWideChunk : split_part(static_cast<int>(r));
+        const double cols = c < 0 ? m : std::min<double>(cw, m - c * cw);
         return rows * cols * eb + rows * rr * 8.0 + (t.a == 0 ? cols * rr * 8.0 : 0.0);
       }
       case K_WPFIN:
-        return t.b * rr * 4.0 * (std::ceil(m / kWideChunk) + 2.0);
+        return t.b * rr * 4.0 * (std::ceil(m / (r < kSplitRank ? kWideChunk : split_part(static_cast<int>(r)))) + 2.0);
       case K_WQSTEP: {
-        const int32_t parts = l.variant == kWideFine ? static_cast<int32_t>(cdiv(d.q_rows, kWideSubRows)) : 1;
-        const double r0 = double(t.a / parts) * d.q_rows + double(t.a % parts) * kWideSubRows;
-        const double rows = std::min<double>(parts > 1 ? kWideSubRows : d.q_rows, n - r0);
+        const int32_t pr = part_rows(static_cast<int>(r));
+        const int32_t parts = l.variant == kWideFine ? static_cast<int32_t>(cdiv(d.q_rows, pr)) : 1;
+        const double r0 = double(t.a / parts) * d.q_rows + double(t.a % parts) * pr;
+        const double rows = std::min<double>(parts > 1 ? pr : d.q_rows, n - r0);
         const double cw = double(q_tile_cols);  // a tile's columns
         const double cols = std::min<double>(cw, m - double(t.b) * cw);
         return rows * cols * eb + (t.b == 0 ? rows * rr * 8.0 : 0.0);
@@ -756,7 +778,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       case K_WRECON: {
         const double rb = r < kSplitRank ? 32.0 : kSplitRecon;
         const double rows = std::min<double>(rb, n - rb * t.a);
-        const double cols = std::min<double>(kWideRCols, m - double(kWideRCols) * t.b);
+        const double cols = std::min<double>(l.variant, m - double(l.variant) * t.b);
         return rows * cols * 4.0 + (t.b == 0 ? rows * rr * 4.0 : 0.0) + (t.a == 0 ? cols * rr * 4.0 : 0.0);
       }
       case K_APPLY:  // from kApplyMfmaRank on a tile covers one of apply_blocks(r) column blocks
@@ -798,8 +820,14 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
   };
   for (BucketPlan& bk : plan.buckets) {
     annotate(bk.compress[0], false);
-    annotate(bk.coarse, false);
-    annotate(bk.fine, false);
+    for (auto* lists : {bk.coarse, bk.fine}) {
+      annotate(lists[0], false);
+      annotate(lists[1], true);
+    }
+    for (auto& lists : bk.recon) {
+      annotate(lists[0], false);
+      annotate(lists[1], true);
+    }
     annotate(bk.compress[1], true);
     annotate(bk.decompress[0], false);
     annotate(bk.decompress[1], true);
@@ -878,14 +906,18 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       const int32_t b1 = std::min(nb, b0 + kMaxGroup);
       std::array<std::vector<Launch>, 2> gc, gd;
       for (int32_t par = 0; par < 2; ++par) {
-        // Q-step of ranks 8..32: the whole group's tiles decide whether its chunks are split further
-        int64_t nt = 0;
-        for (int32_t b = b0; b < b1; ++b) nt += q_tiles(plan.buckets[b].coarse);
-        const bool pick = wide && r < kSplitRank && par == 0, fine = nt < kWideFullTiles;
-        gc[par] = merge(b0, b1, [par, pick, fine](const BucketPlan& bk) -> const std::vector<Launch>& {
-          return !pick ? bk.compress[par] : fine ? bk.fine : bk.coarse;
+        // ranks 8 and up: the whole group's tiles decide whether its sums are split into parts and
+        // how many columns its decompress tiles take
+        int64_t nt = 0, nr = 0;
+        for (int32_t b = b0; b < b1; ++b) nt += main_tiles(plan.buckets[b].coarse[par]), nr += recon_tiles(plan.buckets[b]);
+        const bool fine = nt < full_tiles;
+        const int32_t rw = nr < kWideRFull ? 1 : 0;
+        gc[par] = merge(b0, b1, [par, wide, fine](const BucketPlan& bk) -> const std::vector<Launch>& {
+          return !wide ? bk.compress[par] : fine ? bk.fine[par] : bk.coarse[par];
         }, par == 1);
-        gd[par] = merge(b0, b1, [par](const BucketPlan& bk) -> const std::vector<Launch>& { return bk.decompress[par]; }, par == 1);
+        gd[par] = merge(b0, b1, [par, wide, rw](const BucketPlan& bk) -> const std::vector<Launch>& {
+          return !wide ? bk.decompress[par] : bk.recon[rw][par];
+        }, par == 1);
       }
       plan.group_compress.push_back(gc);
       plan.group_decompress.push_back(gd);

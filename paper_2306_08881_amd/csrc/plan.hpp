@@ -33,10 +33,12 @@ struct BucketPlan {
   std::vector<int32_t> mats, vecs;    // members by kind
   bool xhold = false;                 // it has a matrix whose P-step leaves X in the arena
   std::vector<Launch> compress[2];    // [0] even step (Q-step), [1] odd step (P-step)
-  // ranks 8..32: the Q-step lists of whole row chunks, and split further; compress[0] is one of the
+  // ranks 8 and up: the compress lists of whole sums, and split into parts; `compress` is one of the
   // two (is_fine)
-  std::vector<Launch> coarse, fine;
-  bool is_fine = false;
+  std::vector<Launch> coarse[2], fine[2];
+  bool is_fine[2] = {false, false};
+  // ranks 8 and up: the decompress lists with kWideRCols and with kWideRNarrow columns per tile
+  std::vector<Launch> recon[2][2];
   std::vector<Launch> decompress[2];
   std::vector<Launch> emat;
   std::vector<Launch> draw[2];        // no reuse: the fresh reused factor and its W, before compress

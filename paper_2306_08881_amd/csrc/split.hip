@@ -225,6 +225,12 @@ constexpr int fix_blocks(int rk) { return split_fix(rk) / 32; }
 // Compress step (see above).  PS: P-step over rows [t.a, t.a + t.b) (t.b <= split_fix) and all
 // columns, P_loc to the factor buffer and its slot.  Else Q-step over row chunk t.a and column
 // block t.b of split_fix columns, the product to the chunk's partials for K_QFIN.
+// The product's sum is that of its parts of split_part(r) walked indices, in order; a list with too
+// few tiles to fill the GPU (split_full_tiles) takes one tile per part (P-step: t.b >> 8 is the part
+// + 1; Q-step: variant kWideFine, t.a = chunk * parts + part), whose sums go to the fine partials
+// and are added by k_wpfin or K_QFIN in the same order: the same bits either way.  (One 186 x 5166
+// matrix at rank 64 is two tiles of 162 blocks: 774 us per two steps whole, 332 by parts.)  The sums
+// by parts are also closer to 64 bits (BERT-large rank 64, worst output 1.6e-6 to 0.7e-6).
 // Per block of 32 walked indices: the next block's M, E and factor rows are requested before this
 // block's products; a 32 x 32 block of M + E goes through an LDS tile (read with the lane on i) and
 // X back, so that memory sees 16-byte words; the factor tiles are shared, with a barrier before
@@ -246,24 +252,29 @@ __global__ __launch_bounds__(64 * fix_blocks(RK) * rank_waves(RK), 2) void k_bst
   const int64_t n = d.n, m = d.m;
   const bool m4 = (m & 3) == 0;
   // the tile's rows and first column; walked indices
-  const int64_t r0 = PS ? t.a : static_cast<int64_t>(t.a) * d.q_rows;
-  const int64_t c0 = PS ? 0 : static_cast<int64_t>(t.b) * FIX;
-  const int rows = PS ? t.b : static_cast<int>((r0 + d.q_rows < n) ? d.q_rows : n - r0);
-  const int64_t walk = PS ? m : rows;
+  constexpr int PART = split_part(RK);
+  const int parts = (d.q_rows + PART - 1) / PART;  // of a Q-step chunk
+  const int part = PS ? (t.b >> 8) - 1 : a.variant == kWideFine ? t.a % parts : -1;  // -1: all of them
+  const int chunk = PS || part < 0 ? t.a : t.a / parts;
+  const int64_t r0 = PS ? t.a : static_cast<int64_t>(chunk) * d.q_rows + (part > 0 ? part * PART : 0);
+  const int64_t c0 = PS ? (part > 0 ? static_cast<int64_t>(part) * PART : 0) : static_cast<int64_t>(t.b) * FIX;
+  const int64_t rend = part >= 0 && part + 1 < parts ? r0 + PART : static_cast<int64_t>(chunk + 1) * d.q_rows;
+  const int rows = PS ? t.b & 0xff : static_cast<int>((rend < n ? rend : n) - r0);
+  const int64_t walk = !PS ? rows : part >= 0 && m - c0 > PART ? PART : m - c0;
   const uint32_t row_bytes = u32(m) * 4u;
   // the wave's part of the tile: its rows (P-step) or columns (Q-step) and resources, at most 2^31
   // bytes (a row is at most 2^26, a Q-step chunk 2^30)
   const int wrows = PS ? (rows - 32 * ib < 32 ? rows - 32 * ib : 32) : rows;
-  const int64_t wm = PS ? m : m - c0 - 32 * ib;
+  const int64_t wm = PS ? m - c0 : m - c0 - 32 * ib;
   const bool on = wrows > 0 && wm > 0;
-  const int64_t first = on ? (PS ? (r0 + 32 * ib) * m : r0 * m + c0 + 32 * ib) : 0;
+  const int64_t first = on ? (PS ? (r0 + 32 * ib) * m + c0 : r0 * m + c0 + 32 * ib) : 0;
   const uint32_t ext = on ? u32(wrows - 1) * row_bytes + u32(wm) * 4u : 0u;
   const Rsrc G = tile_rsrc(src_of(a, d.bucket) + d.grad_off + first, ext);
   const Rsrc E = tile_rsrc(a.e + d.e_off + first, a.ef ? ext : 0u);
   const bool term = PS ? deferred_of(a, d.bucket) : deferred_p_of(a, d);
   const int64_t f0 = PS ? r0 : c0;                              // first fixed index
   const int64_t fix = PS ? rows : (m - c0 < FIX ? m - c0 : FIX);  // fixed indices of the tile
-  const int64_t w0 = PS ? 0 : r0;                               // first walked index
+  const int64_t w0 = PS ? c0 : r0;                              // first walked index
   const Rsrc R = tile_rsrc(a.fac + (PS ? d.ph_slot : d.qh_slot) + f0 * RK, term ? u32(fix) * RK * 4u : 0u);
   const float* S1 = a.fac + (PS ? d.ql_slot : d.pl_slot) + w0 * RK;
   const float* S2 = a.fac + (PS ? (a.image ? d.q_slot : d.qh_slot) : d.ph_slot) + w0 * RK;
@@ -277,7 +288,7 @@ __global__ __launch_bounds__(64 * fix_blocks(RK) * rank_waves(RK), 2) void k_bst
   // columns; the wave moves words kh NU ... of it
   const BlockMove<NU> mv(lane, kh * NU, row_bytes, PS ? wrows : 32);
   auto at = [&](int64_t j) { return j >= walk ? kOut : PS ? u32(j) * 4u : u32(j) * row_bytes; };
-  auto cols = [&](int64_t j) { return PS ? m - j : wm; };
+  auto cols = [&](int64_t j) { return PS ? wm - j : wm; };
 
   float4 g[NU], e[NU];
   RowFetch<RK, NT> x1;
@@ -302,9 +313,13 @@ __global__ __launch_bounds__(64 * fix_blocks(RK) * rank_waves(RK), 2) void k_bst
       const float x[8] = {p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w};
       rs[s] = split8(x);
     }
-  v16f acc[NR];
+  constexpr bool NEST = split_nested(RK);
+  v16f acc[NR], tot[NEST ? NR : 1];  // the sum of the current part, of the parts before it
 #pragma unroll
-  for (int kb = 0; kb < NR; ++kb) acc[kb] = zero16();
+  for (int kb = 0; kb < NR; ++kb) {
+    acc[kb] = zero16();
+    if constexpr (NEST) tot[kb] = zero16();
+  }
 
   for (int64_t j = 0; j < walk; j += kWalk) {
     if (term) x1.put(s1);
@@ -368,18 +383,32 @@ __global__ __launch_bounds__(64 * fix_blocks(RK) * rank_waves(RK), 2) void k_bst
     __syncthreads();  // every wave has read the factor tiles and written its share of X
 #pragma unroll
     for (int u = 0; u < NU; ++u) mv.store(E, at(j), u, cols(j), m4, *mv.word(st, u));
+    if (NEST && (j + kWalk) % PART == 0 && j + kWalk < walk) {  // the part ends and another follows
+#pragma unroll
+      for (int kb = 0; kb < NR; ++kb) {
+        tot[kb] += acc[kb];
+        acc[kb] = zero16();
+      }
+    }
   }
+#pragma unroll
+  for (int kb = 0; kb < NR; ++kb)
+    if constexpr (NEST) acc[kb] = tot[kb] + acc[kb];
 
   // lane l: fixed index 32 ib + l % 32, ranks RS kh + 32 kb + 8 q + 4 h ... + 3
   const int64_t i = 32 * ib + li;
   if (i >= fix) return;
   float *o1, *o2 = nullptr;
   if constexpr (PS) {
-    o1 = dst_of(a, d.bucket) + d.fac_off_p + (r0 + i) * RK;
-    o2 = a.fac + d.pl_slot + (r0 + i) * RK;
+    if (part >= 0) {
+      o1 = a.fpart + d.fpart + (static_cast<int64_t>(part) * n + r0 + i) * RK;
+    } else {
+      o1 = dst_of(a, d.bucket) + d.fac_off_p + (r0 + i) * RK;
+      o2 = a.fac + d.pl_slot + (r0 + i) * RK;
+    }
   } else {
     const int64_t ncb = (m + d.q_cb - 1) / d.q_cb;
-    o1 = a.qpart + d.qpart + static_cast<int64_t>(t.a) * ncb * d.q_cb * RK + (c0 + i) * RK;
+    o1 = (part >= 0 ? a.fpart + d.fpart : a.qpart + d.qpart) + static_cast<int64_t>(t.a) * ncb * d.q_cb * RK + (c0 + i) * RK;
   }
   typedef float v4u_f __attribute__((ext_vector_type(4), aligned(4)));  // the factor buffer is 4-byte aligned
 #pragma unroll
@@ -389,11 +418,11 @@ __global__ __launch_bounds__(64 * fix_blocks(RK) * rank_waves(RK), 2) void k_bst
       const v4u_f v = {acc[kb][4 * q], acc[kb][4 * q + 1], acc[kb][4 * q + 2], acc[kb][4 * q + 3]};
       const int k = RS * kh + 32 * kb + 8 * q + 4 * h;
       *reinterpret_cast<v4u_f*>(o1 + k) = v;
-      if constexpr (PS) *reinterpret_cast<v4u_f*>(o2 + k) = v;
+      if (PS && part < 0) *reinterpret_cast<v4u_f*>(o2 + k) = v;
     }
 }
 
-// Decompress, M_hat = A B^T / p, over 128 rows and 1024 columns (tile t.a, t.b): wave w keeps rows
+// Decompress, M_hat = A B^T / p, over 128 rows and a.variant columns (tile t.a, t.b): wave w keeps rows
 // 32 w ... of A / p split in registers, the workgroup walks the columns in blocks of 32 whose rows
 // of B are split once into LDS (two tiles in turn, one barrier per block), and the lane on the row
 // holds four adjacent columns per register group: the wave's block goes through its staging tile
@@ -408,9 +437,9 @@ __global__ __launch_bounds__(kBlock, RK == 64 ? 2 : 1) void k_brecon(KArgs a) {
   const int lane = tid() & 63, h = lane >> 5, li = lane & 31;
   const int64_t n = d.n, m = d.m;
   const bool m4 = (m & 3) == 0;
-  const int64_t r0 = static_cast<int64_t>(t.a) * kSplitRecon, c0 = static_cast<int64_t>(t.b) * kWideRCols;
+  const int64_t r0 = static_cast<int64_t>(t.a) * kSplitRecon, c0 = static_cast<int64_t>(t.b) * a.variant;
   const int rows = static_cast<int>((r0 + kSplitRecon < n) ? kSplitRecon : n - r0);
-  const int64_t wcols = m - c0 < kWideRCols ? m - c0 : kWideRCols;
+  const int64_t wcols = m - c0 < a.variant ? m - c0 : a.variant;
   const float* agg = src_of(a, d.bucket);
   const Rsrc A = tile_rsrc((odd ? agg + d.fac_off_p : a.fac + d.ph_slot) + r0 * RK, u32(rows) * RK * 4u);
   const float* B = (odd ? a.fac + d.qh_slot : agg + d.fac_off_q) + c0 * RK;

@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
   }
 }
 
-// P of the rows whose P-step ran by column chunks: the chunks' sums added in order, to the factor
+// P of the rows whose P-step ran by column chunks (from kSplitRank on: parts): their sums added in order, to the factor
 // buffer and the P_loc slot.  Tile: rows [t.a, t.a + t.b), one thread per four ranks of a row.
 template <int RK>
 __global__ __launch_bounds__(kBlock) void k_wpfin(KArgs a) {
@@ -239,9 +239,10 @@ __global__ __launch_bounds__(kBlock) void k_wpfin(KArgs a) {
   const MatDesc d = a.mats[t.idx];
   if (tid() >= t.b * (RK / 4)) return;
   const int64_t e = static_cast<int64_t>(t.a) * RK + tid() * 4;
-  const int nc = (d.m + kWideChunk - 1) / kWideChunk;
+  constexpr int CH = RK < kSplitRank ? kWideChunk : split_part(RK);
+  const int nc = (d.m + CH - 1) / CH;
   const int64_t stride = static_cast<int64_t>(d.n) * RK;  // one chunk's sums
-  const float* part = a.qpart + d.qpart + e;
+  const float* part = (RK < kSplitRank ? a.qpart + d.qpart : a.fpart + d.fpart) + e;
   constexpr int U = 4;  // sums requested at a time
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int c = 0; c < nc; c += U) {
@@ -434,7 +435,7 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
   }
 }
 
-// Decompress up to rank 32 with four waves per tile (32-row block t.a, 1024-column group t.b):
+// Decompress up to rank 32 with four waves per tile (32-row block t.a, group t.b of WC columns):
 // at step k the waves compute the 32 x 32 blocks 4k ... 4k + 3 (wave w block 4k + w), as the
 // one-wave kernel does, and put them in an LDS tile of 32 rows x 128 columns; then all 256
 // threads store that tile with 16-byte nontemporal stores, thread t taking the four columns
@@ -443,7 +444,7 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
 // tiles alternate, one barrier per step.  Rows past the tile fall outside the output resource;
 // columns past m are masked (the last step of a row length that is not a multiple of four stores
 // float by float: its last 16-byte word would reach into the next row).
-template <int RK>
+template <int RK, int WC>
 __global__ __launch_bounds__(kBlock) void k_wrecon4w(KArgs a) {
   constexpr int KH = RK / 2;
   constexpr int LP = 132;  // LDS row pitch (floats): rows stay 16-byte aligned for the reads
@@ -468,8 +469,8 @@ __global__ __launch_bounds__(kBlock) void k_wrecon4w(KArgs a) {
   const uint32_t row_bytes = u32(m) * 4u;
   const Rsrc Or = tile_rsrc(O, u32(rows) * row_bytes);
   const bool m4 = (m & 3) == 0;
-  const int64_t c0 = static_cast<int64_t>(t.b) * kWideRCols;
-  constexpr int NS = kWideRCols / 128;  // steps of four blocks
+  const int64_t c0 = static_cast<int64_t>(t.b) * WC;
+  constexpr int NS = WC / 128;  // steps of four blocks
   auto bcol = [&](int k) { return c0 + k * 128 + wave * 32; };  // the wave's block at step k
   auto boff = [&](int k) { return bcol(k) + li < m ? u32((bcol(k) + li) * RK + KH * h) * 4u : kOut; };
   __shared__ __attribute__((aligned(16))) float tile[2][32 * LP];
@@ -527,12 +528,18 @@ hipError_t launch_wide_rank(const Launch& l, const KArgs& args, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(l.ntiles));
   if (l.kernel == K_WFACT) {
     hipLaunchKernelGGL(k_wfact<RK>, grid, dim3(kBlock), 0, s, args);
+  } else if (l.kernel == K_WPFIN) {
+    hipLaunchKernelGGL(k_wpfin<RK>, grid, dim3(kBlock), 0, s, args);
   } else if constexpr (RK < kSplitRank) {
     switch (l.kernel) {
       case K_WPSTEP: hipLaunchKernelGGL(k_wpstep<RK>, grid, dim3(kWideBlock * kWidePWaves), 0, s, args); break;
       case K_WQSTEP: hipLaunchKernelGGL(k_wqstep<RK>, grid, dim3(kWideBlock * kWideQWaves), 0, s, args); break;
-      case K_WRECON: hipLaunchKernelGGL(k_wrecon4w<RK>, grid, dim3(kBlock), 0, s, args); break;
-      case K_WPFIN: hipLaunchKernelGGL(k_wpfin<RK>, grid, dim3(kBlock), 0, s, args); break;
+      case K_WRECON:
+        if (l.variant == kWideRNarrow)
+          hipLaunchKernelGGL((k_wrecon4w<RK, kWideRNarrow>), grid, dim3(kBlock), 0, s, args);
+        else
+          hipLaunchKernelGGL((k_wrecon4w<RK, kWideRCols>), grid, dim3(kBlock), 0, s, args);
+        break;
       default: return hipErrorInvalidValue;
     }
   } else {

@@ -10,6 +10,7 @@ import torch
 import synthgrad as sg
 from tests import parity_util as PU
 from tests.test_gpu_powersgd import run_psgd_parity
+from tests.test_gpu_state import _grouped_vs_per_bucket
 
 pytestmark = pytest.mark.gpu
 
@@ -64,3 +65,19 @@ def test_error_is_that_of_fp32(rank, scale):
         for k in range(a.shape[1]):  # one rounding per term, as a chain of fp32 multiply-adds has
             plain += a[:, k:k + 1] * b[k:k + 1, :]
         assert PU.rel_err(x, exact) <= 1.5 * PU.rel_err(plain, exact)
+
+
+@pytest.mark.parametrize("rank", [32, 128, 256])
+def test_split_sums_agree_between_calls(rank):
+    """Per-bucket calls, whose launches are too small to fill the GPU and split every sum into
+    parts, against all-bucket calls over enough buckets that they do not: the same bits."""
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    shapes = [(12000, 600), (77,), (600, 12000)] * 6
+    rng = np.random.default_rng(2)
+    base = {i: (0.02 * rng.standard_normal(s)).astype(np.float32) for i, s in enumerate(shapes[:3])}
+
+    def grads_of(t):
+        return {i: np.roll(base[i % 3], 7 * t + i).reshape(s) for i, s in enumerate(shapes)}
+
+    _grouped_vs_per_bucket(shapes, rank, grads_of, 4)
