@@ -178,7 +178,7 @@ constexpr int split_part(int r) { return 4 * r; }
 constexpr bool split_nested(int r) { return r < 256; }
 constexpr int64_t split_full_tiles(int r) { return r >= 128 ? 512 : 1024; }
 constexpr int part_rows(int r) { return r >= kSplitRank ? split_part(r) : 256; }  // of a Q-step part
-constexpr int kMaxParts = 4;  // parts of a Q-step chunk, at most
+constexpr int max_parts(int r) { return r == 128 ? 4 : 2; }  // parts of a Q-step chunk, at most (rank 256: one)
 // ranks whose orthogonal factor X W is formed on the fp64 matrix cores (one block of
 // min(r, 64) columns per tile; below kBlockedRank a factor has one such block)
 constexpr int32_t kApplyMfmaRank = 32;

@@ -229,11 +229,248 @@ __device__ void vec_tile(const KArgs& a, const Tile& t, bool compress) {
 // residual norm is at most tau times the column norm.
 
 typedef double v4d __attribute__((ext_vector_type(4)));
+
+// The lane's double from lane `src` of the wave (src uniform).
+__device__ inline double readlane_d(double v, int src) {
+  const int2 h = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(h.x, src),
+                                              __builtin_amdgcn_readlane(h.y, src)));
+}
+
+// 1 / sqrt(x) for x > 0: the hardware estimate, then two Newton steps y += y (1 - x y^2) / 2, each
+// of which squares the relative error.
+__device__ inline double rsqrt_newton(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+  return y;
+}
+
+// Cholesky G = R^T R with L^-1 = R^-T beside it, by the first wave, in place in A (shared memory, B
+// rows of 2 B: [G | I] on entry, [R | L^-1] on return; the caller synchronises before and after).
+// At pivot p the updated diagonal decides the drop (against ref(p)), row p is scaled by 1 / sqrt of
+// it and subtracted from the rows after it, in both halves:
+//   row p *= rinv;  row i -= R[p][i] row p  (i > p).
+// L^-1 = W^T, and its entries are those of the back substitution W[a][c] = (delta_ac - sum over
+// i < c of R[i][c] W[a][i]) / R[c][c] in the same order.  A dropped pivot's row is zero in both.
+// Lane j holds column j of A, rows p ... in g[0] ...: each pivot's
+// update also shifts the rows down one register, so that the pivots are one rolled loop.  The
+// chain is bound by latency, and before that by fetching instructions: unrolled over the pivots
+// the code ran once through tens of KB that no cache held (this form unrolled took 53 us a launch
+// at rank 32).  Launch at rank 32 with a second, unrolled pass of dependent divisions for W 22 us,
+// this way 17.7; rank 256, whose eight diagonal blocks come here, 432 and 351 us.
+template <int B, typename Ref>
+__device__ inline void chol_inverse(double* A, Ref ref) {
+  constexpr int LD = 2 * B;
+  static_assert(LD <= kWave, "one column per lane");
+  if (tid() >= kWave) return;
+  const int j = tid();
+  const bool on = j < LD;
+  double g[B < 2 ? 2 : B];
+  g[1] = 0.0;
+#pragma unroll
+  for (int a = 0; a < B; ++a) g[a] = A[a * LD + (on ? j : 0)];
+  const double refl = ref(j < B ? j : 0);
+  // 1 / sqrt of pivot p's diagonal dk, zero when it is dropped
+  auto pivot = [&](double dk, int p) {
+    const double rf = readlane_d(refl, p);
+    const double y = rsqrt_newton(dk);
+    return rf > 0.0 && dk > kTau * kTau * rf ? y : 0.0;
+  };
+  double rinv = pivot(readlane_d(g[0], 0), 0);
+#pragma unroll 1
+  for (int p = 0; p < B; ++p) {
+    double* row = A + p * LD;
+    // G's columns left of the pivot hold nothing of R's row; nor does a dropped pivot's, whatever g is
+    const double y = rinv > 0.0 && j >= p ? g[0] * rinv : 0.0;
+    if (on) row[j] = y;
+    asm volatile("" ::: "memory");  // one wave: its LDS accesses keep their order
+    // all of the row is requested at once (three entries at a time, as the compiler had it, were
+    // 640 of a pivot's 760 cycles); past R's row: rows that do not exist
+    double r[B < 3 ? 1 : B - 2];
+#pragma unroll
+    for (int a = 1; a < B - 1; ++a) r[a - 1] = row[p + 1 + a];
+    __builtin_amdgcn_sched_barrier(0);
+    // the next pivot's row and its root meanwhile
+    const double n0 = fma(-readlane_d(y, p + 1), y, g[1]);
+    rinv = pivot(readlane_d(n0, p + 1), p + 1 < B ? p + 1 : p);
+#pragma unroll
+    for (int a = 1; a < B - 1; ++a) g[a] = fma(-r[a - 1], y, g[a + 1]);
+    g[0] = n0;
+    asm volatile("" ::: "memory");
+  }
+}
+
+// A = [G | I] for chol_inverse, G in its left half already; by the whole workgroup.
+template <int B>
+__device__ inline void beside_identity(double* A) {
+  for (int e = tid(); e < B * B; e += kBlock) A[e / B * 2 * B + B + e % B] = e / B == e % B ? 1.0 : 0.0;
+}
+
+// Cholesky G = R^T R and W = R^-1 of a Gram matrix in shared memory (RK = 64 or 128, row-major; only
+// the upper triangle is read) for ranks from 64 on, by the whole workgroup, in blocks
+// of 32.  For each diagonal block K in order:
+//   (i)   one wave factors the block and forms W_KK = R_KK^-1 beside it (chol_inverse);
+//   (ii)  the block row right of it: R_KJ = W_KK^T G_KJ (with dropped pivots W_KK's zero columns
+//         give R's zero rows, as forward substitution over the kept pivots would);
+//   (iii) the trailing upper triangle: G_IJ -= R_KI^T R_KJ.
+// These are the pivots of the unblocked right-looking form, in the same order.  Then block column
+// J of W (J = 1, 2, 3) from the earlier ones: W_IJ = -(sum_{I <= L < J} W_IL R_LJ) W_JJ.  W[i][c]
+// (i < c) is kept in the strictly lower triangle at G[RK-1-i][RK-1-c] and its diagonal apart.
+// Dropped pivots give zero rows and columns of R and W.  G[] is overwritten.  The drop test
+// compares with the diagonal gref[i * gstride] (G's own unless given: a trailing block of a
+// larger Gram matrix is tested against that matrix's diagonal); W goes to w_out with rows ldw
+// apart.
+template <int RK>
+__device__ __attribute__((always_inline)) void cholesky_w_blocked(double* G, double* w_out, int ldw = RK,
+                                                                const double* gref = nullptr, int gstride = 0) {
+  static_assert((RK == 64 || RK == 128) && kBlock == 256, "blocks of 32 on 256 threads");
+  constexpr int B = 32, NBK = RK / B;
+  __shared__ double g0[RK], wdiag[RK];
+  // a diagonal block beside the identity, then one block column's W[0:k0][.] R[.][block] products
+  __shared__ double T[(RK - B) * B > 2 * B * B ? (RK - B) * B : 2 * B * B];
+  auto wl = [&](int i, int c) -> double& { return G[(RK - 1 - i) * RK + (RK - 1 - c)]; };  // W[i][c], i < c
+  for (int i = tid(); i < RK; i += kBlock) g0[i] = gref ? gref[i * gstride] : G[i * RK + i];
+  __syncthreads();
+  const int lane = tid() & 63;
+  for (int K = 0; K < NBK; ++K) {
+    const int k0 = K * B, nc = RK - k0 - B;  // columns right of the block
+    // (i) the diagonal block and W_KK (chol_inverse in T, which is free here)
+    for (int e = tid(); e < B * B; e += kBlock) {
+      const int a = e / B, c = e % B;
+      T[a * 2 * B + c] = G[(k0 + (a < c ? a : c)) * RK + k0 + (a < c ? c : a)];
+    }
+    beside_identity<B>(T);
+    __syncthreads();
+    chol_inverse<B>(T, [&](int p) { return g0[k0 + p]; });
+    __syncthreads();
+    for (int e = tid(); e < B * B; e += kBlock) {
+      const int a = e / B, c = e % B;
+      if (a <= c) G[(k0 + a) * RK + k0 + c] = T[a * 2 * B + c];
+      if (a < c) wl(k0 + a, k0 + c) = T[c * 2 * B + B + a];
+      if (a == c) wdiag[k0 + a] = T[a * 2 * B + B + a];
+    }
+    __syncthreads();
+    if (nc == 0) break;
+    // (ii) R_KJ = W_KK^T G_KJ on the fp64 matrix cores in 16 x 16 tiles (row block t % 2, column
+    // block t / 2, tile t on wave t % 4; one v_mfma_f64_16x16x4f64 per four ranks b, W_KK's operand
+    // zero past its column a >= b); every tile is formed before any is written
+    {
+      constexpr int QN = (2 * (RK - B) / 16 + 3) / 4;  // tiles per wave, at most
+      const int nt = 2 * (nc / 16), w = tid() / kWave, li = lane % 16, lk = lane / 16, c0 = k0 + B;
+      v4d acc[QN];
+#pragma unroll
+      for (int q = 0; q < QN; ++q) {
+        acc[q] = v4d{0.0, 0.0, 0.0, 0.0};
+        const int t = w + 4 * q, a = 16 * (t % 2) + li;
+        if (t < nt)
+#pragma unroll
+          for (int s4 = 0; s4 < B / 4; ++s4) {
+            const int b = 4 * s4 + lk;
+            const double wv = b < a ? wl(k0 + b, k0 + a) : (b == a ? wdiag[k0 + a] : 0.0);
+            acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv, G[(k0 + b) * RK + c0 + 16 * (t / 2) + li], acc[q], 0, 0, 0);
+          }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < QN; ++q) {
+        const int t = w + 4 * q;
+        if (t < nt)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) G[(k0 + 16 * (t % 2) + 4 * v + lk) * RK + c0 + 16 * (t / 2) + li] = acc[q][v];
+      }
+      __syncthreads();
+    }
+    // (iii) the trailing upper triangle: G[i][j] -= sum_a R[k0 + a][i] R[k0 + a][j], i <= j, on
+    // the fp64 matrix cores in 16 x 16 tiles (tiles ti <= tj, tile t on wave t % 4; one
+    // v_mfma_f64_16x16x4f64 per four rows a); entries below the diagonal of a diagonal tile are
+    // not written (that triangle keeps W)
+    {
+      const int nt = nc / 16, w = tid() / kWave, li = lane % 16, lk = lane / 16, c0 = k0 + B;
+      int t = 0;
+      for (int ti = 0; ti < nt; ++ti)
+        for (int tj = ti; tj < nt; ++tj, ++t) {
+          if (t % (kBlock / kWave) != w) continue;
+          v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int s4 = 0; s4 < B / 4; ++s4) {
+            const double* r = G + (k0 + 4 * s4 + lk) * RK + c0 + li;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(r[16 * ti], r[16 * tj], acc, 0, 0, 0);
+          }
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int i = c0 + 16 * ti + 4 * v + lk, j = c0 + 16 * tj + li;
+            if (i <= j) G[i * RK + j] -= acc[v];
+          }
+        }
+    }
+    __syncthreads();
+  }
+  // block columns of W: T = W[0:k0][0:k0] R[0:k0][block], then W[0:k0][block] = -T W_JJ, both
+  // on the fp64 matrix cores in 16 x 16 tiles (tile t of the k0 / 16 x 2 on wave t % 4; one
+  // v_mfma_f64_16x16x4f64 per four ranks, the operands of W taken from its triangle: zero below
+  // the diagonal, wdiag on it)
+  {
+    const int w = tid() / kWave, li = lane % 16, lk = lane / 16;
+    auto wv = [&](int r, int c) { return c > r ? wl(r, c) : (c == r ? wdiag[r] : 0.0); };  // W[r][c]
+    for (int J = 1; J < NBK; ++J) {
+      const int k0 = J * B, nt = 2 * (k0 / 16);
+      for (int t = w; t < nt; t += kBlock / kWave) {
+        const int i0 = 16 * (t / 2), c0 = 16 * (t % 2);
+        v4d acc = {0.0, 0.0, 0.0, 0.0};
+        for (int l0 = i0; l0 < k0; l0 += 4)  // W[i][l] is zero for l < i
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(wv(i0 + li, l0 + lk), G[(l0 + lk) * RK + k0 + c0 + li],
+                                                     acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) T[(i0 + 4 * v + lk) * B + c0 + li] = acc[v];
+      }
+      __syncthreads();
+      for (int t = w; t < nt; t += kBlock / kWave) {
+        const int i0 = 16 * (t / 2), c0 = 16 * (t % 2);
+        v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q0 = 0; q0 < B; q0 += 4)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(T[(i0 + li) * B + q0 + lk], wv(k0 + q0 + lk, k0 + c0 + li),
+                                                     acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) wl(i0 + 4 * v + lk, k0 + c0 + li) = -acc[v];
+      }
+      __syncthreads();
+    }
+  }
+  for (int e = tid(); e < RK * RK; e += kBlock) {
+    const int i = e / RK, c = e % RK;
+    w_out[i * ldw + c] = i < c ? wl(i, c) : (i == c ? wdiag[c] : 0.0);
+  }
+}
+
+// Floats between the rows of a Gram matrix in shared memory up to rank 64: the left half of [G | I]
+// where chol_inverse takes the whole matrix.  Rank 64 goes in two blocks of 32: in one, 126
+// multiply-adds a pivot on two columns per lane made the launch 89 us.
+constexpr int gram_ld(int rk) { return rk <= 32 ? 2 * rk : rk; }
+
+// W = R^-1 of the Gram matrix in A (shared memory, RK rows of gram_ld) into w_out, by the whole
+// workgroup; every entry of A is in place on entry.
+template <int RK>
+__device__ inline void cholesky_w(double* A, double* w_out) {
+  if constexpr (RK > 32) {
+    cholesky_w_blocked<RK>(A, w_out);
+  } else {
+    __shared__ double diag[RK];
+    beside_identity<RK>(A);
+    if (tid() < RK) diag[tid()] = A[tid() * (2 * RK + 1)];
+    __syncthreads();
+    chol_inverse<RK>(A, [&](int p) { return diag[p]; });
+    __syncthreads();
+    for (int e = tid(); e < RK * RK; e += kBlock) w_out[e] = A[e % RK * 2 * RK + RK + e / RK];
+  }
+}
+
 template <int RK, bool DIAG, int NB = 4>
 __device__ void gram_band(const float* X, int64_t r0, int64_t r1, float* copy, int I, int J, int nw, int w,
                           v4d (&acc)[NB][NB]);
 
-// Gram of rows [r0, r1) of X (row-major, RK columns) into shared G (RK rows of 2 RK: the left half),
+// Gram of rows [r0, r1) of X (row-major, RK columns) into shared G (RK rows of gram_ld),
 // by the whole workgroup, in a fixed order; the rows are also copied to `copy` when it is set.
 template <int RK>
 __device__ void gram_rows(const float* X, int64_t r0, int64_t r1, double* G, float* copy) {
@@ -284,8 +521,8 @@ __device__ void gram_rows(const float* X, int64_t r0, int64_t r1, double* G, flo
       while (rem >= RK - i) rem -= RK - i, ++i;
       const int j = i + rem;
       const double s = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
-      G[i * 2 * RK + j] = s;
-      G[j * 2 * RK + i] = s;
+      G[i * gram_ld(RK) + j] = s;
+      G[j * gram_ld(RK) + i] = s;
     }
     __syncthreads();
   } else if constexpr (RK == 16 || RK == 32 || RK == 64) {
@@ -304,101 +541,17 @@ __device__ void gram_rows(const float* X, int64_t r0, int64_t r1, double* G, flo
           for (int b = a; b < NB; ++b)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-              double& g = G[(16 * a + 4 * v + k) * 2 * RK + 16 * b + i];
+              double& g = G[(16 * a + 4 * v + k) * gram_ld(RK) + 16 * b + i];
               g = q == 0 ? acc[a][b][v] : g + acc[a][b][v];
             }
       __syncthreads();
     }
     for (int e = tid(); e < RK * RK; e += kBlock) {
       const int r = e / RK, c = e % RK;
-      if (r / 16 > c / 16) G[r * 2 * RK + c] = G[c * 2 * RK + r];
+      if (r / 16 > c / 16) G[r * gram_ld(RK) + c] = G[c * gram_ld(RK) + r];
     }
     __syncthreads();
   }
-}
-
-// The lane's double from lane `src` of the wave (src uniform).
-__device__ inline double readlane_d(double v, int src) {
-  const int2 h = __builtin_bit_cast(int2, v);
-  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(h.x, src),
-                                              __builtin_amdgcn_readlane(h.y, src)));
-}
-
-// 1 / sqrt(x) for x > 0: the hardware estimate, then two Newton steps y += y (1 - x y^2) / 2, each
-// of which squares the relative error.
-__device__ inline double rsqrt_newton(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-  return y;
-}
-
-// Cholesky G = R^T R with L^-1 = R^-T beside it, by the first wave, in place in A (shared memory, B
-// rows of 2 B: [G | I] on entry, [R | L^-1] on return; the caller synchronises before and after).
-// At pivot p the updated diagonal decides the drop (against ref(p)), row p is scaled by 1 / sqrt of
-// it and subtracted from the rows after it, in both halves:
-//   row p *= rinv;  row i -= R[p][i] row p  (i > p).
-// L^-1 = W^T, and its entries are those of the back substitution W[a][c] = (delta_ac - sum over
-// i < c of R[i][c] W[a][i]) / R[c][c] in the same order.  A dropped pivot's row is zero in both.
-// Lane j holds column j of A (B = 64: columns j and 64 + j), rows p ... in g[0] ...: each pivot's
-// update also shifts the rows down one register, so that the pivots are one rolled loop.  The
-// chain is bound by latency, and before that by fetching instructions: unrolled over the pivots
-// the code ran once through tens of KB that no cache held (this form unrolled took 53 us a launch
-// at rank 32).  Launch at rank 32 with a second, unrolled pass of dependent divisions for W 22 us,
-// this way 17.7; rank 256, whose eight diagonal blocks come here, 432 and 351 us.
-template <int B, typename Ref>
-__device__ inline void chol_inverse(double* A, Ref ref) {
-  constexpr int LD = 2 * B, NC = B > 32 ? 2 : 1;  // columns per lane
-  if (tid() >= kWave) return;
-  const int j = tid();
-  const bool on = j < LD;
-  double g[NC][B];
-#pragma unroll
-  for (int q = 0; q < NC; ++q)
-#pragma unroll
-    for (int a = 0; a < B; ++a) g[q][a] = A[a * LD + (on ? j : 0) + kWave * q];
-  const double refl = ref(j < B ? j : 0);
-#pragma unroll 1
-  for (int p = 0; p < B; ++p) {
-    const double dk = readlane_d(g[0][0], p), rf = readlane_d(refl, p);
-    const bool keep = rf > 0.0 && dk > kTau * kTau * rf;
-    const double rinv = keep ? rsqrt_newton(dk) : 0.0;
-    double* row = A + p * LD;
-    double y[NC];
-#pragma unroll
-    for (int q = 0; q < NC; ++q) {
-      // G's columns left of the pivot hold nothing of R's row
-      y[q] = keep && (q > 0 || j >= p) ? g[q][0] * rinv : 0.0;
-      if (on) row[j + kWave * q] = y[q];
-    }
-    asm volatile("" ::: "memory");  // one wave: its LDS accesses keep their order
-#pragma unroll
-    for (int a = 0; a < B - 1; ++a) {
-      const double r = row[p + 1 + a];  // past R's row: a row that does not exist
-#pragma unroll
-      for (int q = 0; q < NC; ++q) g[q][a] = fma(-r, y[q], g[q][a + 1]);
-    }
-    asm volatile("" ::: "memory");
-  }
-}
-
-// A = [G | I] for chol_inverse, G in its left half already; by the whole workgroup.
-template <int B>
-__device__ inline void beside_identity(double* A) {
-  for (int e = tid(); e < B * B; e += kBlock) A[e / B * 2 * B + B + e % B] = e / B == e % B ? 1.0 : 0.0;
-}
-
-// W = R^-1 of the Gram matrix in the left half of A (shared memory, RK rows of 2 RK) into w_out, by
-// the whole workgroup; every entry of A is in place on entry.
-template <int RK>
-__device__ inline void cholesky_w(double* A, double* w_out) {
-  __shared__ double diag[RK];
-  beside_identity<RK>(A);
-  if (tid() < RK) diag[tid()] = A[tid() * (2 * RK + 1)];
-  __syncthreads();
-  chol_inverse<RK>(A, [&](int p) { return diag[p]; });
-  __syncthreads();
-  for (int e = tid(); e < RK * RK; e += kBlock) w_out[e] = A[e % RK * 2 * RK + RK + e / RK];
 }
 
 // Band block X_I^T X_J of rows [r0, r1) of X (row-major, RK columns; 64-column bands I <= J)
@@ -536,13 +689,13 @@ __device__ void fact_tile(const KArgs& a, const Tile& t, const float* src, float
   } else {
     const int64_t r0 = static_cast<int64_t>(t.a) * d.fact_rows;
     const int64_t r1 = r0 + d.fact_rows < rows ? r0 + d.fact_rows : rows;
-    __shared__ double G[RK * 2 * RK];
+    __shared__ double G[RK * gram_ld(RK)];
     gram_rows<RK>(src, r0, r1, G, dst);
     if (t.b == 1) {
       cholesky_w<RK>(G, a.w + d.w_slot);
     } else {
       double* part = a.gpart + d.gpart + static_cast<int64_t>(t.a) * RK * RK;
-      for (int e = tid(); e < RK * RK; e += kBlock) part[e] = G[e / RK * 2 * RK + e % RK];
+      for (int e = tid(); e < RK * RK; e += kBlock) part[e] = G[e / RK * gram_ld(RK) + e % RK];
     }
   }
 }

@@ -75,139 +75,6 @@ __global__ __launch_bounds__(kBlock) void k_draw(KArgs a) {
   }
 }
 
-// Cholesky G = R^T R and W = R^-1 of a Gram matrix in shared memory (RK = 128, row-major; only
-// the upper triangle is read) for ranks from kBlockedRank on, by the whole workgroup, in blocks
-// of 32.  For each diagonal block K in order:
-//   (i)   one wave factors the block and forms W_KK = R_KK^-1 beside it (chol_inverse);
-//   (ii)  the block row right of it: R_KJ = W_KK^T G_KJ (with dropped pivots W_KK's zero columns
-//         give R's zero rows, as forward substitution over the kept pivots would);
-//   (iii) the trailing upper triangle: G_IJ -= R_KI^T R_KJ.
-// These are the pivots of the unblocked right-looking form, in the same order.  Then block column
-// J of W (J = 1, 2, 3) from the earlier ones: W_IJ = -(sum_{I <= L < J} W_IL R_LJ) W_JJ.  W[i][c]
-// (i < c) is kept in the strictly lower triangle at G[RK-1-i][RK-1-c] and its diagonal apart.
-// Dropped pivots give zero rows and columns of R and W.  G[] is overwritten.  The drop test
-// compares with the diagonal gref[i * gstride] (G's own unless given: a trailing block of a
-// larger Gram matrix is tested against that matrix's diagonal); W goes to w_out with rows ldw
-// apart.
-template <int RK>
-__device__ __attribute__((always_inline)) void cholesky_w_blocked(double* G, double* w_out, int ldw = RK,
-                                                                const double* gref = nullptr, int gstride = 0) {
-  static_assert(RK == 128 && kBlock == 256, "4 x 4 blocks of 32 on 256 threads");
-  constexpr int B = 32, NBK = RK / B;
-  __shared__ double g0[RK], wdiag[RK];
-  // a diagonal block beside the identity, then one block column's W[0:k0][.] R[.][block] products
-  __shared__ double T[(RK - B) * B];
-  static_assert((RK - B) * B >= 2 * B * B, "the diagonal block and the identity");
-  auto wl = [&](int i, int c) -> double& { return G[(RK - 1 - i) * RK + (RK - 1 - c)]; };  // W[i][c], i < c
-  for (int i = tid(); i < RK; i += kBlock) g0[i] = gref ? gref[i * gstride] : G[i * RK + i];
-  __syncthreads();
-  const int lane = tid() & 63;
-  for (int K = 0; K < NBK; ++K) {
-    const int k0 = K * B, nc = RK - k0 - B;  // columns right of the block
-    // (i) the diagonal block and W_KK (chol_inverse in T, which is free here)
-    for (int e = tid(); e < B * B; e += kBlock) {
-      const int a = e / B, c = e % B;
-      T[a * 2 * B + c] = G[(k0 + (a < c ? a : c)) * RK + k0 + (a < c ? c : a)];
-    }
-    beside_identity<B>(T);
-    __syncthreads();
-    chol_inverse<B>(T, [&](int p) { return g0[k0 + p]; });
-    __syncthreads();
-    for (int e = tid(); e < B * B; e += kBlock) {
-      const int a = e / B, c = e % B;
-      if (a <= c) G[(k0 + a) * RK + k0 + c] = T[a * 2 * B + c];
-      if (a < c) wl(k0 + a, k0 + c) = T[c * 2 * B + B + a];
-      if (a == c) wdiag[k0 + a] = T[a * 2 * B + B + a];
-    }
-    __syncthreads();
-    if (nc == 0) break;
-    // (ii) R_KJ = W_KK^T G_KJ: entry (k0 + a, k0 + B + c), a sum over b <= a
-    {
-      constexpr int QN = B * (RK - B) / kBlock;
-      double res[QN];
-#pragma unroll
-      for (int q = 0; q < QN; ++q) {
-        const int e = tid() + q * kBlock, a = e / nc, c = e % nc;
-        double v = 0.0;
-        if (e < B * nc) {
-          const int j = k0 + B + c;
-          double s2[2] = {wdiag[k0 + a] * G[(k0 + a) * RK + j], 0.0};
-          for (int b = 0; b < a; ++b) s2[b & 1] += wl(k0 + b, k0 + a) * G[(k0 + b) * RK + j];
-          v = s2[0] + s2[1];
-        }
-        res[q] = v;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < QN; ++q) {
-        const int e = tid() + q * kBlock;
-        if (e < B * nc) G[(k0 + e / nc) * RK + k0 + B + e % nc] = res[q];
-      }
-      __syncthreads();
-    }
-    // (iii) the trailing upper triangle: G[i][j] -= sum_a R[k0 + a][i] R[k0 + a][j], i <= j, on
-    // the fp64 matrix cores in 16 x 16 tiles (tiles ti <= tj, tile t on wave t % 4; one
-    // v_mfma_f64_16x16x4f64 per four rows a); entries below the diagonal of a diagonal tile are
-    // not written (that triangle keeps W)
-    {
-      const int nt = nc / 16, w = tid() / kWave, li = lane % 16, lk = lane / 16, c0 = k0 + B;
-      int t = 0;
-      for (int ti = 0; ti < nt; ++ti)
-        for (int tj = ti; tj < nt; ++tj, ++t) {
-          if (t % (kBlock / kWave) != w) continue;
-          v4d acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-          for (int s4 = 0; s4 < B / 4; ++s4) {
-            const double* r = G + (k0 + 4 * s4 + lk) * RK + c0 + li;
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(r[16 * ti], r[16 * tj], acc, 0, 0, 0);
-          }
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int i = c0 + 16 * ti + 4 * v + lk, j = c0 + 16 * tj + li;
-            if (i <= j) G[i * RK + j] -= acc[v];
-          }
-        }
-    }
-    __syncthreads();
-  }
-  // block columns of W: T = W[0:k0][0:k0] R[0:k0][block], then W[0:k0][block] = -T W_JJ, both
-  // on the fp64 matrix cores in 16 x 16 tiles (tile t of the k0 / 16 x 2 on wave t % 4; one
-  // v_mfma_f64_16x16x4f64 per four ranks, the operands of W taken from its triangle: zero below
-  // the diagonal, wdiag on it)
-  {
-    const int w = tid() / kWave, li = lane % 16, lk = lane / 16;
-    auto wv = [&](int r, int c) { return c > r ? wl(r, c) : (c == r ? wdiag[r] : 0.0); };  // W[r][c]
-    for (int J = 1; J < NBK; ++J) {
-      const int k0 = J * B, nt = 2 * (k0 / 16);
-      for (int t = w; t < nt; t += kBlock / kWave) {
-        const int i0 = 16 * (t / 2), c0 = 16 * (t % 2);
-        v4d acc = {0.0, 0.0, 0.0, 0.0};
-        for (int l0 = i0; l0 < k0; l0 += 4)  // W[i][l] is zero for l < i
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(wv(i0 + li, l0 + lk), G[(l0 + lk) * RK + k0 + c0 + li],
-                                                     acc, 0, 0, 0);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) T[(i0 + 4 * v + lk) * B + c0 + li] = acc[v];
-      }
-      __syncthreads();
-      for (int t = w; t < nt; t += kBlock / kWave) {
-        const int i0 = 16 * (t / 2), c0 = 16 * (t % 2);
-        v4d acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int q0 = 0; q0 < B; q0 += 4)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(T[(i0 + li) * B + q0 + lk], wv(k0 + q0 + lk, k0 + c0 + li),
-                                                     acc, 0, 0, 0);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) wl(i0 + 4 * v + lk, k0 + c0 + li) = -acc[v];
-      }
-      __syncthreads();
-    }
-  }
-  for (int e = tid(); e < RK * RK; e += kBlock) {
-    const int i = e / RK, c = e % RK;
-    w_out[i * ldw + c] = i < c ? wl(i, c) : (i == c ? wdiag[c] : 0.0);
-  }
-}
-
 // C = C0 + sg A B for 128 x 128 fp64 blocks in global or shared memory (sg = +1 or -1; C0 = 0
 // when c0 is null, else C0[i][j] = c0[i * ldc + j]), by the whole workgroup on the fp64 matrix
 // cores: wave w forms the 64 x 64 quadrant at rows 64 (w / 2), columns 64 (w % 2) as 4 x 4
@@ -357,11 +224,11 @@ __global__ __launch_bounds__(kBlock) void k_gsum(KArgs a) {
 // W from the Gram partials of a matrix's t.b slices, added in slice order (from kBlockedRank on
 // K_GSUM has added them into the first).
 template <int RK>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RK <= 32 ? 4 : 1))) void k_chol(KArgs a) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RK <= 32 ? 2 : 1))) void k_chol(KArgs a) {
   const Tile t = a.tiles[blockIdx.x];
   const MatDesc d = a.mats[t.idx];
   constexpr bool SPLIT = RK >= kCholBlockRank;
-  __shared__ double Gs[SPLIT ? 128 * 128 : RK >= kBlockedRank ? RK * RK : RK * 2 * RK];
+  __shared__ double Gs[SPLIT ? 128 * 128 : RK >= kBlockedRank ? RK * RK : RK * gram_ld(RK)];
   double* gp = a.gpart + d.gpart;
   if constexpr (RK >= kBlockedRank) {
     if constexpr (SPLIT) {
@@ -398,7 +265,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RK <= 32
     for (int q = 0; q < EPT; ++q)
     {
       const int e = tid() + q * kBlock;
-      if (e < RK * RK) Gs[e / RK * 2 * RK + e % RK] = acc[q];
+      if (e < RK * RK) Gs[e / RK * gram_ld(RK) + e % RK] = acc[q];
     }
     __syncthreads();
     cholesky_w<RK>(Gs, a.w + d.w_slot);
@@ -595,19 +462,21 @@ __global__ __launch_bounds__(kBlock) void k_qfin(KArgs a) {
   const int64_t stride = ncb * d.q_cb * RK;  // one row chunk of partials
   const int ne = qfin_entries(d.q_chunks);   // entries per tile
   const float* part = FINE ? a.fpart + d.fpart : a.qpart + d.qpart;
-  constexpr int PR = part_rows(RK), MP = kMaxParts;
+  constexpr int PR = part_rows(RK), MP = max_parts(RK);
   const int parts = FINE ? (d.q_rows + PR - 1) / PR : 1;  // at most MP
   // chunk c's sum at entry offset o
   auto chunk = [&](int64_t c, int64_t o) {
     if constexpr (!FINE) return part[c * stride + o];
     const float* p = part + c * parts * stride + o;
-    float v[MP];  // a part past the chunk or the matrix has no rows
+    float s = p[0];
 #pragma unroll
-    for (int k = 0; k < MP; ++k) v[k] = k < parts && c * d.q_rows + k * PR < d.n ? p[k * stride] : 0.f;
-    float s = v[0];
-#pragma unroll
-    for (int k = 1; k < MP; ++k)
-      if (k < parts && c * d.q_rows + k * PR < d.n) s += v[k];
+    for (int k = 1; k < MP; ++k) {
+      // a part past the chunk or the matrix has no rows: the first one is read again, without a
+      // branch, so that all parts of all the thread's entries are requested together
+      const bool has = k < parts && c * d.q_rows + k * PR < d.n;
+      const float v = p[has ? k * stride : 0];
+      s = has ? s + v : s;
+    }
     return s;
   };
   float* out = dst_of(a, d.bucket) + d.fac_off_q;
@@ -629,7 +498,7 @@ __global__ __launch_bounds__(kBlock) void k_qfin(KArgs a) {
       for (int k = 0; k < EPT; ++k)
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-          v[k][u] = (e[k] < m * RK && u < d.q_chunks) ? chunk(u, e[k]) : 0.f;
+          v[k][u] = chunk(u < d.q_chunks ? u : 0, e[k] < m * RK ? e[k] : 0);  // no branch around the requests
 #pragma unroll
       for (int k = 0; k < EPT; ++k)
 #pragma unroll
@@ -663,7 +532,7 @@ __global__ __launch_bounds__(kBlock) void k_qfin(KArgs a) {
     if (ch < ch1) {  // the rest (fewer than U chunks) requested together too, added in order
       float v[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = ch + u < ch1 ? chunk(ch + u, e) : 0.f;
+      for (int u = 0; u < U; ++u) v[u] = chunk(ch + u < ch1 ? ch + u : ch, e);
 #pragma unroll
       for (int u = 0; u < U; ++u)
         if (ch + u < ch1) s += v[u];
