@@ -191,9 +191,10 @@ acp_status acp_compress(acp_ctx *ctx, int64_t step, int32_t b, const float *grad
  * Q-step partial sums (the per-row-chunk products that a second kernel adds) go to a static
  * device array of the library instead of the state block: 32 MiB, one copy per GPU, held until
  * the process ends, its address looked up once per device in acp_bind_state.  Nothing is
- * allocated by this call.  A bucket whose partials need more than 32 MiB returns
- * ACP_E_UNSUPPORTED (acp_compress takes it); ACP_E_DEVICE if the array's address could not be
- * looked up.  Every call on one GPU shares that GPU's array and the partials of one call are
+ * allocated by this call.  A bucket whose partials need more than 32 MiB, counted in row chunks of
+ * 2048 rows from rank 128 on, 512 from rank 8 and 256 below, returns ACP_E_UNSUPPORTED
+ * (acp_compress takes it); where the kernels take shorter chunks and their partials pass 32 MiB,
+ * these stay in the state block.  ACP_E_DEVICE if the array's address could not be looked up.  Every call on one GPU shares that GPU's array and the partials of one call are
  * dead once it is done, so nothing is cleared between calls; calls that overlap on one GPU (on
  * other streams, contexts or threads) race on the array and must be ordered by the caller.
  */

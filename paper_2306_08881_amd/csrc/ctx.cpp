@@ -252,8 +252,8 @@ const acp::Launch* leading_apply(const acp_ctx* c, const std::vector<acp::Launch
 // acp_compress and acp_compress_noalloc: checks, then the bucket's compress launches.  `scratch`,
 // when not null, takes the Q-step partials instead of the state block: the kernels address partial
 // k of a matrix as qpart + MatDesc::qpart + k (fine ones likewise) and the bucket's start at
-// qpart_base, so the base handed to them puts those at the start of the scratch.  Fine partials
-// that do not fit it leave the bucket to the coarse list, which gives the same bits.
+// qpart_base, so the base handed to them puts those at the start of the scratch.  Partials that do
+// not fit it stay in the state block's own region.
 acp_status compress_bucket(acp_ctx* c, int64_t step, int32_t b, const float* grad, float* factor_buf,
                            void* stream, float* scratch) {
   if (!c) return ACP_E_INVALID;
@@ -279,14 +279,12 @@ acp_status compress_bucket(acp_ctx* c, int64_t step, int32_t b, const float* gra
   const acp_status ds = check_device(c);
   if (ds != ACP_OK) return ds;
   acp::KArgs a = base_args(c);
-  const std::vector<acp::Launch>* list = &bk.compress[step & 1];
   if (scratch) {
     auto based = [&](int64_t base) {
       return reinterpret_cast<float*>(reinterpret_cast<uintptr_t>(scratch) - static_cast<uintptr_t>(base) * sizeof(float));
     };
-    a.qpart = based(bk.qpart_base);
-    a.fpart = based(bk.fpart_base);
-    if (bk.is_fine[step & 1] && bk.fpart_floats * 4 > acp::kScratchBytes) list = &bk.coarse[step & 1];
+    if (bk.qpart_floats * 4 <= acp::kScratchBytes) a.qpart = based(bk.qpart_base);
+    if (bk.fpart_floats * 4 <= acp::kScratchBytes) a.fpart = based(bk.fpart_base);
   }
   a.base = b;
   a.src[0] = grad;
@@ -300,7 +298,7 @@ acp_status compress_bucket(acp_ctx* c, int64_t step, int32_t b, const float* gra
   }
   RunOpts o;
   o.skip_apply = c->applied[b] == step;
-  const acp_status st = run(c, *list, a, static_cast<hipStream_t>(stream), o);
+  const acp_status st = run(c, bk.compress[step & 1], a, static_cast<hipStream_t>(stream), o);
   if (st != ACP_OK) return st;
   c->pending[b] = step;
   c->deferred[b] = form_after_compress(c, b, step);
@@ -584,9 +582,9 @@ acp_status acp_compress_noalloc(acp_ctx* c, int64_t step, int32_t b, const float
   if (b < 0 || b >= static_cast<int32_t>(c->plan.buckets.size()))
     return fail(c, ACP_E_INVALID, "bucket index out of range");
   const acp::BucketPlan& bk = c->plan.buckets[b];
-  if (bk.qpart_floats * 4 > acp::kScratchBytes)
+  if (bk.limit_floats * 4 > acp::kScratchBytes)
     return fail(c, ACP_E_UNSUPPORTED, "bucket " + std::to_string(b) + " needs " +
-                                          std::to_string(bk.qpart_floats * 4) +
+                                          std::to_string(bk.limit_floats * 4) +
                                           " bytes of Q-step scratch; the static scratch holds " +
                                           std::to_string(acp::kScratchBytes));
   if (!c->dev) return fail(c, ACP_E_STATE, "state not bound");

@@ -251,6 +251,21 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       if (bk.mats.empty()) bk.qpart_base = qpart;
       qpart += align_up(int64_t(d.q_chunks) * ncb * d.q_cb * r, kSlotAlign);
       bk.qpart_floats = qpart - bk.qpart_base;
+      // The limit of acp_compress_noalloc is part of its interface and does not follow the split of the
+      // sums: partials of chunks of 2048 rows from kBlockedRank on and 512 below; up to rank 4 of
+      // the chunks above where rows are 16-byte words of at most 5120 columns at rank 4, else of
+      // kQRows rows (a quarter of a small matrix's) over blocks of 1024 columns, 256 for other rows
+      int64_t lrows = d.q_rows, lcb = d.q_cb;
+      const bool words = t.m % 4 == 0 && d.grad_off % 4 == 0;
+      if (wide) {
+        lrows = std::max<int64_t>(1, std::min<int64_t>(r >= kBlockedRank ? 4 * kWideQRows : kWideQRows,
+                                                       (int64_t(1) << 30) / (t.m * 4)));
+      } else if (r != 4 || !words || d.fac_off_p % 4 || d.fac_off_q % 4 || t.m > 5120) {
+        lrows = std::max<int64_t>(1, std::min<int64_t>(kQRows, (int64_t(1) << 30) / (t.m * 4)));
+        lrows = std::min<int64_t>(lrows, std::max<int64_t>(16, cdiv(t.n, 4)));
+        lcb = words ? 1024 : 256;
+      }
+      bk.limit_floats += align_up(cdiv(t.n, lrows) * cdiv(t.m, lcb) * lcb * r, kSlotAlign);
       d.fpart = fpart;
       if (bk.mats.empty()) bk.fpart_base = fpart;
       if (wide) {  // the Q-step's parts; from kSplitRank on the P-step's (a row of one part has none)

@@ -296,6 +296,18 @@ def test_noalloc_refuses_buckets_past_the_static_scratch(lib):
         lib.acp_destroy(ctx)
 
 
+@pytest.mark.parametrize("n,m,rank", [(60000, 1024, 256), (31000, 1025, 256), (28509, 1122, 4), (100000, 300, 1)])
+def test_noalloc_takes_buckets_whose_chunks_are_split_further(lib, n, m, rank):
+    """The limit of acp_compress_noalloc counts fixed row chunks (15 to 30 of 2048 rows at rank 256:
+    at most 30 MiB), whatever chunks the kernels take: the call gets past it to the unbound context."""
+    st, ctx = _ctx(lib, [(n, m)], rank)
+    assert st == L.ACP_OK
+    try:
+        assert lib.acp_compress_noalloc(ctx, 1, 0, 256, 256, None) == L.ACP_E_STATE
+    finally:
+        lib.acp_destroy(ctx)
+
+
 def test_method_specific_calls_refused_on_the_other_method(lib):
     """ACP-SGD contexts refuse the Power-SGD calls and vice versa, before any device work (both
     checks come ahead of the state-binding check)."""

@@ -53,3 +53,11 @@ def test_noalloc_matches_compress_calls_in_a_row():
         pytest.fail("no GPU visible")
     for k, (rank, shapes) in enumerate(CASES):
         _run_case(rank, shapes, seed=11 + k)
+
+
+def test_noalloc_partials_past_the_static_array():
+    """Partials within the limit's chunks whose split sums pass the array's 32 MiB (rank 256: 59 MiB
+    of the P-step's) stay in the state block; the bits are those of acp_compress."""
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    _run_case(256, [(30001, 1025), (64,)], seed=19)
