@@ -336,7 +336,7 @@ __device__ void rnarrow_tile(const KArgs& a, const Tile& t, const MatDesc& d, Fr
   for (int g = 0; g < G; ++g)
 #pragma unroll
     for (int c = 0; c < 4; ++c)
-      b[g][c] = ld_fr<RK>(B + static_cast<int64_t>(c < nm.nv[g] ? 4 * nm.c4[g] + c : 0) * RK);  // past m: unused
+      b[g][c] = c < nm.nv[g] ? ld_fr<RK>(B + static_cast<int64_t>(4 * nm.c4[g] + c) * RK) : zero_fr<RK>();
   __syncthreads();
   __builtin_amdgcn_s_waitcnt(0);
   const uint32_t row_bytes = static_cast<uint32_t>(d.m) * 4u;
@@ -432,11 +432,8 @@ struct Cols {
 // deferred).  Per row: M' = M + E (or M + F - Ph_row Q_loc^T), P = M' Qh summed over the row (DPP
 // wave sums, then the waves' sums in wave order), E = M' - P Qh^T written back, P written to the
 // factor buffer.  The next rows' M and E are requested before the reduction.
-// Waves per SIMD its registers are held to: without the bound some classes ended just past a step
-// (264 registers for two waves, 172 for three) and ran with one wave less.
-constexpr int pfused_waves(int rk, int S) { return rk == 1 && S <= 3 ? 3 : rk == 4 && S == 2 ? 3 : 2; }
 template <int RK, int S, int W = 4>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(pfused_waves(RK, S)))) void k_pfused(KArgs a) {
+__global__ __launch_bounds__(64 * W) void k_pfused(KArgs a) {
   constexpr int RB = Cols<RK, S, W>::RB;
   const Tile t = a.tiles[blockIdx.x];
   if (t.kind == T_VEC) {
@@ -654,7 +651,7 @@ __global__ __launch_bounds__(kBlock) void k_pfin(KArgs a) {
 // rows k_pwide takes, whose arena may hold X: F = M + X - P_loc Qh^T (a launch of their own: the
 // column rows of Qh would cost every row length the third wave per SIMD).
 template <int RK, bool XF>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(XF ? 2 : 3))) void k_qstep(KArgs a) {
+__global__ __launch_bounds__(kBlock) void k_qstep(KArgs a) {
   constexpr int U = 8;  // rows per group
   const Tile t = a.tiles[blockIdx.x];
   if (t.kind == T_VEC) {
@@ -796,7 +793,7 @@ __global__ __launch_bounds__(kBlock) void k_recon4(KArgs a) {
   Fr<RK> b[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c)
-    b[c] = ld_fr<RK>(B + (static_cast<int64_t>(cb) * 1024 + (lcol + c < cols ? lcol + c : 0)) * RK);  // past m: unused
+    b[c] = lcol + c < cols ? ld_fr<RK>(B + (static_cast<int64_t>(cb) * 1024 + lcol + c) * RK) : zero_fr<RK>();
   __syncthreads();
   // the B rows are in registers before the stores, so no wait for them lands between them
   __builtin_amdgcn_s_waitcnt(0);
