@@ -14,6 +14,10 @@ namespace {
 
 __device__ inline int tid() { return static_cast<int>(threadIdx.x); }
 
+// Between a wave's writes to shared memory and its reads of what other lanes wrote: the wave's LDS
+// accesses take effect in program order, so it is enough that the compiler keeps that order.
+__device__ inline void wave_lds_fence() { asm volatile("" ::: "memory"); }
+
 __device__ inline double wave_sum(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -284,7 +288,7 @@ __device__ inline void chol_inverse(double* A, Ref ref) {
     // G's columns left of the pivot hold nothing of R's row; nor does a dropped pivot's, whatever g is
     const double y = rinv > 0.0 && j >= p ? g[0] * rinv : 0.0;
     if (on) row[j] = y;
-    asm volatile("" ::: "memory");  // one wave: its LDS accesses keep their order
+    wave_lds_fence();
     // all of the row is requested at once (three entries at a time, as the compiler had it, were
     // 640 of a pivot's 760 cycles); past R's row: rows that do not exist
     double r[B < 3 ? 1 : B - 2];
@@ -297,7 +301,7 @@ __device__ inline void chol_inverse(double* A, Ref ref) {
 #pragma unroll
     for (int a = 1; a < B - 1; ++a) g[a] = fma(-r[a - 1], y, g[a + 1]);
     g[0] = n0;
-    asm volatile("" ::: "memory");
+    wave_lds_fence();
   }
 }
 

@@ -475,10 +475,9 @@ __global__ __launch_bounds__(kBlock, RK == 64 ? 2 : 1) void k_brecon(KArgs a) {
     for (int q = 0; q < 4; ++q)
       *reinterpret_cast<float4*>(st + li * kPitchM + 8 * q + 4 * h) =
           make_float4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
+    wave_lds_fence();  // other lanes' rows are read back (the next block's barrier follows these reads)
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      mv.store(O, u32(j) * 4u, u, m - c0 - j, m4,
-               *mv.word(st, u));
+    for (int u = 0; u < 4; ++u) mv.store(O, u32(j) * 4u, u, m - c0 - j, m4, *mv.word(st, u));
   }
 }
 
