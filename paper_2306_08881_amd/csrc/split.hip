@@ -180,7 +180,7 @@ struct RankFetch {
 // lanes per row of 128 bytes: word u of lane l is row l / 8 + 8 u, columns 4 (l % 8) ... + 3.  The
 // block starts at byte `at` of the resource; rows from `rows` on are left out, and `cols` columns
 // are in the matrix (a block with fewer than 32 moves float by float when the row length is not a
-// multiple of four: its last word would reach into the next row).
+// multiple of four: its last word would reach into the next row; one with none moves nothing).
 template <int NU>
 struct BlockMove {
   uint32_t off[NU];  // byte offset of the lane's words u0 ... u0 + NU - 1
@@ -284,11 +284,13 @@ __global__ __launch_bounds__(64 * fix_blocks(RK) * rank_waves(RK), 2) void k_bst
   __shared__ __attribute__((aligned(16))) float stage[IB][32 * kPitchM];
   __shared__ float4 share[KH > 1 ? IB * KH : 1][4][64];  // the waves' shares of D
   float* st = stage[ib];
-  // the block at walked index j: byte offset of its first element (kOut past the walk) and its
-  // columns; the wave moves words kh NU ... of it
+  // the block at walked index j: byte offset of its first element and its columns (none past the
+  // walk); the wave moves words kh NU ... of it
   const BlockMove<NU> mv(lane, kh * NU, row_bytes, PS ? wrows : 32);
-  auto at = [&](int64_t j) { return j >= walk ? kOut : PS ? u32(j) * 4u : u32(j) * row_bytes; };
-  auto cols = [&](int64_t j) { return PS ? wm - j : wm; };
+  auto at = [&](int64_t j) { return PS ? u32(j) * 4u : u32(j) * row_bytes; };
+  auto cols = [&](int64_t j) { return j >= walk ? 0 : PS ? wm - j : wm; };
+  // a left-out row's kOut plus a P-step's offset in the row (a Q-step leaves out none) does not wrap
+  static_assert(uint64_t{kOut} + 4 * uint64_t(kMaxCols + kWalk) < uint64_t{1} << 32, "kOut stays past the tile");
 
   float4 g[NU], e[NU];
   RowFetch<RK, NT> x1;
