@@ -210,6 +210,8 @@ constexpr int kDrawRows = 256;     // K_DRAW factor rows per tile
 // waves, for rows of 3076 to 4096 columns
 constexpr int32_t kThreeWaves = 32;
 constexpr int32_t kEightWaves = 64;
+// ... and on four waves with S = 2 to 5: some row length of the launch is not a multiple of four
+constexpr int32_t kRaggedRows = 128;
 // K_FACT variants: bit 0 = Q (else P); bit 1 (kFactFromBuffer): the factor is read from the
 // aggregated factor buffer (src) and copied into its slot, else read from its slot
 constexpr int32_t kFactFromBuffer = 2;

@@ -390,13 +390,24 @@ struct RowRsrc {
     return tile_rsrc(base, on && r < rows ? static_cast<uint32_t>(r) * step + width : 0u);
   }
 };
-// f(RAG) for the row length m
-template <typename F>
+// f(RAG) for the row length m of a matrix of a launch that takes any (ANY) or only multiples of four.
+// A kernel that holds both forms has the registers of the ragged one, which cost the P-step of 4100
+// to 5120 columns at rank 4 (and 2) one of its two waves per SIMD (252 VGPRs to 264), that of two
+// groups per lane at rank 1 and of three at rank 2 one of three.  So k_pfused of 2 to 5 groups is
+// built both ways and a launch without a ragged row takes the second: ResNet-50 rank 4 223.9 to
+// 215 us per two steps, ResNet-152 rank 2 411 to 402, rank 4 426 to 418.  The other kernels gain
+// nothing from their third wave: with the Q-step split the same way (170 to 148 VGPRs at rank 4)
+// BERT-large rank 4 took 1760 us instead of 1755, and with the P-step of one group per lane and
+// that of eight waves BERT-large rank 2 1754 instead of 1748.
+template <bool ANY, typename F>
 __device__ inline void by_raggedness(int m, F f) {
-  if (m & 3)
-    f(std::true_type{});
-  else
-    f(std::false_type{});
+  if constexpr (ANY) {
+    if (m & 3) {
+      f(std::true_type{});
+      return;
+    }
+  }
+  f(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------------------
@@ -432,7 +443,7 @@ struct Cols {
 // deferred).  Per row: M' = M + E (or M + F - Ph_row Q_loc^T), P = M' Qh summed over the row (DPP
 // wave sums, then the waves' sums in wave order), E = M' - P Qh^T written back, P written to the
 // factor buffer.  The next rows' M and E are requested before the reduction.
-template <int RK, int S, int W = 4>
+template <int RK, int S, bool ANY, int W = 4>
 __global__ __launch_bounds__(64 * W) void k_pfused(KArgs a) {
   constexpr int RB = Cols<RK, S, W>::RB;
   const Tile t = a.tiles[blockIdx.x];
@@ -452,7 +463,7 @@ __global__ __launch_bounds__(64 * W) void k_pfused(KArgs a) {
   }
   __shared__ Fr<RK> red[2][W][RB];
   __shared__ Fr<RK> phs[kMaxTileRows];  // the tile's rows of Ph (zero unless E is deferred)
-  by_raggedness(d.m, [&](auto rag) {
+  by_raggedness<ANY>(d.m, [&](auto rag) {
     constexpr bool RAG = decltype(rag)::value;
     const Cols<RK, S, W> cl(d.m);
     const bool deferred = deferred_of(a, d.bucket);
@@ -548,7 +559,7 @@ __global__ __launch_bounds__(kBlock) void k_pwide(KArgs a) {
   __shared__ double Wsh[RK * RK];
   __shared__ Fr<RK> red[2][4][RB];
   __shared__ Fr<RK> phs[kMaxTileRows];
-  by_raggedness(d.m, [&](auto rag) {
+  by_raggedness<true>(d.m, [&](auto rag) {
     constexpr bool RAG = decltype(rag)::value;
     const int wave = tid() >> 6, lane = tid() & 63;
     const bool deferred = deferred_of(a, d.bucket);
@@ -671,7 +682,7 @@ __global__ __launch_bounds__(kBlock) void k_qstep(KArgs a) {
     }
   }
   __shared__ Fr<RK> pls[XF ? kQRows : 1];
-  by_raggedness(d.m, [&](auto rag) {
+  by_raggedness<true>(d.m, [&](auto rag) {
     constexpr bool RAG = decltype(rag)::value;
     const int64_t m = d.m;
     const ChunkRows ch = q_chunk_rows(d, t.a);  // rows ch.first + k * ch.stride, k < ch.rows
@@ -802,7 +813,7 @@ __global__ __launch_bounds__(kBlock) void k_recon4(KArgs a) {
   const uint32_t width = static_cast<uint32_t>(cols) * 4u;
   const uint32_t coff = lcol < cols ? static_cast<uint32_t>(lcol) * 4u : kOut;
   // rows past the tile's count read unset LDS entries; their stores fall outside the resource
-  by_raggedness(d.m, [&](auto rag) {
+  by_raggedness<true>(d.m, [&](auto rag) {
     const RowRsrc<decltype(rag)::value> O(Ob, rows, step_bytes, width);
 #pragma unroll
     for (int k = 0; k < kReconRows; ++k) {
@@ -819,13 +830,17 @@ hipError_t launch_low_rank(const Launch& l, const KArgs& args, hipStream_t s) {
   switch (l.kernel) {
     case K_PFUSED:
       switch (l.variant) {
-        case 1: hipLaunchKernelGGL((k_pfused<RK, 1>), grid, block, 0, s, args); break;
-        case 1 | kThreeWaves: hipLaunchKernelGGL((k_pfused<RK, 1, 3>), grid, dim3(3 * kWave), 0, s, args); break;
-        case 2 | kEightWaves: hipLaunchKernelGGL((k_pfused<RK, 2, 8>), grid, dim3(8 * kWave), 0, s, args); break;
-        case 2: hipLaunchKernelGGL((k_pfused<RK, 2>), grid, block, 0, s, args); break;
-        case 3: hipLaunchKernelGGL((k_pfused<RK, 3>), grid, block, 0, s, args); break;
-        case 4: hipLaunchKernelGGL((k_pfused<RK, 4>), grid, block, 0, s, args); break;
-        case 5: hipLaunchKernelGGL((k_pfused<RK, 5>), grid, block, 0, s, args); break;
+        case 1: hipLaunchKernelGGL((k_pfused<RK, 1, true>), grid, block, 0, s, args); break;
+        case 1 | kThreeWaves: hipLaunchKernelGGL((k_pfused<RK, 1, true, 3>), grid, dim3(3 * kWave), 0, s, args); break;
+        case 2 | kEightWaves: hipLaunchKernelGGL((k_pfused<RK, 2, true, 8>), grid, dim3(8 * kWave), 0, s, args); break;
+        case 2: hipLaunchKernelGGL((k_pfused<RK, 2, false>), grid, block, 0, s, args); break;
+        case 3: hipLaunchKernelGGL((k_pfused<RK, 3, false>), grid, block, 0, s, args); break;
+        case 4: hipLaunchKernelGGL((k_pfused<RK, 4, false>), grid, block, 0, s, args); break;
+        case 5: hipLaunchKernelGGL((k_pfused<RK, 5, false>), grid, block, 0, s, args); break;
+        case 2 | kRaggedRows: hipLaunchKernelGGL((k_pfused<RK, 2, true>), grid, block, 0, s, args); break;
+        case 3 | kRaggedRows: hipLaunchKernelGGL((k_pfused<RK, 3, true>), grid, block, 0, s, args); break;
+        case 4 | kRaggedRows: hipLaunchKernelGGL((k_pfused<RK, 4, true>), grid, block, 0, s, args); break;
+        case 5 | kRaggedRows: hipLaunchKernelGGL((k_pfused<RK, 5, true>), grid, block, 0, s, args); break;
         default: return hipErrorInvalidValue;
       }
       break;

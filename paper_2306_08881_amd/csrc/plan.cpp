@@ -589,9 +589,11 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       auto pfused_tiles = [&](int32_t S) {
         // rows of 4 KB: 32K elements per tile; rows of 12 KB and more: 64K
         const int64_t base = (S >= 4 ? 4 : 2) * kTileElems;
-        for (int32_t mi : of_class(S))
+        for (int32_t mi : of_class(S)) {
           pstep_tiles(mi, rows_for(mi, std::max<int64_t>(kPMinRows * plan.mats[mi].m,
                                                           class_tile(K_PFUSED, S, base))));
+          if (S >= 2 && plan.mats[mi].m % 4) l.variant |= kRaggedRows;
+        }
       };
       for (int32_t S = 1; S <= 5; ++S) {
         const bool merged = S >= 2 && class_of_p(S) != S;
@@ -861,7 +863,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       case K_DRAW: return -3;
       case K_FACT: return -2;
       case K_APPLY: return 0;
-      case K_PFUSED: return (l.variant & kEightWaves) ? 8 : (l.variant & kThreeWaves) ? 7 : 1 + l.variant;  // 2..8
+      case K_PFUSED: return (l.variant & kEightWaves) ? 8 : (l.variant & kThreeWaves) ? 7 : 1 + (l.variant & ~kRaggedRows);  // 2..8
       case K_PWIDE: return 10;
       case K_PFIN: return 11;
       case K_WPSTEP: return 12;
@@ -882,6 +884,10 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
     std::vector<Launch> all;
     for (int32_t b = b0; b < b1; ++b)
       for (const Launch& l : get(plan.buckets[b])) all.push_back(l);
+    // a launch with some ragged rows takes the group's others of its class along: one launch per class
+    for (const Launch& x : all)
+      for (Launch& y : all)
+        if (x.kernel == K_PFUSED && y.kernel == K_PFUSED && y.variant == (x.variant & ~kRaggedRows)) y.variant = x.variant;
     // sorted by kind, then variant: every (kernel, variant) of the group becomes one launch
     std::stable_sort(all.begin(), all.end(), [&](const Launch& x, const Launch& y) {
       return order_of(x) != order_of(y) ? order_of(x) < order_of(y) : x.variant < y.variant;

@@ -33,6 +33,24 @@ def test_row_classes(rank, ef):
         assert not rep.failures, "\n".join(rep.failures[:20])
 
 
+# the same classes with whole 16-byte words only, whose launches take the kernels without the ragged form
+ALIGNED = [(9, 64), (70, 68), (33, 128), (41, 256), (65, 512), (66, 516), (5, 4), (63, 768), (20, 772), (8,),
+           (300, 1024), (40, 1028), (40, 2052), (17, 3072), (13, 3076), (12, 4096), (11, 4100), (9, 5120), (67, 5124),
+           (4,), (520, 5128), (16, 17004)]
+
+
+@pytest.mark.parametrize("rank", [1, 2, 4])
+@pytest.mark.parametrize("ef", [True, False])
+def test_aligned_row_classes(rank, ef):
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    params = [sg.Param(f"t{i}", s) for i, s in enumerate(ALIGNED)]
+    wl = sg.Workload("cols", params, rank, 7, lambda p: 0.05, seed=5, cap_bytes=1 << 20)
+    for grouped in (False, True):
+        rep = PU.run_parity(wl, "fresh", 5, range(1, 6), list(range(len(ALIGNED))), ef=ef, free=3, grouped=grouped)
+        assert not rep.failures, "\n".join(rep.failures[:20])
+
+
 @pytest.mark.parametrize("rank", [1, 4])
 def test_long_rows_resume_after_a_p_step(rank):
     """A state saved after an odd step (the long rows' arena holds X), and the same state with the
