@@ -296,7 +296,10 @@ acp_status acp_factor(const acp_ctx *ctx, int32_t tensor_id, int32_t which, floa
  * Checkpoint: acp_get_state writes the whole state (step counters, E, factors, orthogonalisation
  * transforms) into a host buffer of acp_checkpoint_bytes; acp_set_state restores it into a bound
  * context built with the same shapes, rank, seed, cap, world size and flags.  Both synchronise
- * the device.  Restoring and continuing is bitwise identical to not stopping.
+ * the device.  Restoring and continuing is bitwise identical to not stopping.  A state saved after
+ * an odd step at ranks 1 to 4 with rows of more than 5120 columns is marked as of version 2 (their E
+ * is stored with the step's product still in it), which a library that cannot read that form refuses;
+ * every other state is of version 1, and both are read.
  */
 acp_status acp_checkpoint_bytes(const acp_ctx *ctx, int64_t *bytes);
 acp_status acp_get_state(const acp_ctx *ctx, void *host_buf, int64_t bytes);

@@ -51,7 +51,9 @@ struct acp_ctx {
 namespace {
 
 constexpr uint64_t kMagic = 0x3153504341ull;  // "ACPS1"
-constexpr int64_t kVersion = 1;
+// Checkpoint versions: 2 where a bucket of rank 1 to 4 holds X (kHoldsX), which a library that only
+// knows version 1 would take for E; 1 otherwise.
+constexpr int64_t kVersion = 1, kVersionLowRankX = 2;
 
 // What the E arena of a bucket holds: E itself, F = M' after a Q-step (E = F - Ph Ql^T), or, after
 // a P-step of a bucket with such matrices, X = M' for those whose P-step leaves X
@@ -966,7 +968,9 @@ acp_status acp_get_state(const acp_ctx* c, void* host_buf, int64_t bytes) {
   const acp_status ds = check_device(c);
   if (ds != ACP_OK) return ds;
   const acp::Plan& p = c->plan;
-  CkptHeader h{kMagic, kVersion, c->num_tensors, p.rank, p.cap_bytes, c->world, c->flags,
+  bool low_x = false;
+  for (uint8_t form : c->deferred) low_x = low_x || (p.rank < acp::kWideRank && form == kHoldsX);
+  CkptHeader h{kMagic, low_x ? kVersionLowRankX : kVersion, c->num_tensors, p.rank, p.cap_bytes, c->world, c->flags,
                static_cast<int64_t>(p.buckets.size()), static_cast<int64_t>(c->seed),
                p.e_floats, p.fac_floats, p.w_doubles};
   uint8_t* o = static_cast<uint8_t*>(host_buf);
@@ -999,7 +1003,7 @@ acp_status acp_set_state(acp_ctx* c, const void* host_buf, int64_t bytes) {
   const acp::Plan& p = c->plan;
   CkptHeader h{};
   std::memcpy(&h, host_buf, sizeof(h));
-  if (h.magic != kMagic || h.version != kVersion || h.num_tensors != c->num_tensors ||
+  if (h.magic != kMagic || (h.version != kVersion && h.version != kVersionLowRankX) || h.num_tensors != c->num_tensors ||
       h.rank != p.rank || h.cap != p.cap_bytes || h.world != c->world ||
       h.flags != static_cast<int64_t>(c->flags) || h.nbuckets != static_cast<int64_t>(p.buckets.size()) ||
       h.seed != static_cast<int64_t>(c->seed) || h.e_floats != p.e_floats ||

@@ -8,6 +8,7 @@ import pytest
 import torch
 
 import synthgrad as sg
+from paper_2306_08881_amd import _lib as L
 from tests import parity_util as PU
 from tests.test_gpu_powersgd import run_psgd_parity
 
@@ -66,7 +67,10 @@ def test_long_rows_resume_after_a_p_step(rank):
     blob = bytearray(a.acp.get_state())
     a.acp.error(0, a.ebuf[0])
     torch.cuda.synchronize()
+    version = slice(8, 16)  # after the magic number
+    assert blob[version] == np.int64(2).tobytes()  # a library without the form has to refuse it
     explicit = bytearray(blob)
+    explicit[version] = np.int64(1).tobytes()
     head = 96 + 8  # the record of the only bucket: step, then the arena's form
     assert np.frombuffer(blob, np.int64, 2, 96).tolist() == [3, 2]
     explicit[head:head + 8] = np.int64(0).tobytes()
@@ -76,6 +80,10 @@ def test_long_rows_resume_after_a_p_step(rank):
         at = 96 + 16 + 4 * off
         explicit[at:at + 4 * k] = e[off:off + k].tobytes()
     b, c = PU.Runner(shapes, rank), PU.Runner(shapes, rank)
+    unknown = bytearray(blob)
+    unknown[version] = np.int64(3).tobytes()
+    with pytest.raises(L.AcpError):
+        b.acp.set_state(bytes(unknown))
     b.acp.set_state(bytes(blob))
     c.acp.set_state(bytes(explicit))
     for t in (4, 5):
@@ -86,6 +94,8 @@ def test_long_rows_resume_after_a_p_step(rank):
         assert torch.equal(a.fbuf[0], b.fbuf[0]) and torch.equal(a.out[0], b.out[0]), t
         # the residual's term is rounded once more when it is written out: a few fp32 roundings
         assert PU.rel_err(c.out[0].cpu().numpy(), a.out[0].cpu().numpy()) < 1e-5, t
+        if t == 4:  # after an even step every matrix has the form version 1 knows
+            assert bytes(a.acp.get_state())[version] == np.int64(1).tobytes()
 
 
 @pytest.mark.parametrize("rank", [1, 2, 4, 8])
