@@ -191,12 +191,25 @@ acp_status acp_compress(acp_ctx *ctx, int64_t step, int32_t b, const float *grad
  * Q-step partial sums (the per-row-chunk products that a second kernel adds) go to a static
  * device array of the library instead of the state block: 32 MiB, one copy per GPU, held until
  * the process ends, its address looked up once per device in acp_bind_state.  Nothing is
- * allocated by this call.  A bucket whose partials need more than 32 MiB, counted in row chunks of
- * 2048 rows from rank 128 on, 512 from rank 8 and 256 below, returns ACP_E_UNSUPPORTED
- * (acp_compress takes it); where the kernels take shorter chunks and their partials pass 32 MiB,
- * these stay in the state block.  ACP_E_DEVICE if the array's address could not be looked up.  Every call on one GPU shares that GPU's array and the partials of one call are
- * dead once it is done, so nothing is cleared between calls; calls that overlap on one GPU (on
- * other streams, contexts or threads) race on the array and must be ordered by the caller.
+ * allocated by this call.  Partials of more than 32 MiB stay in the state block.
+ *
+ * A bucket that counts more than 32 MiB returns ACP_E_UNSUPPORTED (acp_compress takes it).  The
+ * count does not follow what the kernels do: each compressed n x m matrix counts
+ * ceil(n / c) ceil(m / w) w r floats, rounded up to 64, with
+ *   from rank 8 on   w = 32, c = 512 (from rank 128 on 2048);
+ *   up to rank 4     w = 1024, or 256 where m or the matrix's offset in the gradient bucket is not a
+ *                    multiple of 4, and c = ceil(n / 4) between 16 and 256;
+ *   rank 4, m <= 5120, and m and the matrix's three offsets multiples of 4
+ *                    w = 1024, c = max(2048, floor(S / 1024)) / min(m, 1024), rounded down to a
+ *                    multiple of 16, between 16 and 256, S being the elements of all such
+ *                    matrices of the model of the same class of row length (m <= 64, 128, 256, 512,
+ *                    5120);
+ * and everywhere c at most floor(2^28 / m), at least 1.
+ *
+ * ACP_E_DEVICE if the array's address could not be looked up.  Every call on one GPU shares that
+ * GPU's array and the partials of one call are dead once it is done, so nothing is cleared between
+ * calls; calls that overlap on one GPU (on other streams, contexts or threads) race on the array and
+ * must be ordered by the caller.
  */
 acp_status acp_compress_noalloc(acp_ctx *ctx, int64_t step, int32_t b, const float *grad,
                                 float *factor_buf, void *stream);

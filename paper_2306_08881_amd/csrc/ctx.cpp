@@ -585,9 +585,8 @@ acp_status acp_compress_noalloc(acp_ctx* c, int64_t step, int32_t b, const float
     return fail(c, ACP_E_INVALID, "bucket index out of range");
   const acp::BucketPlan& bk = c->plan.buckets[b];
   if (bk.limit_floats * 4 > acp::kScratchBytes)
-    return fail(c, ACP_E_UNSUPPORTED, "bucket " + std::to_string(b) + " needs " +
-                                          std::to_string(bk.limit_floats * 4) +
-                                          " bytes of Q-step scratch; the static scratch holds " +
+    return fail(c, ACP_E_UNSUPPORTED, "bucket " + std::to_string(b) + " counts " + std::to_string(bk.limit_floats * 4) +
+                                          " bytes of Q-step partials; the static scratch holds " +
                                           std::to_string(acp::kScratchBytes));
   if (!c->dev) return fail(c, ACP_E_STATE, "state not bound");
   if (!c->scratch) return fail(c, ACP_E_DEVICE, c->scratch_err);

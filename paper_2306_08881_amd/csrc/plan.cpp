@@ -188,6 +188,35 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
     return tot < kMergeElems ? pmerge : S;
   };
 
+  // ---- what acp_compress_noalloc's limit is held against: part of that call's interface, stated
+  // there, and independent of the chunks that the kernels take.  A matrix counts
+  // ceil(n / rows) ceil(m / cols) cols r floats.
+  auto whole_words = [&](int64_t m, int64_t off, int64_t offp, int64_t offq) {
+    return r == 4 && m <= 5120 && (m | off | offp | offq) % 4 == 0;
+  };
+  auto row_class = [](int64_t m) { return m <= 64 ? 0 : m <= 128 ? 1 : m <= 256 ? 2 : m <= 512 ? 3 : 4; };
+  int64_t word_elems[5] = {0, 0, 0, 0, 0};  // elements of such matrices of the model, by row_class
+  for (const BucketPlan& bk : plan.buckets)
+    for (size_t k = 0; k < bk.tids.size(); ++k) {
+      const TensorPlan& t = plan.tensors[bk.tids[k]];
+      if (t.compressed && whole_words(t.m, bk.grad_off[k], bk.fac_off_p[k], bk.fac_off_q[k]))
+        word_elems[row_class(t.m)] += t.n * t.m;
+    }
+  auto limit_floats = [&](int64_t n, int64_t m, int64_t off, int64_t offp, int64_t offq) {
+    const int64_t most = std::max<int64_t>(1, (int64_t(1) << 28) / m);
+    int64_t rows = std::min<int64_t>(most, r >= 128 ? 2048 : r >= 8 ? 512 : 256), cols = 32;
+    if (r < 8) {
+      cols = (m | off) % 4 == 0 ? 1024 : 256;
+      int64_t c = cdiv(n, 4);
+      if (whole_words(m, off, offp, offq)) {
+        const int64_t w = std::min<int64_t>(m, 1024);
+        c = std::max<int64_t>(2048, word_elems[row_class(m)] / 1024) / w / 16 * 16;
+      }
+      rows = std::min(rows, std::max<int64_t>(16, c));
+    }
+    return align_up(cdiv(n, rows) * cdiv(m, cols) * cols * r, kSlotAlign);
+  };
+
   // ---- per-tensor device descriptors and state regions
   int64_t e_floats = 0, fac_floats = 0, gpart = 0, qpart = 0, fpart = 0;
   for (int32_t b = 0; b < static_cast<int32_t>(plan.buckets.size()); ++b) {
@@ -251,21 +280,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       if (bk.mats.empty()) bk.qpart_base = qpart;
       qpart += align_up(int64_t(d.q_chunks) * ncb * d.q_cb * r, kSlotAlign);
       bk.qpart_floats = qpart - bk.qpart_base;
-      // The limit of acp_compress_noalloc is part of its interface and does not follow the split of the
-      // sums: partials of chunks of 2048 rows from kBlockedRank on and 512 below; up to rank 4 of
-      // the chunks above where rows are 16-byte words of at most 5120 columns at rank 4, else of
-      // kQRows rows (a quarter of a small matrix's) over blocks of 1024 columns, 256 for other rows
-      int64_t lrows = d.q_rows, lcb = d.q_cb;
-      const bool words = t.m % 4 == 0 && d.grad_off % 4 == 0;
-      if (wide) {
-        lrows = std::max<int64_t>(1, std::min<int64_t>(r >= kBlockedRank ? 4 * kWideQRows : kWideQRows,
-                                                       (int64_t(1) << 30) / (t.m * 4)));
-      } else if (r != 4 || !words || d.fac_off_p % 4 || d.fac_off_q % 4 || t.m > 5120) {
-        lrows = std::max<int64_t>(1, std::min<int64_t>(kQRows, (int64_t(1) << 30) / (t.m * 4)));
-        lrows = std::min<int64_t>(lrows, std::max<int64_t>(16, cdiv(t.n, 4)));
-        lcb = words ? 1024 : 256;
-      }
-      bk.limit_floats += align_up(cdiv(t.n, lrows) * cdiv(t.m, lcb) * lcb * r, kSlotAlign);
+      bk.limit_floats += limit_floats(t.n, t.m, d.grad_off, d.fac_off_p, d.fac_off_q);
       d.fpart = fpart;
       if (bk.mats.empty()) bk.fpart_base = fpart;
       if (wide) {  // the Q-step's parts; from kSplitRank on the P-step's (a row of one part has none)

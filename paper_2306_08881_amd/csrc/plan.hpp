@@ -30,7 +30,7 @@ struct BucketPlan {
   int64_t qpart_base = 0;             // first Q-step partial of the bucket's matrices (floats)
   int64_t qpart_floats = 0;           // Q-step partials of the bucket's matrices (floats)
   int64_t fpart_base = 0, fpart_floats = 0;  // the same of its fine partials
-  int64_t limit_floats = 0;           // what acp_compress_noalloc's limit is held against
+  int64_t limit_floats = 0;           // what acp_compress_noalloc's limit is held against (see acp.h)
   std::vector<int32_t> mats, vecs;    // members by kind
   bool xhold = false;                 // it has a matrix whose P-step leaves X in the arena
   std::vector<Launch> compress[2];    // [0] even step (Q-step), [1] odd step (P-step)

@@ -298,14 +298,78 @@ def test_noalloc_refuses_buckets_past_the_static_scratch(lib):
 
 @pytest.mark.parametrize("n,m,rank", [(60000, 1024, 256), (31000, 1025, 256), (28509, 1122, 4), (100000, 300, 1)])
 def test_noalloc_takes_buckets_whose_chunks_are_split_further(lib, n, m, rank):
-    """The limit of acp_compress_noalloc counts fixed row chunks (15 to 30 of 2048 rows at rank 256:
-    at most 30 MiB), whatever chunks the kernels take: the call gets past it to the unbound context."""
+    """The limit of acp_compress_noalloc counts its own row chunks (15 to 30 of 2048 rows at rank 256:
+    at most 30 MiB), not the shorter ones the kernels take: the call gets past it to the unbound
+    context."""
     st, ctx = _ctx(lib, [(n, m)], rank)
     assert st == L.ACP_OK
     try:
         assert lib.acp_compress_noalloc(ctx, 1, 0, 256, 256, None) == L.ACP_E_STATE
     finally:
         lib.acp_destroy(ctx)
+
+
+def _noalloc_count(lib, ctx, shapes, rank, b):
+    """Bytes that bucket b counts towards acp_compress_noalloc's limit, by the rule in acp.h."""
+    def rows_of(m):
+        return 0 if m <= 64 else 1 if m <= 128 else 2 if m <= 256 else 3 if m <= 512 else 4
+
+    def matrices(k):
+        _, tids, go, po, qo, comp = _layout(lib, ctx, k)
+        for i, tid in enumerate(tids):
+            if comp[i]:
+                n, m = shapes[tid][0], int(np.prod(shapes[tid][1:]))
+                words = rank == 4 and m <= 5120 and m % 4 == go[i] % 4 == po[i] % 4 == qo[i] % 4 == 0
+                yield n, m, int(go[i]), words
+
+    total = [0] * 5
+    for k in range(lib.acp_num_buckets(ctx)):
+        for n, m, _, words in matrices(k):
+            total[rows_of(m)] += n * m * words
+    count = 0
+    for n, m, off, words in matrices(b):
+        w = 32 if rank >= 8 else 1024 if m % 4 == off % 4 == 0 else 256
+        c = 2048 if rank >= 128 else 512
+        if rank < 8:
+            c = min(256, max(16, -(-n // 4)))
+        if words:
+            c = min(256, max(16, max(2048, total[rows_of(m)] // 1024) // min(m, 1024) // 16 * 16))
+        c = max(1, min(c, 2 ** 28 // m))
+        count += -(-(-(-n // c) * -(-m // w) * w * rank) // 64) * 64 * 4
+    return count
+
+
+def test_noalloc_limit_is_the_one_of_the_header(lib):
+    """Every bucket of drawn models (alone and beside others, whole 16-byte words and ragged) is taken
+    or refused as acp.h says; the limit's message states the count."""
+    rng = np.random.default_rng(5)
+    taken = {True: 0, False: 0}
+    models = [([(60000, 1028)], 4), ([(70000, 1028)], 4), ([(60000, 1028), (300000, 1029)], 4),
+              ([(60000, 1028), (300000, 1032)], 4), ([(28509, 1122)], 4), ([(100000, 300)], 1), ([(100, 3000000)], 1),
+              ([(60000, 1024)], 256), ([(31000, 1025)], 256)]
+    while len(models) < 120:
+        rank = int(rng.choice([1, 2, 4, 4, 4, 8, 32, 64, 128, 256]))
+        shapes = []
+        for _ in range(int(rng.integers(1, 5))):
+            n, m = (int(2.0 ** rng.uniform(1, 18)) for _ in range(2))
+            m = m if rng.random() < 0.5 else -(-m // 4) * 4
+            shapes.append((n, m) if rng.random() < 0.8 and n * m < 2 ** 28 else (n,))
+        models.append((shapes, rank))
+    for shapes, rank in models:
+        st, ctx = _ctx(lib, shapes, rank)
+        assert st == L.ACP_OK
+        try:
+            for b in range(lib.acp_num_buckets(ctx)):
+                count = _noalloc_count(lib, ctx, shapes, rank, b)
+                got = lib.acp_compress_noalloc(ctx, 1, b, 256, 256, None)
+                # a bucket within the limit gets past it to the unbound context
+                assert got == (L.ACP_E_STATE if count <= 32 << 20 else L.ACP_E_UNSUPPORTED), (shapes, rank, b, count)
+                if got == L.ACP_E_UNSUPPORTED:
+                    assert f" {count} bytes" in lib.acp_last_error(ctx).decode()
+                taken[got == L.ACP_E_STATE] += 1
+        finally:
+            lib.acp_destroy(ctx)
+    assert taken[True] > 50 and taken[False] > 4, taken
 
 
 def test_method_specific_calls_refused_on_the_other_method(lib):
