@@ -16,9 +16,9 @@
 //             factor that the next step orthogonalises.
 //   gpart     fp64 Gram partial sums, r x r per slice of factor rows (factors of more than one
 //             slice only).
-//   qpart     fp32 Q-step partial products, per row chunk: m_pad x r (in a P-step of rows longer
-//             than kFusedCols, the column blocks' shares of P: n x r each).
-//   fpart     fp32, ranks 8..32: Q-step partials of the lists that split row chunks further.
+//   qpart     fp32 partial products of a compress call, dead after it: of a Q-step, per row chunk
+//             (or, in lists that split the chunks, per part) m_pad x r; of a P-step that splits
+//             rows, per column block, chunk or part n x r.
 //   tables    MatDesc[], VecDesc[], Tile[] for every launch.
 // No kernel communicates across workgroups: every reduction that spans workgroups is
 // finished by a later kernel in the same stream.
@@ -57,8 +57,7 @@ struct MatDesc {
   int64_t p_slot, q_slot, ph_slot, qh_slot, ql_slot, pl_slot;  // float offsets in the factor region
   int64_t w_slot;     // double offset in the W region
   int64_t gpart;      // double offset in the Gram-partial region
-  int64_t qpart;      // float offset in the Q-partial region
-  int64_t fpart;      // float offset in the fine-partial region (Q-step, ranks 8..32)
+  int64_t qpart;      // float offset in the partial-product region
   int32_t n, m;
   int32_t q_rows;     // rows per Q-step row chunk
   int32_t q_chunks;   // number of Q-step row chunks
@@ -241,8 +240,7 @@ struct KArgs {
   float* fac;           // factor region
   double* w;            // W region
   double* gpart;        // Gram partials
-  float* qpart;         // Q-step partials
-  float* fpart;         // fine partials
+  float* qpart;         // partial products
   const MatDesc* mats;
   const VecDesc* vecs;
   const Tile* tiles;    // this launch's tiles

@@ -96,7 +96,6 @@ acp::KArgs base_args(const acp_ctx* c) {
   a.w = reinterpret_cast<double*>(d + p.off_w);
   a.gpart = reinterpret_cast<double*>(d + p.off_gpart);
   a.qpart = reinterpret_cast<float*>(d + p.off_qpart);
-  a.fpart = reinterpret_cast<float*>(d + p.off_fpart);
   a.mats = reinterpret_cast<const acp::MatDesc*>(d + p.off_mats);
   a.vecs = reinterpret_cast<const acp::VecDesc*>(d + p.off_vecs);
   a.ef = p.ef ? 1 : 0;
@@ -252,10 +251,10 @@ const acp::Launch* leading_apply(const acp_ctx* c, const std::vector<acp::Launch
 }
 
 // acp_compress and acp_compress_noalloc: checks, then the bucket's compress launches.  `scratch`,
-// when not null, takes the Q-step partials instead of the state block: the kernels address partial
-// k of a matrix as qpart + MatDesc::qpart + k (fine ones likewise) and the bucket's start at
-// qpart_base, so the base handed to them puts those at the start of the scratch.  Partials that do
-// not fit it stay in the state block's own region.
+// when not null, takes the partial products instead of the state block: the kernels address partial
+// k of a matrix as qpart + MatDesc::qpart + k and the bucket's start at qpart_base, so the base
+// handed to them puts those at the start of the scratch.  Partials that do not fit it stay in the
+// state block's own region.
 acp_status compress_bucket(acp_ctx* c, int64_t step, int32_t b, const float* grad, float* factor_buf,
                            void* stream, float* scratch) {
   if (!c) return ACP_E_INVALID;
@@ -281,13 +280,9 @@ acp_status compress_bucket(acp_ctx* c, int64_t step, int32_t b, const float* gra
   const acp_status ds = check_device(c);
   if (ds != ACP_OK) return ds;
   acp::KArgs a = base_args(c);
-  if (scratch) {
-    auto based = [&](int64_t base) {
-      return reinterpret_cast<float*>(reinterpret_cast<uintptr_t>(scratch) - static_cast<uintptr_t>(base) * sizeof(float));
-    };
-    if (bk.qpart_floats * 4 <= acp::kScratchBytes) a.qpart = based(bk.qpart_base);
-    if (bk.fpart_floats * 4 <= acp::kScratchBytes) a.fpart = based(bk.fpart_base);
-  }
+  if (scratch && bk.qpart_floats * 4 <= acp::kScratchBytes)
+    a.qpart = reinterpret_cast<float*>(reinterpret_cast<uintptr_t>(scratch) -
+                                       static_cast<uintptr_t>(bk.qpart_base) * sizeof(float));
   a.base = b;
   a.src[0] = grad;
   a.dst[0] = factor_buf;

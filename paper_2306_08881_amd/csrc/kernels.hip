@@ -461,7 +461,7 @@ __global__ __launch_bounds__(kBlock) void k_qfin(KArgs a) {
   const int64_t ncb = (m + d.q_cb - 1) / d.q_cb;
   const int64_t stride = ncb * d.q_cb * RK;  // one row chunk of partials
   const int ne = qfin_entries(d.q_chunks);   // entries per tile
-  const float* part = FINE ? a.fpart + d.fpart : a.qpart + d.qpart;
+  const float* part = a.qpart + d.qpart;
   constexpr int PR = part_rows(RK), MP = max_parts(RK);
   const int parts = FINE ? (d.q_rows + PR - 1) / PR : 1;  // at most MP
   // chunk c's sum at entry offset o
@@ -577,7 +577,7 @@ hipError_t launch_rank(const Launch& l, const KArgs& args, hipStream_t s) {
     case K_FACT: hipLaunchKernelGGL(k_fact<RK>, grid, block, 0, s, args); break;
     case K_CHOL: hipLaunchKernelGGL(k_chol<RK>, grid, block, 0, s, args); break;
     case K_QFIN:
-      if constexpr (RK >= kWideRank) {
+      if constexpr (RK >= kWideRank && split_nested(RK)) {
         if (l.variant == kWideFine) {
           hipLaunchKernelGGL((k_qfin<RK, true>), grid, block, 0, s, args);
           break;

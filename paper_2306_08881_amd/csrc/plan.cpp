@@ -218,7 +218,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
   };
 
   // ---- per-tensor device descriptors and state regions
-  int64_t e_floats = 0, fac_floats = 0, gpart = 0, qpart = 0, fpart = 0;
+  int64_t e_floats = 0, fac_floats = 0, gpart = 0;
   for (int32_t b = 0; b < static_cast<int32_t>(plan.buckets.size()); ++b) {
     BucketPlan& bk = plan.buckets[b];
     bk.e_base = e_floats;
@@ -275,20 +275,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       // would pass kMaxExtent
       d.q_grp = !wide && t.m > 512 && kQGroup * d.q_rows * t.m * 4 <= kMaxExtent ? static_cast<int32_t>(kQGroup) : 1;
       d.q_chunks = static_cast<int32_t>(cdiv(t.n, d.q_rows));
-      const int64_t ncb = cdiv(t.m, d.q_cb);
-      d.qpart = qpart;
-      if (bk.mats.empty()) bk.qpart_base = qpart;
-      qpart += align_up(int64_t(d.q_chunks) * ncb * d.q_cb * r, kSlotAlign);
-      bk.qpart_floats = qpart - bk.qpart_base;
       bk.limit_floats += limit_floats(t.n, t.m, d.grad_off, d.fac_off_p, d.fac_off_q);
-      d.fpart = fpart;
-      if (bk.mats.empty()) bk.fpart_base = fpart;
-      if (wide) {  // the Q-step's parts; from kSplitRank on the P-step's (a row of one part has none)
-        const int64_t pp = r >= kSplitRank ? cdiv(t.m, split_part(static_cast<int>(r))) : 1;
-        fpart += align_up(std::max(pp > 1 ? pp * t.n * r : 0, int64_t(d.q_chunks) * cdiv(d.q_rows, part_rows(static_cast<int>(r))) * ncb * d.q_cb * r),
-                          kSlotAlign);
-      }
-      bk.fpart_floats = fpart - bk.fpart_base;
       d.bucket = b;
       // factor rows per Gram slice: at r <= 8 up to 5120 (one slice, and no K_CHOL, for
       // factors of at most that many rows; where nothing runs beside it, as in Power-SGD's second
@@ -456,6 +443,31 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
         for (int32_t i = 0; i < l.ntiles; ++i) n += plan.tiles[l.tile_off + i].kind != T_VEC;
     return n;
   };
+  // whether the sums of a parity's compress step have parts that tiles can take one by one (at rank 256
+  // every list does)
+  auto has_parts = [&](int32_t par) { return (par == 0 || r >= kSplitRank) && split_nested(static_cast<int>(r)); };
+  // columns of a P-step tile
+  auto p_cols = [&](bool fine) -> int64_t {
+    const int rk = static_cast<int>(r);
+    return r < kSplitRank ? kWideChunk : fine || !split_nested(rk) ? split_part(rk) : kMaxCols;
+  };
+  // floats of partial products per matrix: the most that a list in use writes
+  std::vector<int64_t> need(plan.mats.size(), 0);
+  auto uses_form = [&](const BucketPlan& bk, int32_t par, bool fine) {
+    const int64_t pr = part_rows(static_cast<int>(r)), cw = p_cols(fine);
+    for (int32_t mi : bk.mats) {
+      const MatDesc& d = plan.mats[mi];
+      int64_t rows;  // of r floats
+      if (par == 1) {
+        rows = d.m > cw ? cdiv(d.m, cw) * d.n : 0;
+      } else {
+        const int64_t last = d.n - int64_t(d.q_chunks - 1) * d.q_rows;  // rows of the last chunk
+        const bool parts = fine && has_parts(par);
+        rows = (parts ? (d.q_chunks - 1) * cdiv(d.q_rows, pr) + cdiv(last, pr) : d.q_chunks) * align_up(d.m, d.q_cb);
+      }
+      need[mi] = std::max(need[mi], rows * r);
+    }
+  };
   auto recon_tiles = [&](const BucketPlan& bk) {  // decompress tiles of kWideRCols columns
     int64_t n = 0;
     for (const Launch& l : bk.recon[0][0])
@@ -473,7 +485,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       Launch l = sink.begin(K_APPLY, 1);
       apply_tiles(bk.mats, true);
       sink.end(l, L);
-      const int64_t cw = r < kSplitRank ? kWideChunk : fine || !split_nested(rk) ? split_part(rk) : kMaxCols;
+      const int64_t cw = p_cols(fine);
       const int64_t rows = r < kSplitRank ? 32 : split_fix(rk);
       l = sink.begin(K_WPSTEP, 0);
       for (int32_t mi : bk.mats) {
@@ -511,13 +523,16 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       sink.end(l, L);
       qfin_launch(bk, L, true, fine ? kWideFine : 0);  // the vectors packed by the finish launch's workgroups
     };
-    for (const bool fine : {false, true}) {
-      p_list((fine ? bk.fine : bk.coarse)[1], fine);
-      q_list((fine ? bk.fine : bk.coarse)[0], fine);
-    }
     for (int32_t par = 0; par < 2; ++par) {
-      bk.is_fine[par] = main_tiles(bk.coarse[par]) < full_tiles;
-      bk.compress[par] = (bk.is_fine[par] ? bk.fine : bk.coarse)[par];
+      auto list = [&](std::vector<Launch>& L, bool fine) { par == 1 ? p_list(L, fine) : q_list(L, fine); };
+      list(bk.coarse[par], false);
+      if (has_parts(par))
+        list(bk.fine[par], true);
+      else
+        bk.fine[par] = bk.coarse[par];
+      const bool fine = main_tiles(bk.coarse[par]) < full_tiles;
+      bk.compress[par] = (fine ? bk.fine : bk.coarse)[par];
+      uses_form(bk, par, fine);
     }
     // -- decompress: factor tiles and vectors, the Gram partials' sum, (row block, 1024-column group)
     // tiles, and beside those the Cholesky
@@ -948,6 +963,8 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
         int64_t nt = 0, nr = 0;
         for (int32_t b = b0; b < b1; ++b) nt += main_tiles(plan.buckets[b].coarse[par]), nr += recon_tiles(plan.buckets[b]);
         const bool fine = nt < full_tiles;
+        if (wide)
+          for (int32_t b = b0; b < b1; ++b) uses_form(plan.buckets[b], par, fine);
         const int32_t rw = nr < kWideRFull ? 1 : 0;
         gc[par] = merge(b0, b1, [par, wide, fine](const BucketPlan& bk) -> const std::vector<Launch>& {
           return !wide ? bk.compress[par] : fine ? bk.fine[par] : bk.coarse[par];
@@ -967,6 +984,21 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
     }
   }
 
+  // ---- partial products: every compress list of a matrix, of its bucket's calls and of the group's,
+  // uses the same place
+  int64_t qpart = 0;
+  for (BucketPlan& bk : plan.buckets) {
+    bk.qpart_base = qpart;
+    for (int32_t mi : bk.mats) {
+      MatDesc& d = plan.mats[mi];
+      d.qpart = qpart;
+      // up to rank 4 a wide row's shares of P take less than its Q-step partials
+      const int64_t floats = wide ? need[mi] : int64_t(d.q_chunks) * align_up(d.m, d.q_cb) * r;
+      qpart += align_up(floats, kSlotAlign);
+    }
+    bk.qpart_floats = qpart - bk.qpart_base;
+  }
+
   // ---- region offsets (bytes)
   auto a256 = [](int64_t x) { return align_up(x, 256); };
   plan.e_floats = e_floats;
@@ -974,14 +1006,12 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
   plan.w_doubles = static_cast<int64_t>(plan.mats.size()) * r * r;
   plan.gpart_doubles = gpart;
   plan.qpart_floats = qpart;
-  plan.fpart_floats = fpart;
   int64_t off = 0;
   plan.off_e = off;     off = a256(off + e_floats * 4);
   plan.off_fac = off;   off = a256(off + fac_floats * 4);
   plan.off_w = off;     off = a256(off + plan.w_doubles * 8);
   plan.off_gpart = off; off = a256(off + gpart * 8);
   plan.off_qpart = off; off = a256(off + qpart * 4);
-  plan.off_fpart = off; off = a256(off + fpart * 4);
   plan.off_mats = off;  off = a256(off + static_cast<int64_t>(plan.mats.size() * sizeof(MatDesc)));
   plan.off_vecs = off;  off = a256(off + static_cast<int64_t>(plan.vecs.size() * sizeof(VecDesc)));
   plan.off_tiles = off; off = a256(off + static_cast<int64_t>(plan.tiles.size() * sizeof(Tile)));

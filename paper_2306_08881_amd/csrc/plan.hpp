@@ -27,17 +27,15 @@ struct BucketPlan {
   std::vector<int64_t> grad_off, fac_off_p, fac_off_q;
   int64_t grad_elems = 0, fac_elems_p = 0, fac_elems_q = 0;
   int64_t e_base = 0;                 // E arena offset of the bucket (floats)
-  int64_t qpart_base = 0;             // first Q-step partial of the bucket's matrices (floats)
-  int64_t qpart_floats = 0;           // Q-step partials of the bucket's matrices (floats)
-  int64_t fpart_base = 0, fpart_floats = 0;  // the same of its fine partials
+  int64_t qpart_base = 0;             // first partial product of the bucket's matrices (floats)
+  int64_t qpart_floats = 0;           // partial products of the bucket's matrices (floats)
   int64_t limit_floats = 0;           // what acp_compress_noalloc's limit is held against (see acp.h)
   std::vector<int32_t> mats, vecs;    // members by kind
   bool xhold = false;                 // it has a matrix whose P-step leaves X in the arena
   std::vector<Launch> compress[2];    // [0] even step (Q-step), [1] odd step (P-step)
-  // ranks 8 and up: the compress lists of whole sums, and split into parts; `compress` is one of the
-  // two (is_fine)
+  // ranks 8 and up: the compress lists of whole sums, and split into parts (the same where the kernel
+  // has no parts: P-steps below kSplitRank, rank 256); `compress` is one of the two
   std::vector<Launch> coarse[2], fine[2];
-  bool is_fine[2] = {false, false};
   // ranks 8 and up: the decompress lists with kWideRCols and with kWideRNarrow columns per tile
   std::vector<Launch> recon[2][2];
   std::vector<Launch> decompress[2];
@@ -64,9 +62,9 @@ struct Plan {
   std::vector<std::vector<Launch>> group_psgd_fact;
 
   // device state regions (byte offsets from the block base)
-  int64_t off_e = 0, off_fac = 0, off_w = 0, off_gpart = 0, off_qpart = 0, off_fpart = 0;
+  int64_t off_e = 0, off_fac = 0, off_w = 0, off_gpart = 0, off_qpart = 0;
   int64_t off_mats = 0, off_vecs = 0, off_tiles = 0, total_bytes = 0;
-  int64_t e_floats = 0, fac_floats = 0, w_doubles = 0, gpart_doubles = 0, qpart_floats = 0, fpart_floats = 0;
+  int64_t e_floats = 0, fac_floats = 0, w_doubles = 0, gpart_doubles = 0, qpart_floats = 0;
 };
 
 // Builds the plan; returns "" on success or an error text.

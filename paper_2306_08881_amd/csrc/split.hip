@@ -253,8 +253,9 @@ __global__ __launch_bounds__(64 * fix_blocks(RK) * rank_waves(RK), 2) void k_bst
   const bool m4 = (m & 3) == 0;
   // the tile's rows and first column; walked indices
   constexpr int PART = split_part(RK);
+  constexpr bool NEST = split_nested(RK);
   const int parts = (d.q_rows + PART - 1) / PART;  // of a Q-step chunk
-  const int part = PS ? (t.b >> 8) - 1 : a.variant == kWideFine ? t.a % parts : -1;  // -1: all of them
+  const int part = PS ? (t.b >> 8) - 1 : NEST && a.variant == kWideFine ? t.a % parts : -1;  // -1: all of them
   const int chunk = PS || part < 0 ? t.a : t.a / parts;
   const int64_t r0 = PS ? t.a : static_cast<int64_t>(chunk) * d.q_rows + (part > 0 ? part * PART : 0);
   const int64_t c0 = PS ? (part > 0 ? static_cast<int64_t>(part) * PART : 0) : static_cast<int64_t>(t.b) * FIX;
@@ -315,7 +316,6 @@ __global__ __launch_bounds__(64 * fix_blocks(RK) * rank_waves(RK), 2) void k_bst
       const float x[8] = {p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w};
       rs[s] = split8(x);
     }
-  constexpr bool NEST = split_nested(RK);
   v16f acc[NR], tot[NEST ? NR : 1];  // the sum of the current part, of the parts before it
 #pragma unroll
   for (int kb = 0; kb < NR; ++kb) {
@@ -403,14 +403,14 @@ __global__ __launch_bounds__(64 * fix_blocks(RK) * rank_waves(RK), 2) void k_bst
   float *o1, *o2 = nullptr;
   if constexpr (PS) {
     if (part >= 0) {
-      o1 = a.fpart + d.fpart + (static_cast<int64_t>(part) * n + r0 + i) * RK;
+      o1 = a.qpart + d.qpart + (static_cast<int64_t>(part) * n + r0 + i) * RK;
     } else {
       o1 = dst_of(a, d.bucket) + d.fac_off_p + (r0 + i) * RK;
       o2 = a.fac + d.pl_slot + (r0 + i) * RK;
     }
   } else {
     const int64_t ncb = (m + d.q_cb - 1) / d.q_cb;
-    o1 = (part >= 0 ? a.fpart + d.fpart : a.qpart + d.qpart) + static_cast<int64_t>(t.a) * ncb * d.q_cb * RK + (c0 + i) * RK;
+    o1 = a.qpart + d.qpart + static_cast<int64_t>(t.a) * ncb * d.q_cb * RK + (c0 + i) * RK;
   }
   typedef float v4u_f __attribute__((ext_vector_type(4), aligned(4)));  // the factor buffer is 4-byte aligned
 #pragma unroll

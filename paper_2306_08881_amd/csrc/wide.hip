@@ -242,7 +242,7 @@ __global__ __launch_bounds__(kBlock) void k_wpfin(KArgs a) {
   constexpr int CH = RK < kSplitRank ? kWideChunk : split_part(RK);
   const int nc = (d.m + CH - 1) / CH;
   const int64_t stride = static_cast<int64_t>(d.n) * RK;  // one chunk's sums
-  const float* part = (RK < kSplitRank ? a.qpart + d.qpart : a.fpart + d.fpart) + e;
+  const float* part = a.qpart + d.qpart + e;
   constexpr int U = 4;  // sums requested at a time
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int c = 0; c < nc; c += U) {
@@ -425,7 +425,7 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
   for (int kb = 0; kb < NR; ++kb) q[kb] = tot[kb] + q[kb];
   const int64_t ncb = (m + d.q_cb - 1) / d.q_cb;
   const int64_t stride = ncb * d.q_cb * RK;  // one row chunk of partials
-  float* part = (fine ? a.fpart + d.fpart : a.qpart + d.qpart) + static_cast<int64_t>(t.a) * stride + c0 * RK;
+  float* part = a.qpart + d.qpart + static_cast<int64_t>(t.a) * stride + c0 * RK;
 #pragma unroll
   for (int kb = 0; kb < NR; ++kb) {
     const int rank = kb * 32 + li;
