@@ -38,8 +38,9 @@
  *
  * Sequencing: per bucket, steps run 1, 2, 3, ... and compress(t) must precede
  * decompress(t); anything else returns ACP_E_STEP and changes nothing.
- * Buckets are independent and may be processed on different streams; calls
- * on one bucket must be ordered on the caller's side.  A context is not
+ * Buckets are independent and may be processed on different streams (up to
+ * four: without any waiting between them, one also captured while others run);
+ * calls on one bucket must be ordered on the caller's side.  A context is not
  * thread-safe.  All argument, state and sequencing checks run on the host
  * before anything is enqueued.  Kernel launch failures return ACP_E_DEVICE;
  * asynchronous device faults surface at a later HIP call.
@@ -220,8 +221,8 @@ acp_status acp_compress_noalloc(acp_ctx *ctx, int64_t step, int32_t b, const flo
  * M_hat = P_t Q_t^T / p for every compressed tensor and raw/p for every vector into `out`
  * (device, grad_elems(b) floats; may alias the gradient bucket but not agg_factor), and keep the
  * aggregated factor as the next step's reused factor (Section IV-A, query reuse).
- * From rank 8 on the decompress kernel runs on the context's second stream beside the
- * orthogonalisation of that factor (Section IV-A: its Gram, Cholesky and W, and the orthogonal
+ * From rank 8 on the decompress kernel runs on a second stream of the context (one of four: each of
+ * the caller's streams has its own) beside the orthogonalisation of that factor (Section IV-A: its Gram, Cholesky and W, and the orthogonal
  * factor the next compress multiplies by), forked from `stream` and joined back into it before the
  * call returns; the bucket's next compress then skips forming the orthogonal factor itself (it
  * forms it after a fresh bind, a state load, or with fresh draws).

@@ -28,10 +28,21 @@ struct acp_ctx {
   int device = -1;
   float* scratch = nullptr;     // the bound device's static Q-step scratch (acp_compress_noalloc)
   std::string scratch_err;      // why it is null after a bind
-  // a second stream (default priority) and fork / join events on the bound device: the P-step's
-  // class launches up to rank 4 after the first run there, beside it
-  hipStream_t side = nullptr;
-  hipEvent_t fork_ev = nullptr, join_ev = nullptr;
+  // second streams (default priority) with their fork and join events, on the bound device: part of a
+  // call's launches run there beside the others (see run).  A caller's stream keeps the side stream
+  // it used last, so that calls on up to kSides streams wait for nothing of each other's and may be
+  // captured while others run (BERT-base rank 128, buckets over four streams: 4803 us per two steps
+  // with one side stream, 3949 this way); further streams take over the one used longest ago.
+  struct Side {
+    hipStream_t stream = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
+    hipStream_t user = nullptr;  // the caller's stream, once used
+    uint64_t used = 0;           // when (0: never)
+  };
+  static constexpr int kSides = 4;
+  Side sides[kSides];
+  bool has_sides = false;
+  uint64_t side_uses = 0;
   std::vector<int64_t> last_step;   // per bucket: last completed step
   std::vector<int64_t> pending;     // per bucket: compressed step awaiting decompress (0 = none)
   std::vector<uint8_t> deferred;    // per bucket: E form of the arena (kExplicit, kHoldsF, kHoldsX)
@@ -124,6 +135,21 @@ bool small_pstep_run(const std::vector<acp::Launch>& launches, size_t i) {
   return k - i >= 2;
 }
 
+// The side stream of the caller's stream s.
+const acp_ctx::Side& side_of(acp_ctx* c, hipStream_t s) {
+  acp_ctx::Side* best = &c->sides[0];
+  for (acp_ctx::Side& x : c->sides) {
+    if (x.used != 0 && x.user == s) {
+      best = &x;
+      break;
+    }
+    if (x.used < best->used) best = &x;
+  }
+  best->user = s;
+  best->used = ++c->side_uses;
+  return *best;
+}
+
 // The decompress of ranks 8 to 256 (K_WRECON) runs on the side stream beside the chain that
 // orthogonalises the aggregated factor (its Gram, Cholesky and, as o.apply, the next compress's
 // orthogonal factor): the chain reads the aggregated factor and writes the factor slot, the Gram
@@ -141,7 +167,7 @@ struct RunOpts {
 };
 constexpr size_t npos = static_cast<size_t>(-1);
 size_t fork_at(const acp_ctx* c, const std::vector<acp::Launch>& launches, const RunOpts& o) {
-  if (!c->side || !o.apply) return npos;
+  if (!c->has_sides || !o.apply) return npos;
   for (size_t i = 0; i < launches.size(); ++i)
     if (launches[i].kernel == acp::K_WRECON) return c->plan.rank < acp::kSplitRank ? 0 : i;
   return npos;
@@ -161,6 +187,7 @@ acp_status run(const acp_ctx* c, const std::vector<acp::Launch>& launches, acp::
   const acp::Tile* tiles = reinterpret_cast<const acp::Tile*>(c->dev + c->plan.off_tiles);
   acp_ctx* mc = const_cast<acp_ctx*>(c);
   bool forked = false, pstep = false;  // the side stream has work; of a P-step run
+  const acp_ctx::Side* side = nullptr;
   if (o.applied) *o.applied = false;
   // one launch of the list (or o.apply) on stream st
   auto enqueue = [&](const acp::Launch& l, hipStream_t st) -> std::string {
@@ -182,7 +209,8 @@ acp_status run(const acp_ctx* c, const std::vector<acp::Launch>& launches, acp::
     return "";
   };
   auto fork = [&]() -> std::string {
-    if (hipEventRecord(c->fork_ev, s) != hipSuccess || hipStreamWaitEvent(c->side, c->fork_ev, 0) != hipSuccess)
+    side = &side_of(mc, s);
+    if (hipEventRecord(side->fork, s) != hipSuccess || hipStreamWaitEvent(side->stream, side->fork, 0) != hipSuccess)
       return "side stream fork failed";
     forked = true;
     return "";
@@ -191,7 +219,7 @@ acp_status run(const acp_ctx* c, const std::vector<acp::Launch>& launches, acp::
   auto join = [&]() -> std::string {
     if (!forked) return "";
     forked = pstep = false;
-    if (hipEventRecord(c->join_ev, c->side) != hipSuccess || hipStreamWaitEvent(s, c->join_ev, 0) != hipSuccess)
+    if (hipEventRecord(side->join, side->stream) != hipSuccess || hipStreamWaitEvent(s, side->join, 0) != hipSuccess)
       return "side stream join failed";
     return "";
   };
@@ -206,12 +234,12 @@ acp_status run(const acp_ctx* c, const std::vector<acp::Launch>& launches, acp::
     const bool p = l.kernel == acp::K_PFUSED;
     if (pstep && !p) msg = join();
     if (!msg.empty()) break;
-    if (p && !pstep && c->side && small_pstep_run(launches, i)) {
+    if (p && !pstep && c->has_sides && small_pstep_run(launches, i)) {
       msg = fork();
       pstep = msg.empty();
       if (msg.empty()) msg = enqueue(l, s);  // this first launch of the run stays on s
     } else {
-      msg = enqueue(l, pstep || (forked && l.kernel == acp::K_WRECON) ? c->side : s);
+      msg = enqueue(l, pstep || (forked && l.kernel == acp::K_WRECON) ? side->stream : s);
     }
   }
   if (msg.empty() && forked && !pstep && o.apply) {
@@ -224,11 +252,14 @@ acp_status run(const acp_ctx* c, const std::vector<acp::Launch>& launches, acp::
 }
 
 void release_side(acp_ctx* c) {
-  if (c->side) (void)hipStreamDestroy(c->side);
-  if (c->fork_ev) (void)hipEventDestroy(c->fork_ev);
-  if (c->join_ev) (void)hipEventDestroy(c->join_ev);
-  c->side = nullptr;
-  c->fork_ev = c->join_ev = nullptr;
+  for (acp_ctx::Side& x : c->sides) {
+    if (x.stream) (void)hipStreamDestroy(x.stream);
+    if (x.fork) (void)hipEventDestroy(x.fork);
+    if (x.join) (void)hipEventDestroy(x.join);
+    x = acp_ctx::Side{};
+  }
+  c->has_sides = false;
+  c->side_uses = 0;
 }
 
 int64_t checkpoint_payload(const acp::Plan& p) {
@@ -455,11 +486,14 @@ acp_status acp_bind_state(acp_ctx* c, void* device_ptr, int64_t bytes, void* str
   std::fill(c->pending.begin(), c->pending.end(), 0);
   std::fill(c->deferred.begin(), c->deferred.end(), 0);
   std::fill(c->phase.begin(), c->phase.end(), 0);
-  // the side stream, on the bound device
+  // the side streams, on the bound device
   release_side(c);
-  if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess ||
-      hipEventCreateWithFlags(&c->fork_ev, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&c->join_ev, hipEventDisableTiming) != hipSuccess) {
+  c->has_sides = true;
+  for (acp_ctx::Side& x : c->sides)
+    c->has_sides = c->has_sides && hipStreamCreateWithFlags(&x.stream, hipStreamNonBlocking) == hipSuccess &&
+                   hipEventCreateWithFlags(&x.fork, hipEventDisableTiming) == hipSuccess &&
+                   hipEventCreateWithFlags(&x.join, hipEventDisableTiming) == hipSuccess;
+  if (!c->has_sides) {
     release_side(c);
     c->dev = nullptr;
     return fail(c, ACP_E_DEVICE, "side stream creation failed");
