@@ -30,6 +30,13 @@
  *                       factor_elems_q(b) floats (Q_t, m x r, at fac_off_q[k]).
  *   output bucket b   : like the gradient bucket; receives M_hat_t (and raw vectors / p).
  *
+ * Arithmetic: products and their sums are fp32, Gram matrices and their Cholesky factors fp64.
+ * From rank 64 on the products multiply fp32 operands on the bf16 matrix cores, as six of the nine
+ * products of three-part splits that hold all 24 bits of a value of at least 2^-109 in magnitude
+ * (smaller ones to 2^-134), with the error of fp32 products.  Infinities and NaNs in a gradient
+ * give results that are not finite at every rank; from rank 64 on NaN where fp32 products would
+ * give an infinity.
+ *
  * Ownership: the caller owns every device buffer and stream.  The library
  * needs one device block for its state (the error E, the factors, small
  * workspaces and its launch tables); the caller allocates it (acp_state_bytes)

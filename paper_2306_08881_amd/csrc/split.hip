@@ -3,12 +3,14 @@
 // decompress 2 r against 4: from rank 64 on that is more than v_mfma_f32_32x32x2f32 does in the
 // time the bytes take (157 TFLOP/s against 6.5 TB/s: 24 flop per byte).  The rank-r products
 // therefore run on the bf16 matrix cores (16 times that rate) with fp32 operands split into three
-// bf16 parts, x = hi + mid + lo, each the nearest bf16 of what the earlier ones leave (2^-27 |x| is
-// left at most), and the six products hi hi, hi mid, mid hi, mid mid, hi lo, lo hi summed in fp32
-// accumulators; the three left out are below 2^-26 of the product.  Against 64 bits the results'
-// error is that of the fp32 matrix cores or less (see the measurements at the kernels).  A value
-// that is not finite gives results that are not finite, as in fp32, but NaN where fp32 may give an
-// infinity (infinity minus its own part).
+// bf16 parts, x = hi + mid + lo: hi is x cut off after eight bits (rounding it would take values past
+// the largest bf16 to infinity), mid the nearest bf16 of what that leaves and lo all of the rest, so
+// that the sum is x exactly down to 2^-109 in magnitude (below, what the bf16 subnormals hold: within
+// 2^-134).  The six products hi hi, hi mid, mid hi, mid mid, hi lo, lo hi are summed in fp32
+// accumulators; the three left out are below 2^-22 of the product, 2^-26 on average and of either
+// sign.  Against 64 bits the results' error is that of the fp32 matrix cores or less (see the
+// measurements at the kernels).  A value that is not finite gives results that are not finite, as in
+// fp32, but NaN where fp32 may give an infinity (infinity minus its own part).
 //
 // Both compress steps are one kernel (k_bstep).  A workgroup keeps 128 (rank 256: 64) "fixed"
 // indices i (P-step: rows, Q-step: columns), 32 per wave, one per lane, and walks the other index
@@ -60,17 +62,22 @@ __device__ inline Split split8(const float (&x)[8]) {
   Split s;
 #pragma unroll
   for (int e = 0; e < 8; e += 2) {
-    v2f r = {x[e], x[e + 1]};
+    // (the residual from the packed parts: from x itself, masked, the rank-256 decompress took 652 us
+    // instead of 613)
+    const uint32_t x0 = __builtin_bit_cast(uint32_t, x[e]), x1 = __builtin_bit_cast(uint32_t, x[e + 1]);
+    const v2bf hi = __builtin_bit_cast(v2bf, __builtin_amdgcn_perm(x1, x0, 0x07060302u));
+    const uint32_t wh = __builtin_bit_cast(uint32_t, hi);
+    v2f r = {x[e] - __builtin_bit_cast(float, wh << 16), x[e + 1] - __builtin_bit_cast(float, wh & 0xffff0000u)};
+    const v2bf mid = __builtin_convertvector(r, v2bf);
+    const uint32_t w = __builtin_bit_cast(uint32_t, mid);
+    r[0] -= __builtin_bit_cast(float, w << 16);
+    r[1] -= __builtin_bit_cast(float, w & 0xffff0000u);
+    const v2bf lo = __builtin_convertvector(r, v2bf);
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const v2bf b = __builtin_convertvector(r, v2bf);
-      s.p[q][e] = b[0];
-      s.p[q][e + 1] = b[1];
-      if (q < 2) {
-        const uint32_t w = __builtin_bit_cast(uint32_t, b);
-        r[0] -= __builtin_bit_cast(float, w << 16);
-        r[1] -= __builtin_bit_cast(float, w & 0xffff0000u);
-      }
+    for (int k = 0; k < 2; ++k) {
+      s.p[0][e + k] = hi[k];
+      s.p[1][e + k] = mid[k];
+      s.p[2][e + k] = lo[k];
     }
   }
   return s;

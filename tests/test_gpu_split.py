@@ -45,16 +45,17 @@ def test_powersgd_tile_edges():
 
 
 @pytest.mark.parametrize("rank", [64, 256])
-@pytest.mark.parametrize("scale", [1.0, 1e-12, 1e12])
-def test_error_is_that_of_fp32(rank, scale):
-    """One P-step and its decompress on a matrix whose entries span six orders of magnitude: the
-    split products are as close to 64 bits as fp32 products (CPU, fp32 accumulation) of the same
-    operands, within a factor of 1.5 for the order of the sums."""
+@pytest.mark.parametrize("scale,spread", [(1.0, 3), (1e-12, 3), (1e12, 3), (1e-30, 3), (1e33, 3), (1e-33, 0)])
+def test_error_is_that_of_fp32(rank, scale, spread):
+    """One P-step and its decompress on a matrix whose entries span six orders of magnitude (or one, at
+    a scale where the lowest parts of the split values are bf16 subnormals): the split products are as
+    close to 64 bits as fp32 products (CPU, fp32 accumulation) of the same operands, within a factor
+    of 1.5 for the order of the sums."""
     if not torch.cuda.is_available():
         pytest.fail("no GPU visible")
     n, m = 600, 1100
     rng = np.random.default_rng(4)
-    g = (scale * rng.standard_normal((n, m)) * 10.0 ** rng.uniform(-3, 3, (n, m))).astype(np.float32)
+    g = (scale * rng.standard_normal((n, m)) * 10.0 ** rng.uniform(-spread, spread, (n, m))).astype(np.float32)
     run = PU.Runner([(n, m)], rank)
     run.step(1, run.pack({0: g}))
     torch.cuda.synchronize()
@@ -65,6 +66,37 @@ def test_error_is_that_of_fp32(rank, scale):
         for k in range(a.shape[1]):  # one rounding per term, as a chain of fp32 multiply-adds has
             plain += a[:, k:k + 1] * b[k:k + 1, :]
         assert PU.rel_err(x, exact) <= 1.5 * PU.rel_err(plain, exact)
+
+
+@pytest.mark.parametrize("rank", [64, 128, 256])
+def test_largest_values(rank):
+    """Values between the largest bf16 and the largest fp32 stay finite; an infinity or NaN makes its
+    own row of P not finite and no other."""
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    n, m = 600, 700
+    rng = np.random.default_rng(6)
+    g = (1e30 * rng.standard_normal((n, m))).astype(np.float32)
+    g[rng.integers(0, n, 40), rng.integers(0, m, 40)] = np.float32(3.4e38)
+    g[rng.integers(0, n, 40), rng.integers(0, m, 40)] = np.float32(-3.395e38)
+
+    def p_of(grad):
+        run = PU.Runner([(n, m)], rank)
+        run.step(1, run.pack({0: grad}))
+        torch.cuda.synchronize()
+        return (run.factor_slice(1, 0).reshape(n, rank), run.out_slice(0).reshape(n, m),
+                run.ortho(1, 0).reshape(m, rank))
+
+    p, hat, q = p_of(g)
+    # fp32 sums of at most 700 products: 1e-5 is far above their error, far below a lost part's
+    assert PU.rel_err(p / 1e38, (g.astype(np.float64) / 1e38) @ q.astype(np.float64)) < 1e-5
+    assert PU.rel_err(hat / 1e38, (p.astype(np.float64) / 1e38) @ q.astype(np.float64).T) < 1e-5
+    bad = g.copy()
+    bad[17, 3], bad[130, 699] = np.inf, np.nan
+    pb = p_of(bad)[0]
+    rows = np.isfinite(pb).all(axis=1)
+    assert np.flatnonzero(~rows).tolist() == [17, 130] and not np.isfinite(pb[~rows]).any()
+    assert np.array_equal(pb[rows], p[rows])
 
 
 @pytest.mark.parametrize("rank", [32, 128, 256])
