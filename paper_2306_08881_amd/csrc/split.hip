@@ -82,14 +82,16 @@ __device__ inline Split split8(const float (&x)[8]) {
   }
   return s;
 }
-// D += A B with split operands, the small products first.
-__device__ inline v16f mfma6(const Split& a, const Split& b, v16f d) {
+// D += A B with split operands, the small products first; mfma5 without the high product.
+__device__ inline v16f mfma5(const Split& a, const Split& b, v16f d) {
   d = mfma(a.p[2], b.p[0], d);
   d = mfma(a.p[0], b.p[2], d);
   d = mfma(a.p[1], b.p[1], d);
   d = mfma(a.p[1], b.p[0], d);
-  d = mfma(a.p[0], b.p[1], d);
-  return mfma(a.p[0], b.p[0], d);
+  return mfma(a.p[0], b.p[1], d);
+}
+__device__ inline v16f mfma6(const Split& a, const Split& b, const v16f& d) {
+  return mfma(a.p[0], b.p[0], mfma5(a, b, d));
 }
 
 constexpr int kWalk = 32;   // walked indices per block
@@ -111,6 +113,7 @@ struct RowTile {
     for (int q = 0; q < 3; ++q) s.p[q] = *reinterpret_cast<const v8bf*>(&p[q][row * LD + k]);
     return s;
   }
+  __device__ v8bf high(int row, int k) const { return *reinterpret_cast<const v8bf*>(&p[0][row * LD + k]); }
 };
 // The transposed form [RK][32] for an operand whose lane holds rank l % 32 of a 32-rank block and
 // eight of the 32 rows, rows in the order of jrow: (s, h, e) at 16 s + 8 h + e.
@@ -477,9 +480,17 @@ __global__ __launch_bounds__(kBlock, RK == 64 ? 2 : 1) void k_brecon(KArgs a) {
     xb.put(bt[buf]);
     __syncthreads();
     xb.load(block_rsrc<RK>(B, j + kWalk, wcols));
+    // all small products before the high ones, whose large sum is then rounded RK / 16 times, not
+    // 6 RK / 16 (rank 256: error of M_hat 2.4e-7 one rank block after the other, 0.9e-7 this way;
+    // the fp32 matrix cores' was 1.5e-7)
     v16f o = zero16();
 #pragma unroll
-    for (int s = 0; s < NK; ++s) o = mfma6(bt[buf].get(li, 16 * s + 8 * h), as[s], o);
+    for (int s = 0; s < NK; ++s) o = mfma5(bt[buf].get(li, 16 * s + 8 * h), as[s], o);
+    // at rank 256 the high parts of B are read again, not held (BERT-base 3770 us per two steps, held
+    // 3900); at 128 holding them is faster by 0.3 % (BERT-large)
+    if constexpr (RK >= 256) wave_lds_fence();
+#pragma unroll
+    for (int s = 0; s < NK; ++s) o = mfma(bt[buf].high(li, 16 * s + 8 * h), as[s].p[0], o);
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       *reinterpret_cast<float4*>(st + li * kPitchM + 8 * q + 4 * h) =

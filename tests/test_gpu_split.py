@@ -66,6 +66,9 @@ def test_error_is_that_of_fp32(rank, scale, spread):
         for k in range(a.shape[1]):  # one rounding per term, as a chain of fp32 multiply-adds has
             plain += a[:, k:k + 1] * b[k:k + 1, :]
         assert PU.rel_err(x, exact) <= 1.5 * PU.rel_err(plain, exact)
+    # the decompress adds all small products first: r / 16 roundings of the large sum, each at most
+    # 2^-24 of it and of either sign, stay below two of them together
+    assert PU.rel_err(hat, p.astype(np.float64) @ q.astype(np.float64).T) <= 2.0 ** -23
 
 
 @pytest.mark.parametrize("rank", [64, 128, 256])
