@@ -384,18 +384,13 @@ __global__ __launch_bounds__(kBlock, RK >= kApplyMfmaRank ? 2 : 1) void k_apply(
       float* Y = a.fac + (q ? d.qh_slot : d.ph_slot) + row * RK;
       double x[RK];
       float y[RK];
-      if constexpr (RK % 4 == 0) {  // factor slots are 256-byte aligned: rows are 16-byte aligned
 #pragma unroll
-        for (int l = 0; l < RK; l += 4) {
-          const float4 v = *reinterpret_cast<const float4*>(X + l);
-          x[l] = v.x;
-          x[l + 1] = v.y;
-          x[l + 2] = v.z;
-          x[l + 3] = v.w;
-        }
-      } else {
-#pragma unroll
-        for (int l = 0; l < RK; ++l) x[l] = static_cast<double>(X[l]);
+      for (int l = 0; l < RK; l += 4) {  // factor slots are 256-byte aligned: rows are 16-byte aligned
+        const float4 v = *reinterpret_cast<const float4*>(X + l);
+        x[l] = v.x;
+        x[l + 1] = v.y;
+        x[l + 2] = v.z;
+        x[l + 3] = v.w;
       }
       // y[k] = sum over l <= k of x[l] W[l][k], added in increasing l; by rows of W, each
       // row's entries loaded together
@@ -408,14 +403,9 @@ __global__ __launch_bounds__(kBlock, RK >= kApplyMfmaRank ? 2 : 1) void k_apply(
         for (int k = l; k < RK; ++k) acc[k] = fma(x[l], W[l * RK + k], acc[k]);
 #pragma unroll
       for (int k = 0; k < RK; ++k) y[k] = static_cast<float>(acc[k]);
-      if constexpr (RK % 4 == 0) {
 #pragma unroll
-        for (int k = 0; k < RK; k += 4)
-          *reinterpret_cast<float4*>(Y + k) = make_float4(y[k], y[k + 1], y[k + 2], y[k + 3]);
-      } else {
-#pragma unroll
-        for (int k = 0; k < RK; ++k) Y[k] = y[k];
-      }
+      for (int k = 0; k < RK; k += 4)
+        *reinterpret_cast<float4*>(Y + k) = make_float4(y[k], y[k + 1], y[k + 2], y[k + 3]);
     }
   }
 }

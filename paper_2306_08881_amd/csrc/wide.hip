@@ -77,7 +77,6 @@ __device__ inline void load_run(Rsrc r, uint32_t off, float* out) {
 template <int RK>
 __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a) {
   constexpr int KH = RK / 2;
-  constexpr int NR = RK > 32 ? RK / 32 : 1;  // 32-rank blocks of P (one MFMA block each)
   constexpr int LD = 33;  // padded LDS row: the transposed reads hit 32 different banks
   constexpr int CS = 32 * kWidePWaves;  // columns per step of the workgroup
   const Tile t = a.tiles[blockIdx.x];
@@ -129,18 +128,15 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
       }
     }
   };
-  // the block's factor operands: Ql rows (correction B) and Qh rows (product B, rank block kb)
-  auto load_ops = [&](int64_t c0, float* qa, float (*qb)[16]) {
+  // the block's factor operands: Ql rows (correction B) and Qh rows (product B)
+  auto load_ops = [&](int64_t c0, float* qa, float* qb) {
     const int64_t qcol = c0 + li;
     if (fform) load_run<KH>(Qlr, qcol < m ? u32(qcol * RK + KH * h) * 4u : kOut, qa);
 #pragma unroll
-    for (int kb = 0; kb < NR; ++kb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t col = c0 + drow(v, h);
-        const int rank = kb * 32 + li;
-        qb[kb][v] = bld1(Qhr, (col < m && rank < RK) ? u32(col * RK + rank) * 4u : kOut);
-      }
+    for (int v = 0; v < 16; ++v) {
+      const int64_t col = c0 + drow(v, h);
+      qb[v] = bld1(Qhr, (col < m && li < RK) ? u32(col * RK + li) * 4u : kOut);
+    }
   };
   // the waves' transposing tiles, two each; a wave's pair starts one float past the previous
   // wave's, so that the row reads of the X stores (four waves' tiles at once) spread over the banks
@@ -150,13 +146,11 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
   constexpr int SP = 32 * kWidePWaves + 4;  // staging tile row pitch (floats, 16-byte aligned rows)
   __shared__ __attribute__((aligned(16))) float st[32 * SP];
   float4 g[4], e[4];
-  float qa[KH], qb[NR][16];
+  float qa[KH], qb[16];
   load_block(cbeg, g, e);
   load_ops(cbeg + 32 * wave, qa, qb);
 
-  v16f p[NR];
-#pragma unroll
-  for (int kb = 0; kb < NR; ++kb) p[kb] = zero16();
+  v16f p = zero16();
   int buf = 0;
   // every wave takes the same number of steps (blocks past m: zero loads, dropped stores)
   for (int64_t cs = cbeg; cs < cend; cs += CS, buf ^= 1) {
@@ -200,33 +194,28 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
     }
 #pragma unroll
     for (int v = 0; v < 16; ++v) {  // P += X Qh: A = X (row, column), B = Qh (column, rank)
-      const float xa = tl[li * LD + drow(v, h)];
-#pragma unroll
-      for (int kb = 0; kb < NR; ++kb) p[kb] = mfma(xa, qb[kb][v], p[kb]);
+      p = mfma(tl[li * LD + drow(v, h)], qb[v], p);
     }
     load_ops(c0 + CS, qa, qb);
   }
 
-  // the waves' shares of P, added in wave order: entry (v, lane) of rank block kb
-  float* red = xt;  // kWidePWaves x 1024 floats per rank block (the transposing tiles are free)
+  // the waves' shares of P, added in wave order: entry (v, lane)
+  float* red = xt;  // kWidePWaves x 1024 floats (the transposing tiles are free)
   float* P = chunk < 0 ? dst_of(a, d.bucket) + d.fac_off_p : a.qpart + d.qpart + static_cast<int64_t>(chunk) * d.n * RK;
   float* Pl = a.fac + d.pl_slot;
+  __syncthreads();  // the last products have read the tiles
 #pragma unroll
-  for (int kb = 0; kb < NR; ++kb) {
-    __syncthreads();  // the last products have read the tiles (and the previous block's sums)
+  for (int v = 0; v < 16; ++v) red[wave * 1024 + v * 64 + lane] = p[v];
+  __syncthreads();
+  for (int en = tid(); en < 1024; en += kWideBlock * kWidePWaves) {
+    float sum = red[en];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) red[wave * 1024 + v * 64 + lane] = p[kb][v];
-    __syncthreads();
-    for (int en = tid(); en < 1024; en += kWideBlock * kWidePWaves) {
-      float sum = red[en];
-#pragma unroll
-      for (int q = 1; q < kWidePWaves; ++q) sum += red[q * 1024 + en];
-      const int v = en >> 6, ln = en & 63;
-      const int row = drow(v, ln >> 5), rank = kb * 32 + (ln & 31);
-      if (rank < RK && row < rows) {
-        P[(r0 + row) * RK + rank] = sum;
-        if (chunk < 0) Pl[(r0 + row) * RK + rank] = sum;
-      }
+    for (int q = 1; q < kWidePWaves; ++q) sum += red[q * 1024 + en];
+    const int v = en >> 6, ln = en & 63;
+    const int row = drow(v, ln >> 5), rank = ln & 31;
+    if (rank < RK && row < rows) {
+      P[(r0 + row) * RK + rank] = sum;
+      if (chunk < 0) Pl[(r0 + row) * RK + rank] = sum;
     }
   }
 }
@@ -278,7 +267,6 @@ __global__ __launch_bounds__(kBlock) void k_wpfin(KArgs a) {
 template <int RK>
 __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a) {
   constexpr int KH = RK / 2;
-  constexpr int NR = RK > 32 ? RK / 32 : 1;  // 32-rank blocks of Q (one MFMA block each)
   const Tile t = a.tiles[blockIdx.x];
   const MatDesc d = a.mats[t.idx];
   const int wave = __builtin_amdgcn_readfirstlane(tid() >> 6);
@@ -336,7 +324,6 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
   // the block's factor rows, Pl (correction A) and Ph (product B): 32 x RK contiguous floats each
   // (factor slots are 256-byte aligned), loaded once for the workgroup, one 16-byte word per
   // thread, into a factor tile beside the staging tile, from which every wave takes its operands
-  static_assert(NR == 1, "one 32-rank block below kSplitRank");
   constexpr int FP = RK + 4;        // factor tile row pitch (floats, 16-byte aligned rows)
   constexpr int FV = 32 * RK / 4;   // 16-byte words per block and factor
   const bool fw = tid() < FV;       // the thread has a word of the block
@@ -354,12 +341,7 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
   float4 g[4], e[4], fl, fh;
   load_block(0, g, e);
   load_fac(0, fl, fh);
-  v16f q[NR], tot[NR];  // the sum of the current part, of the parts before it
-#pragma unroll
-  for (int kb = 0; kb < NR; ++kb) {
-    q[kb] = zero16();
-    tot[kb] = zero16();
-  }
+  v16f q = zero16(), tot = zero16();  // the sum of the current part, of the parts before it
   int buf = 0;
   for (int rb = 0; rb < rows; rb += 32, buf ^= 1) {
     float* sb = st[buf];
@@ -394,7 +376,7 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const float pb = fph[drow(v, h) * FP + rk];
-        q[0] = mfma(x[v], li < RK ? pb : 0.f, q[0]);
+        q = mfma(x[v], li < RK ? pb : 0.f, q);
       }
     }
     __syncthreads();  // the waves stay on the same rows; every block's F is in the tile
@@ -413,26 +395,18 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
       }
     }
     if ((rb + 32) % kWideSubRows == 0 && rb + 32 < rows) {  // the part ends and another follows
-#pragma unroll
-      for (int kb = 0; kb < NR; ++kb) {
-        tot[kb] += q[kb];
-        q[kb] = zero16();
-      }
+      tot += q;
+      q = zero16();
     }
   }
   if (w == 0) return;  // a block past m has no partials
-#pragma unroll
-  for (int kb = 0; kb < NR; ++kb) q[kb] = tot[kb] + q[kb];
+  q = tot + q;
   const int64_t ncb = (m + d.q_cb - 1) / d.q_cb;
   const int64_t stride = ncb * d.q_cb * RK;  // one row chunk of partials
   float* part = a.qpart + d.qpart + static_cast<int64_t>(t.a) * stride + c0 * RK;
+  if (li < RK)
 #pragma unroll
-  for (int kb = 0; kb < NR; ++kb) {
-    const int rank = kb * 32 + li;
-    if (rank < RK)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) part[drow(v, h) * RK + rank] = q[kb][v];
-  }
+    for (int v = 0; v < 16; ++v) part[drow(v, h) * RK + li] = q[v];
 }
 
 // Decompress up to rank 32 with four waves per tile (32-row block t.a, group t.b of WC columns):
