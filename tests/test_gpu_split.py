@@ -102,13 +102,19 @@ def test_largest_values(rank):
     assert np.array_equal(pb[rows], p[rows])
 
 
-@pytest.mark.parametrize("rank", [32, 128, 256])
+def sums_shapes(rank):
+    """Enough of them that all-bucket launches fill the GPU (see test_plan_host.py)."""
+    return [(12000, 600), (77,), (600, 12000)] * (12 if rank == 64 else 6)
+
+
+@pytest.mark.parametrize("rank", [8, 16, 32, 64, 128, 256])
 def test_split_sums_agree_between_calls(rank):
     """Per-bucket calls, whose launches are too small to fill the GPU and split every sum into
-    parts, against all-bucket calls over enough buckets that they do not: the same bits."""
+    parts, against all-bucket calls over enough buckets that they do not (at rank 256 both take a
+    tile per part): the same bits."""
     if not torch.cuda.is_available():
         pytest.fail("no GPU visible")
-    shapes = [(12000, 600), (77,), (600, 12000)] * 6
+    shapes = sums_shapes(rank)
     rng = np.random.default_rng(2)
     base = {i: (0.02 * rng.standard_normal(s)).astype(np.float32) for i, s in enumerate(shapes[:3])}
 

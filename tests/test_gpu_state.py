@@ -161,9 +161,9 @@ def test_grouped_calls_over_several_launch_groups():
     assert nb > 64
 
 
-@pytest.mark.parametrize("rank", [16, 32, 64])
+@pytest.mark.parametrize("rank", [16, 32, 64, 128, 256])
 def test_mixed_calls_and_reload_in_place(rank):
-    """From rank 8 to 64 a decompress also forms the next compress's orthogonal factor and the
+    """From rank 8 on a decompress also forms the next compress's orthogonal factor and the
     context records it: per-bucket and all-bucket calls in alternation, and a state load into the
     same context (which must drop the record while the slots hold the early factor), continue
     bitwise like plain per-bucket calls."""

@@ -9,6 +9,7 @@ import subprocess
 import pytest
 
 import synthgrad as sg
+from tests.test_gpu_split import sums_shapes
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2306_08881_amd", "csrc")
@@ -54,6 +55,22 @@ int main() {
   };
   for (size_t b = 0; b < p.buckets.size(); ++b) show("bucket", b, p.buckets[b].compress[1]);
   for (size_t g = 0; g < p.group_compress.size(); ++g) show("group", g, p.group_compress[g][1]);
+  // from rank 8 on: whether a compress list splits its sums into parts (P-step: rows of several parts)
+  auto form = [&](const char* what, size_t i, int par, const std::vector<Launch>& L) {
+    for (const Launch& l : L) {
+      if (l.kernel != K_WPSTEP && l.kernel != K_WQSTEP) continue;
+      bool parts = l.kernel == K_WQSTEP && l.variant == kWideFine;
+      for (int32_t t = 0; t < l.ntiles && l.kernel == K_WPSTEP; ++t) {
+        const Tile& x = p.tiles[l.tile_off + t];
+        parts = parts || (x.kind != T_VEC && (x.b >> 8) != 0);
+      }
+      printf("form %s %d %d %d\n", what, int(i), par, int(parts));
+    }
+  };
+  for (int par = 0; par < 2; ++par) {
+    for (size_t b = 0; b < p.buckets.size(); ++b) form("bucket", b, par, p.buckets[b].compress[par]);
+    for (size_t g = 0; g < p.group_compress.size(); ++g) form("group", g, par, p.group_compress[g][par]);
+  }
   // the region of partial products, the ends of its uses in every compress list, per matrix its slot
   printf("partials %lld\n", (long long)p.qpart_floats);
   auto uses = [&](const std::vector<Launch>& L) {
@@ -136,3 +153,17 @@ def test_whole_sums_and_parts_share_one_region(plan, rank):
     elements = sum(math.prod(s) for s in shapes if len(s) > 1)
     (floats,) = (int(w[1]) for w in plan(shapes, rank) if w[0] == "partials")
     assert 4 * floats <= 1.05 * min(1, rank / 64) * elements
+
+
+@pytest.mark.parametrize("rank", [8, 16, 32, 64, 128, 256])
+def test_large_calls_take_whole_sums(plan, rank):
+    """The shapes of test_split_sums_agree_between_calls compare what it says they compare: buckets
+    that split their sums with a group that does not."""
+    forms = {}
+    for w in plan(sums_shapes(rank), rank):
+        if w[0] == "form":
+            forms.setdefault((w[1], int(w[3])), set()).add(int(w[4]))
+    # at rank 256 every list takes a tile per part, below 64 every P-step one per 1024 columns
+    assert forms["bucket", 0] == ({0} if rank == 256 else {1}) and forms["group", 0] == {0}
+    if 64 <= rank < 256:
+        assert forms["bucket", 1] == {1} and forms["group", 1] == {0}
