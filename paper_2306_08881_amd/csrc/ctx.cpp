@@ -281,6 +281,22 @@ const acp::Launch* leading_apply(const acp_ctx* c, const std::vector<acp::Launch
   return &compress[0];
 }
 
+// Whether any call of the context forks to a side stream (see run).
+bool forks(const acp_ctx* c) {
+  const acp::Plan& p = c->plan;
+  if (p.rank >= acp::kWideRank) return p.reuse && !p.psgd;  // the decompress
+  auto any = [](const std::vector<acp::Launch>& l) {
+    for (size_t i = 0; i < l.size(); ++i)
+      if (small_pstep_run(l, i)) return true;
+    return false;
+  };
+  for (const acp::BucketPlan& bk : p.buckets)
+    if (any(bk.compress[1])) return true;
+  for (const auto& g : p.group_compress)
+    if (any(g[1])) return true;
+  return false;
+}
+
 // acp_compress and acp_compress_noalloc: checks, then the bucket's compress launches.  `scratch`,
 // when not null, takes the partial products instead of the state block: the kernels address partial
 // k of a matrix as qpart + MatDesc::qpart + k and the bucket's start at qpart_base, so the base
@@ -488,12 +504,15 @@ acp_status acp_bind_state(acp_ctx* c, void* device_ptr, int64_t bytes, void* str
   std::fill(c->phase.begin(), c->phase.end(), 0);
   // the side streams, on the bound device
   release_side(c);
-  c->has_sides = true;
-  for (acp_ctx::Side& x : c->sides)
-    c->has_sides = c->has_sides && hipStreamCreateWithFlags(&x.stream, hipStreamNonBlocking) == hipSuccess &&
-                   hipEventCreateWithFlags(&x.fork, hipEventDisableTiming) == hipSuccess &&
-                   hipEventCreateWithFlags(&x.join, hipEventDisableTiming) == hipSuccess;
-  if (!c->has_sides) {
+  bool made = true;
+  if (forks(c)) {
+    for (acp_ctx::Side& x : c->sides)
+      made = made && hipStreamCreateWithFlags(&x.stream, hipStreamNonBlocking) == hipSuccess &&
+             hipEventCreateWithFlags(&x.fork, hipEventDisableTiming) == hipSuccess &&
+             hipEventCreateWithFlags(&x.join, hipEventDisableTiming) == hipSuccess;
+    c->has_sides = made;
+  }
+  if (!made) {
     release_side(c);
     c->dev = nullptr;
     return fail(c, ACP_E_DEVICE, "side stream creation failed");
