@@ -324,7 +324,7 @@ def compare_powersgd(acp, wl, shapes, gsets, fbuf, out, dev, stream, steps, warm
             "powersgd_compress_ms": round(p_c, 4), "powersgd_decompress_ms": round(p_d, 4),
             "powersgd_step_ms": round(p_s, 4),
             "compress_time_ratio": round(p_c / a_c, 3), "step_time_ratio": round(p_s / a_s, 3),
-            "bytes_per_compressed_element": {"acp": 16, "powersgd": 24},
+            "bytes_per_compressed_element": {"acp": 16, "powersgd": 20},
             "note": "events around each call group of every step (a pass of its own); Power-SGD's "
                     "compress is both halves (P product, orthogonalisation of the all-reduced P, Q "
                     "product), ACP-SGD's one product with the orthogonalisation of the reused factor"}
