@@ -139,11 +139,12 @@ enum KernelId : int32_t {
   K_CHOL,        // sum of a factor's Gram partials (more than one slice) -> W
   K_EMAT,        // materialise E into a bucket-shaped buffer
   K_VEC,         // pack raw vectors only
-  K_WPSTEP,      // P-step, ranks 8..32 (MFMA): X = M' written, P_loc = X Qh per 32-row tile
-  K_WQSTEP,      // Q-step, ranks 8..32 (MFMA): F = M' written, per-chunk partials of F^T Ph
-  K_WPFIN,       // P-step, ranks 8..32: P_loc = sum of K_WPSTEP's column chunks -> factor buffer and Pl
-  K_WRECON,      // decompress, ranks 8..32 (MFMA): M_hat = A B^T / p
-  K_WFACT,       // decompress, ranks 8..32: factor tiles and vectors / p
+  K_WPSTEP,      // P-step, ranks >= 8 (MFMA): X = M' written, P_loc = X Qh per row tile
+  K_WQSTEP,      // Q-step, ranks >= 8 (MFMA): F = M' written, per-chunk (or per-part) partials of F^T Ph
+  K_WPFIN,       // P-step, ranks >= 8: P_loc = sum of K_WPSTEP's column chunks (from kSplitRank on:
+                 // parts) -> factor buffer and Pl
+  K_WRECON,      // decompress, ranks >= 8 (MFMA): M_hat = A B^T / p
+  K_WFACT,       // decompress, ranks >= 8: factor tiles and vectors / p
   // tile-size classes of the narrow-row tiles up to rank 4 (rows of at most 512 columns: several
   // rows per wave); they run inside the K_PFUSED (S = 1), K_QSTEP and K_RECON4 launches
   K_PNARROW,
@@ -188,7 +189,7 @@ constexpr int32_t gram_parts(int32_t r) {
   return r >= kBlockedRank ? ((r / 64) * (r / 64 + 1) / 2 + 3) / 4 : 1;
 }
 constexpr int32_t kGsumEntries = 4096;  // Gram entries per K_GSUM tile
-constexpr int kWideBlock = 64;     // threads per workgroup of K_WPSTEP, K_WQSTEP, K_WRECON: one wave
+constexpr int kWideBlock = 64;     // threads per wave of K_WPSTEP and K_WQSTEP, ranks 8..32
 constexpr int kWideQCols = 32;     // K_WQSTEP column block (one MFMA block)
 constexpr int kWidePWaves = 4;     // ranks 8..32: waves of a K_WPSTEP workgroup (adjacent column blocks)
 constexpr int kWideQWaves = 4;     // ranks 8..32: waves of a K_WQSTEP workgroup (adjacent column blocks)

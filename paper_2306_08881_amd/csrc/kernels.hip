@@ -1,7 +1,7 @@
 // gfx950 kernels of the ACP-SGD compressor (arXiv 2306.08881, Algorithms 1 and 2) that every rank
 // shares: the orthogonalisation of ranks 8 and up, the Q-step finish, the factor tiles, the draws
 // and exports, and the launch dispatch.  The streaming kernels of ranks 1, 2 and 4 are in
-// lowrank.hip, the MFMA kernels of ranks 8 to 256 in wide.hip.
+// lowrank.hip, the MFMA kernels of ranks 8 to 32 in wide.hip, those of ranks 64 to 256 in split.hip.
 //
 // Every kernel runs 256-thread workgroups (4 waves of 64) over a table of tiles; one
 // workgroup per tile.  Workgroups never wait for each other: a reduction that spans

@@ -660,7 +660,7 @@ __global__ __launch_bounds__(kBlock) void k_pfin(KArgs a) {
 // before the previous group's F stores, so stores never hold up the next loads.  Each lane stores
 // its partial sums for K_QFIN (columns past m store zeros into the padded partial block).  XF: the
 // rows k_pwide takes, whose arena may hold X: F = M + X - P_loc Qh^T (a launch of their own: the
-// column rows of Qh would cost every row length the third wave per SIMD).
+// column rows of Qh take 20, 56 and 60 more registers at ranks 1, 2 and 4, and of rank 2 a wave per SIMD).
 template <int RK, bool XF>
 __global__ __launch_bounds__(kBlock) void k_qstep(KArgs a) {
   constexpr int U = 8;  // rows per group

@@ -410,11 +410,10 @@ __global__ __launch_bounds__(kWideBlock * kWideQWaves, 2) void k_wqstep(KArgs a)
 }
 
 // Decompress up to rank 32 with four waves per tile (32-row block t.a, group t.b of WC columns):
-// at step k the waves compute the 32 x 32 blocks 4k ... 4k + 3 (wave w block 4k + w), as the
-// one-wave kernel does, and put them in an LDS tile of 32 rows x 128 columns; then all 256
-// threads store that tile with 16-byte nontemporal stores, thread t taking the four columns
-// 4 (t % 32) ... of rows t / 32 + 8 i, so one store instruction writes 512 contiguous bytes of
-// each of two rows (the one-wave kernel's stores write 128 bytes of a row at a time).  Two LDS
+// at step k the waves compute the 32 x 32 blocks 4k ... 4k + 3 (wave w block 4k + w) and put them
+// in an LDS tile of 32 rows x 128 columns; then all 256 threads store that tile with 16-byte
+// nontemporal stores, thread t taking the four columns 4 (t % 32) ... of rows t / 32 + 8 i, so
+// one store instruction writes 512 contiguous bytes of each of two rows.  Two LDS
 // tiles alternate, one barrier per step.  Rows past the tile fall outside the output resource;
 // columns past m are masked (the last step of a row length that is not a multiple of four stores
 // float by float: its last 16-byte word would reach into the next row).
