@@ -198,7 +198,16 @@ constexpr int kWideQRows = 512;    // K_WQSTEP rows per chunk (at most)
 // takes the narrower
 constexpr int kWideRCols = 1024, kWideRNarrow = 256;
 constexpr int64_t kWideRFull = 128;
-constexpr int kWideChunk = 1024;   // K_WPSTEP columns per tile (longer rows: K_WPFIN adds the chunks' sums)
+// K_WPSTEP, ranks 8..32: a row goes in chunks of kWideChunk columns, a tile each, whose sums K_WPFIN
+// adds.  A rest of less than half a chunk goes with the chunk before it, and a row of up to one and a
+// half chunks is one: the rest's short tile takes a slot for a fraction of a chunk's work, and one
+// chunk needs no K_WPFIN (hidden size 1088 at rank 32 bucket by bucket 1911 us per two steps with the
+// rest apart, 1764 this way; 1536, 3470 and 3378; two and a half chunks are better cut in three:
+// 2560 columns 1555 us, in two 1578)
+constexpr int kWideChunk = 1024;
+constexpr int32_t wide_chunks(int64_t m) {
+  return m <= kWideChunk * 3 / 2 ? 1 : static_cast<int32_t>((m + kWideChunk / 2) / kWideChunk);
+}
 // Ranks 8..32: a Q-step chunk's sum is that of its parts of kWideSubRows rows, in order; a list with
 // fewer than kWideFullTiles tiles (the workgroups that 256 CUs hold, three each, and a third more)
 // takes one tile per part (variant kWideFine of K_WQSTEP and K_QFIN)

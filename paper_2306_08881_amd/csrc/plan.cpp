@@ -446,20 +446,21 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
   // whether the sums of a parity's compress step have parts that tiles can take one by one (at rank 256
   // every list does)
   auto has_parts = [&](int32_t par) { return (par == 0 || r >= kSplitRank) && split_nested(static_cast<int>(r)); };
-  // columns of a P-step tile
-  auto p_cols = [&](bool fine) -> int64_t {
+  // tiles that share a row in a P-step
+  auto p_parts = [&](int64_t m, bool fine) -> int64_t {
     const int rk = static_cast<int>(r);
-    return r < kSplitRank ? kWideChunk : fine || !split_nested(rk) ? split_part(rk) : kMaxCols;
+    return r < kSplitRank ? wide_chunks(m) : fine || !split_nested(rk) ? cdiv(m, split_part(rk)) : 1;
   };
   // floats of partial products per matrix: the most that a list in use writes
   std::vector<int64_t> need(plan.mats.size(), 0);
   auto uses_form = [&](const BucketPlan& bk, int32_t par, bool fine) {
-    const int64_t pr = part_rows(static_cast<int>(r)), cw = p_cols(fine);
+    const int64_t pr = part_rows(static_cast<int>(r));
     for (int32_t mi : bk.mats) {
       const MatDesc& d = plan.mats[mi];
       int64_t rows;  // of r floats
       if (par == 1) {
-        rows = d.m > cw ? cdiv(d.m, cw) * d.n : 0;
+        const int64_t nc = p_parts(d.m, fine);
+        rows = nc > 1 ? nc * d.n : 0;
       } else {
         const int64_t last = d.n - int64_t(d.q_chunks - 1) * d.q_rows;  // rows of the last chunk
         const bool parts = fine && has_parts(par);
@@ -485,12 +486,11 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       Launch l = sink.begin(K_APPLY, 1);
       apply_tiles(bk.mats, true);
       sink.end(l, L);
-      const int64_t cw = p_cols(fine);
       const int64_t rows = r < kSplitRank ? 32 : split_fix(rk);
       l = sink.begin(K_WPSTEP, 0);
       for (int32_t mi : bk.mats) {
         const MatDesc& d = plan.mats[mi];
-        const int64_t nc = cdiv(d.m, cw);
+        const int64_t nc = p_parts(d.m, fine);
         for (int64_t s = 0; s < d.n; s += rows)
           for (int64_t c = 0; c < nc; ++c)
             plan.tiles.push_back(Tile{T_ROWS, mi, static_cast<int32_t>(s),
@@ -500,7 +500,7 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       sink.end(l, L);
       l = sink.begin(K_WPFIN, 0);
       for (int32_t mi : bk.mats)
-        if (plan.mats[mi].m > cw) row_tiles(mi, 4 * kBlock / r);
+        if (p_parts(plan.mats[mi].m, fine) > 1) row_tiles(mi, 4 * kBlock / r);
       sink.end(l, L);
     };
     // -- Q-step (even t): Ph = P W, (row chunk, column block) tiles (fine: of the chunks' parts),
@@ -804,11 +804,12 @@ std::string build_plan(Plan& plan, int32_t num_tensors, const int32_t* ndims, co
       case K_WPSTEP: {
         const double rows = t.b & 0xff, c = (t.b >> 8) - 1;
         const double cw = r < kSplitRank ? kWideChunk : split_part(static_cast<int>(r));
-        const double cols = c < 0 ? m : std::min<double>(cw, m - c * cw);
+        const bool last = r < kSplitRank && c + 1 == wide_chunks(d.m);
+        const double cols = c < 0 ? m : last ? m - c * cw : std::min<double>(cw, m - c * cw);
         return rows * cols * eb + rows * rr * 8.0 + (t.a == 0 ? cols * rr * 8.0 : 0.0);
       }
       case K_WPFIN:
-        return t.b * rr * 4.0 * (std::ceil(m / (r < kSplitRank ? kWideChunk : split_part(static_cast<int>(r)))) + 2.0);
+        return t.b * rr * 4.0 * (double(p_parts(d.m, true)) + 2.0);
       case K_WQSTEP: {
         const int32_t pr = part_rows(static_cast<int>(r));
         const int32_t parts = l.variant == kWideFine ? static_cast<int32_t>(cdiv(d.q_rows, pr)) : 1;

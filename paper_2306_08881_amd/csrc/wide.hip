@@ -70,7 +70,7 @@ __device__ inline void load_run(Rsrc r, uint32_t off, float* out) {
 // from the four waves' tiles and stores them as 16-byte vectors.  The four shares of P are added
 // in wave order through LDS at the end.  The next step's M and E are requested before the
 // current block's MFMAs, its factor rows after them.
-// A row longer than kWideChunk columns is cut into tiles of that many (t.b >> 8 is the chunk + 1),
+// A longer row is cut into chunks of kWideChunk columns (wide_chunks; t.b >> 8 is the chunk + 1),
 // whose sums of P go to the partial region for k_wpfin: a row walked whole is a serial chain of
 // steps of 2.2 us of latency each, and a bucket of 25 MiB at rank 32 has about 200 row tiles for
 // the GPU's 768 workgroup slots (BERT-base, rows of 3072 columns: 55 us a bucket, 30 by chunks).
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(kWideBlock * kWidePWaves, 2) void k_wpstep(KArgs a)
   const int64_t m = d.m, r0 = t.a;
   const int rows = t.b & 0xff, chunk = (t.b >> 8) - 1;  // chunk -1: all columns
   const int64_t cbeg = chunk > 0 ? static_cast<int64_t>(chunk) * kWideChunk : 0;
-  const int64_t cend = chunk >= 0 && cbeg + kWideChunk < m ? cbeg + kWideChunk : m;
+  const int64_t cend = chunk >= 0 && chunk + 1 < wide_chunks(m) ? cbeg + kWideChunk : m;
   const bool fform = deferred_of(a, d.bucket);
   const uint32_t row_bytes = u32(m) * 4u;
   const uint32_t ext = u32(rows) * row_bytes;
@@ -228,8 +228,7 @@ __global__ __launch_bounds__(kBlock) void k_wpfin(KArgs a) {
   const MatDesc d = a.mats[t.idx];
   if (tid() >= t.b * (RK / 4)) return;
   const int64_t e = static_cast<int64_t>(t.a) * RK + tid() * 4;
-  constexpr int CH = RK < kSplitRank ? kWideChunk : split_part(RK);
-  const int nc = (d.m + CH - 1) / CH;
+  const int nc = RK < kSplitRank ? wide_chunks(d.m) : (d.m + split_part(RK) - 1) / split_part(RK);
   const int64_t stride = static_cast<int64_t>(d.n) * RK;  // one chunk's sums
   const float* part = a.qpart + d.qpart + e;
   constexpr int U = 4;  // sums requested at a time

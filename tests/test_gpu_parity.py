@@ -121,6 +121,16 @@ def test_ragged_shapes_all_ranks(rank):
     _assert_ok(_custom(RAGGED, rank))
 
 
+# ranks 8 to 32: rows on both sides of one and a half and two and a half column chunks of the P-step
+CHUNKS = [(70, 1024), (33, 1025), (9,), (64, 1535), (40, 1536), (65, 1537), (35, 2048), (66, 2559), (34, 2560), (40, 2561)]
+
+
+@pytest.mark.parametrize("rank", [8, 32])
+def test_row_chunks(rank):
+    _require_gpu()
+    _assert_ok(_custom(CHUNKS, rank, steps=6))
+
+
 # rank 256 (the four waves of a workgroup split the rank; W in 2 x 2 blocks): ragged column
 # tails, row counts just past r, a factor of 2100 rows (two Q-step chunks, several Gram slices)
 RANK256 = [(257, 333), (2100, 300), (64,), (270, 1000)]
